@@ -154,9 +154,9 @@ size_t hydra_bwd_ds_bytes(const hydra_problem_t* p, int32_t kv_heads_per_pass);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): hydra_attn_bwd without the workspace
  * argument.  The workspace (plan, D, LSE*log2(e)) lives in a device array of the library,
- * one per GPU, of hydra_noalloc_scratch_bytes() = 32 MiB, held until the process ends; the
- * call allocates nothing.  Problems whose hydra_workspace_size() exceeds it are refused with
- * HYDRA_ERR_TOO_LARGE before any HIP call (32 MiB covers n_heads x Nq up to about 4M, e.g.
+ * one per GPU, held until the process ends; the call allocates nothing.  Problems whose D,
+ * LSE*log2(e), documents and tile plan exceed hydra_noalloc_scratch_bytes() = 32 MiB are
+ * refused with HYDRA_ERR_TOO_LARGE before any HIP call (32 MiB covers n_heads x Nq up to about 4M, e.g.
  * 16 heads x 256K rows).  Every call on a GPU uses that GPU's one array: calls that overlap
  * on one GPU (other streams, other threads) race and must be serialised by the caller.
  * Everything else (arguments, checks, results) is hydra_attn_bwd's, bit for bit. */

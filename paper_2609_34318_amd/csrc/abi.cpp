@@ -115,15 +115,18 @@ int upload_plan(const Problem& pr, const WsLayout& w, bool with_kv_items, void* 
   const size_t bytes = with_kv_items ? w.d_off : w.kitems_off;
   std::vector<char> img(bytes, 0);
   std::memcpy(img.data() + w.cu_off, pr.cu.data(), pr.cu.size() * sizeof(int32_t));
-  std::memcpy(img.data() + w.qitems_off, qitems->data(), qitems->size() * sizeof(int32_t));
+  auto put = [&](size_t off, const std::vector<int32_t>& v) {
+    std::memcpy(img.data() + off, v.data(), v.size() * sizeof(int32_t));
+  };
+  std::vector<int32_t> units, kbase, kmap32, krec;
   if (with_kv_items) {
-    std::memcpy(img.data() + w.kitems_off, kitems->data(), kitems->size() * sizeof(int32_t));
-    std::vector<int32_t> kbase, kmap32, krec;
     ds_tables(pr, *kitems, &kbase, &kmap32, &krec);
-    std::memcpy(img.data() + w.kbase_off, kbase.data(), kbase.size() * sizeof(int32_t));
-    std::memcpy(img.data() + w.kmap_off, kmap32.data(), kmap32.size() * sizeof(int32_t));
-    std::memcpy(img.data() + w.krec_off, krec.data(), krec.size() * sizeof(int32_t));
+    launch_units(pr, 1, *kitems, kbase, &units);
+    put(w.kitems_off, units);
+    put(w.krec_off, krec);
   }
+  launch_units(pr, 0, *qitems, kmap32, &units);
+  put(w.qitems_off, units);
   // Pageable source: the runtime has consumed `img` when the call returns.
   if (hipMemcpyAsync(ws, img.data(), bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return HYDRA_ERR_HIP;
   return HYDRA_OK;
@@ -178,10 +181,7 @@ AttnArgs base_args(const Problem& pr, const WsLayout& w, void* ws) {
   a.Dvec = reinterpret_cast<float*>(base + w.d_off);
   a.lse2 = reinterpret_cast<float*>(base + w.lse2_off);
   a.kitems = reinterpret_cast<const int*>(base + w.kitems_off);
-  a.kbase = reinterpret_cast<const int*>(base + w.kbase_off);
-  a.kmap32 = reinterpret_cast<const int*>(base + w.kmap_off);
   a.krec = reinterpret_cast<const int*>(base + w.krec_off);
-  a.n_docs = int(pr.cu.size()) - 1;
   a.H = pr.H;
   a.Hkv = pr.Hkv;
   a.grp = pr.H / pr.Hkv;
@@ -384,7 +384,7 @@ int hydra_attn_bwd_ds(const hydra_problem_t* p, const void* q, const void* k, co
 // each device's address comes from hipGetSymbolAddress, once per device, with that device
 // current.
 namespace {
-constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;  // 32 MiB
+constexpr size_t kNoAllocScratchBytes = kNoAllocLimitBytes + kNoAllocExtraBytes;
 static __device__ __align__(256) char scratch[kNoAllocScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -407,7 +407,7 @@ int scratch_ptr(void** out) {
 
 extern "C" {
 
-size_t hydra_noalloc_scratch_bytes(void) { return kNoAllocScratchBytes; }
+size_t hydra_noalloc_scratch_bytes(void) { return kNoAllocLimitBytes; }
 
 int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* k, const void* v,
                            const void* o_final, const float* lse_final, const void* d_o, float* dq_acc,
@@ -416,7 +416,7 @@ int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* 
     Problem pr;
     int rc = check_problem(p, &pr);
     if (rc != HYDRA_OK) return rc;
-    if (ws_layout(pr).total > kNoAllocScratchBytes) return HYDRA_ERR_TOO_LARGE;
+    if (noalloc_bytes(pr) > kNoAllocLimitBytes) return HYDRA_ERR_TOO_LARGE;
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws)) != HYDRA_OK) return rc;
     return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, ws,

@@ -2,7 +2,7 @@
 //   D_i = <dO_i, O_i>,  P = exp(S - LSE),  dV += P^T dO,  dS = P o (dO V^T - D),
 //   dK += scale dS^T Q,  dQ += scale dS K.
 // Three kernels:
-//   bwd_pre   D = rowsum(dO o O) and LSE * log2(e)                  (HBM-bound)
+//   bwd_pre   -D = -rowsum(dO o O) and LSE * log2(e)                (HBM-bound)
 //   bwd_dq    query-stationary: recomputes S^T and dP^T per key tile, accumulates dQ^T
 //   bwd_dkdv  key-stationary: recomputes S and dP per query tile, accumulates dK^T, dV^T
 // Splitting dQ from dK/dV recomputes S and dP once more but needs no atomics and is
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(const uint16_t* __restrict
     if (sub == 0) {
       const int row = (int)(rh / H), head = (int)(rh % H);
       const int64_t li = (int64_t)head * nq + row;
-      D[li] = acc;
+      D[li] = -acc;
       lse2[li] = lse[li] * LOG2E;
     }
   }
@@ -53,26 +53,26 @@ constexpr int DQ_STAGE = DQ_KBYTES + DQ_BK * DV * 2;  // 60 KB
 constexpr int DQ_NSTAGE = 2;  // measured faster than three stages
 constexpr int DQ_WAVES = 8;                           // 256 query rows per workgroup
 constexpr int DQ_COPY_WAVES = 4;                      // the 12 copies per column block split evenly over 4
-// copies per tile per copying wave: (3 (K) + 2 (V) column blocks) x 3
-constexpr int DQ_VMCNT_ONE_TILE = (DQK / 64 + DV / 64) * (DQ_BK / 8 / DQ_COPY_WAVES);
 
-__device__ __forceinline__ void dq_issue(lds_char* smem, const AttnArgs& a, const TileRanges kr, int t, int koff,
-                                         int voff, int wave) {
-  int row0, pos0, n;
-  tile_at(kr, t, DQ_BK, row0, pos0, n);
-  lds_char* dst = smem + (t % DQ_NSTAGE) * DQ_STAGE;
+__device__ __forceinline__ void dq_issue(lds_char* stage, const AttnArgs& a, const Tile k, int kv_head, int wave) {
   if (wave >= DQ_COPY_WAVES) return;  // wave-uniform
-  dma_tile<DQK, DQ_BK, DQ_COPY_WAVES>(dst, tile_rsrc(a.k, row0, n, a.k_s), koff, a.k_s, wave);
-  dma_tile<DV, DQ_BK, DQ_COPY_WAVES>(dst + DQ_KBYTES, tile_rsrc(a.v, row0, n, a.v_s), voff, a.v_s, wave);
+  const int koff = dma_lane_off<DQK>(a.k_s, kv_head, wave, lane_now());
+  const int voff = dma_lane_off<DV>(a.v_s, kv_head, wave, lane_now());
+  dma_tile<DQK, DQ_BK, DQ_COPY_WAVES>(stage, tile_rsrc(a.k, k.row0, k.n, a.k_s), koff, a.k_s, wave);
+  dma_tile<DV, DQ_BK, DQ_COPY_WAVES>(stage + DQ_KBYTES, tile_rsrc(a.v, k.row0, k.n, a.v_s), voff, a.v_s, wave);
 }
 
 __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[DQ_NSTAGE * DQ_STAGE];
+  // stage 0 | stage 1; before the loop the waves' Q, then dO rows from the start of stage 1,
+  // after it their outputs
+  constexpr int LDS_BYTES = DQ_STAGE + DQ_WAVES * own_bytes<DQK>();
+  static_assert(LDS_BYTES >= DQ_NSTAGE * DQ_STAGE && LDS_BYTES >= DQ_WAVES * ROWS_OUT_BYTES, "LDS");
+  __shared__ __attribute__((aligned(1024))) char smem_raw[LDS_BYTES];
   lds_char* smem = (lds_char*)smem_raw;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, known to the compiler
-  const int m = lane & 31, hh = lane >> 5;
+  const int m = lane & 31;
   int hl, item;
   xcd_head_item(blockIdx.x, a.q_heads, a.n_items, hl, item);
   const int head = a.q_head0 + hl;
@@ -80,48 +80,33 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
   const TileRanges kr = tile_ranges(it, DQ_BK);
   const int n_tiles = kr.nt;
   if (n_tiles == 0) return;  // uniform over the workgroup
-  const int q_row0 = it.row0, q_pos0 = it.pos0, q_n = it.n;
-
-  lds_clear<64 * DQ_WAVES>(smem, DQ_NSTAGE * DQ_STAGE, tid);
-  const int qi = wave * 32 + m;
-  const bool q_valid = qi < q_n;
-  const int pos_q = q_valid ? q_pos0 + qi : -1;
-  int lo_q = q_valid ? a.cu[doc_of(a.cu, a.n_docs, pos_q)] : 0;
-  // finish this load here: left pending, the tile loop would wait for all copies in flight
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(lo_q)::"memory");
-  const int lo_last = a.cu[doc_of(a.cu, a.n_docs, q_pos0 + q_n - 1)];
-  const float sl2 = a.scale * LOG2E;
-  const int64_t qrow = q_row0 + (q_valid ? qi : 0);
-  // invalid rows: LSE = +inf makes P = 0, D = 0 keeps dS = 0
-  float lse2 = q_valid ? a.lse2[(int64_t)head * a.nq + qrow] : INFINITY;
-  float Dq = q_valid ? a.Dvec[(int64_t)head * a.nq + qrow] : 0.f;
-  settle(lse2);
-  settle(Dq);
   const int kv_head = head / a.grp;  // grouped K/V heads: contiguous groups of query heads
-  const int koff = dma_lane_off<DQK>(a.k_s, kv_head, wave, lane);
-  const int voff = dma_lane_off<DV>(a.v_s, kv_head, wave, lane);
+  const float sl2 = a.scale * LOG2E;
 
+  // this wave's rows: [q_row0, q_row0 + q_n) at positions from q_pos0 on (q_n = 0: none)
+  const int q_n = min(32, max(it.n - 32 * wave, 0));
+  const int q_row0 = it.row0 + 32 * wave, q_pos0 = it.pos0 + 32 * wave;
+  const int q_last = q_n > 0 ? q_pos0 + q_n - 1 : -1;
+
+  lds_char* own = smem + DQ_STAGE + wave * own_bytes<DQK>();
+  own_rows_issue<DQK>(own, a.q, q_row0, q_n, a.q_s, head, lane);
+  Tile cur = tile_at(kr, 0, DQ_BK);
+  dq_issue(smem, a, cur, kv_head, wave);
+  // rows past the end repeat the last one (an empty wave the item's first row)
+  const int mc = q_n > 0 ? min(m, q_n - 1) : -32 * wave;
+  float lse2 = a.lse2[(int64_t)head * a.nq + q_row0 + mc];
+  float neg_D = a.Dvec[(int64_t)head * a.nq + q_row0 + mc];
+  const int lo_q = doc_edge<false>(a.cu, it.d0, it.d1, it.edge0, q_pos0 + mc);
+  const int lo_first = __builtin_amdgcn_readfirstlane(lo_q);
+  const int lo_last = __builtin_amdgcn_readlane(lo_q, 31);
+  settle(lse2);
+  settle(neg_D);
   bf16x8 qf[DQK / 16], df[DV / 16];
-  {
-    const uint16_t* qp = a.q + qrow * a.q_s + head * DQK + 8 * hh;
-    const uint16_t* dp = a.dO + (qrow * a.H + head) * DV + 8 * hh;
-#pragma unroll
-    for (int t = 0; t < DQK / 16; ++t) {
-      u32x4 u = {0u, 0u, 0u, 0u};
-      if (q_valid) u = ldg16(qp + 16 * t);
-      settle(u);
-      qf[t] = __builtin_bit_cast(bf16x8, u);
-    }
-#pragma unroll
-    for (int t = 0; t < DV / 16; ++t) {
-      u32x4 u = {0u, 0u, 0u, 0u};
-      if (q_valid) u = ldg16(dp + 16 * t);
-      settle(u);
-      df[t] = __builtin_bit_cast(bf16x8, u);
-    }
-  }
-  __syncthreads();  // LDS cleared before the first copy lands
-  for (int t = 0; t < DQ_NSTAGE - 1 && t < n_tiles; ++t) dq_issue(smem, a, kr, t, koff, voff, wave);
+  wait_dma();
+  own_rows_read<DQK>(own, lane, qf);
+  own_rows_issue<DV>(own, a.dO, q_row0, q_n, a.H * DV, head, lane);
+  wait_dma();
+  own_rows_read<DV>(own, lane, df);
 
   f32x16 acc[DQK / 32];
 #pragma unroll
@@ -131,16 +116,21 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
 
   for (int t = 0; t < n_tiles; ++t) {
     refresh(o);
-    int k_row0, kpos, kn;
-    tile_at(kr, t, DQ_BK, k_row0, kpos, kn);
-    // copies of tile t are done once at most the later tiles' copies issued so far (with
-    // two stages: none) are still in flight
-    if (DQ_NSTAGE > 2 && t + 1 < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DQ_VMCNT_ONE_TILE) : "memory");
-    else wait_dma();
+    const int kpos = cur.pos0, kn = cur.n;
+    lds_char* Ks = smem + (t % DQ_NSTAGE) * DQ_STAGE;
+    lds_char* Vs = Ks + DQ_KBYTES;
+    wait_dma();  // tile t's copies, the only ones in flight
+    if (kn < DQ_BK && wave < DQ_COPY_WAVES) {
+      clear_tail<DQK, DQ_BK, DQ_COPY_WAVES>(Ks, kn, wave, lane_now());
+      clear_tail<DV, DQ_BK, DQ_COPY_WAVES>(Vs, kn, wave, lane_now());
+    }
     barrier_lds();
-    if (t + DQ_NSTAGE - 1 < n_tiles) dq_issue(smem, a, kr, t + DQ_NSTAGE - 1, koff, voff, wave);
-    const lds_char* Ks = smem + (t % DQ_NSTAGE) * DQ_STAGE;
-    const lds_char* Vs = Ks + DQ_KBYTES;
+    if (t + 1 < n_tiles) {
+      cur = tile_at(kr, t + 1, DQ_BK);
+      dq_issue(smem + ((t + 1) % DQ_NSTAGE) * DQ_STAGE, a, cur, kv_head, wave);
+    }
+    // a wave none of whose rows sees the tile leaves the matrix cores to the others
+    if (kpos > q_last || kpos + kn <= lo_first) continue;
     const bool full = (kn == DQ_BK) && (lo_last <= kpos) && (kpos + DQ_BK - 1 <= q_pos0);
 
     static_for<DQ_BK / 32>([&](auto kb_) {
@@ -154,18 +144,20 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
       float ds[16];
       if (full) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) ds[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], sl2, -lse2)) * (dp[e] - Dq);
+        for (int e = 0; e < 16; ++e) ds[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], sl2, -lse2)) * (dp[e] + neg_D);
       } else {
         // key kpos + key(e) is visible iff lo_q <= it <= pos_q and key(e) < kn, i.e. iff
         // 0 <= base + c(e) < lim with base = kpos - lo_q + 32*kb + 8*hh; masked entries get
-        // exp2(-inf) = 0
-        const int base = kpos - lo_q + 32 * kb + 8 * hh;
-        const int lim = q_valid ? max(0, min(pos_q + 1, kpos + kn) - lo_q) : 0;
+        // exp2(-inf) = 0.  pos_q is formed here: this kernel has no register to spare for it.
+        const int ml = lane_now();
+        const int pos_q = (ml & 31) < q_n ? q_pos0 + (ml & 31) : -1;
+        const int base = kpos - lo_q + 32 * kb + 8 * (ml >> 5);
+        const int lim = max(0, min(pos_q + 1, kpos + kn) - lo_q);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int r = base + 16 * (e >> 3) + (e & 7);
           const bool vis = (unsigned)r < (unsigned)lim;
-          ds[e] = __builtin_amdgcn_exp2f(vis ? __builtin_fmaf(s[e], sl2, -lse2) : -INFINITY) * (dp[e] - Dq);
+          ds[e] = __builtin_amdgcn_exp2f(vis ? __builtin_fmaf(s[e], sl2, -lse2) : -INFINITY) * (dp[e] + neg_D);
         }
       }
       const bf16x8 dsf[2] = {to_bf16x8(ds), to_bf16x8(ds + 8)};
@@ -185,21 +177,9 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
     });
   }
 
-  if (q_valid) {
-    float* dq = a.dq + (qrow * a.H + head) * DQK + 4 * hh;
-#pragma unroll
-    for (int c = 0; c < DQK / 32; ++c)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        f32x4* p = reinterpret_cast<f32x4*>(dq + 32 * c + 8 * rr);
-        f32x4 old = *p;
-        old[0] += a.scale * acc[c][4 * rr];
-        old[1] += a.scale * acc[c][4 * rr + 1];
-        old[2] += a.scale * acc[c][4 * rr + 2];
-        old[3] += a.scale * acc[c][4 * rr + 3];
-        *p = old;
-      }
-  }
+  barrier_lds();  // every wave is past its last tile
+  rows_add<DQK / 64>(smem + wave * ROWS_OUT_BYTES, lane_now(), acc, a.scale, a.dq + ((int64_t)q_row0 * a.H + head) * DQK,
+                     a.H * DQK, q_n);
 }
 
 // ------------------------------------------------------------------ dK, dV (key-stationary)
@@ -207,10 +187,10 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
 // waves of a pair split the work so that each fits in 256 registers (two waves per SIMD,
 // whose matrix and vector work then overlap):
 //   wave A: S = Q K^T, P = exp(S - LSE) (masked), dV^T += dO^T P
-//   wave B: dP = dO V^T, dS = P o (dP - D), dK^T += Q^T dS
+//   wave B: dP - D = dO V^T - D, dS = P o (dP - D), dK^T += Q^T dS
 // P crosses from A to B through LDS (rounded to bf16, the value the dV product uses).  Per
 // 96-query tile: barrier, start the copy of the next tile (LDS holds two), phase 1 (A: S
-// and P, B: dP), barrier, phase 2 (A: dV, B: dS and dK).
+// and P, B: dP - D), barrier, phase 2 (A: dV, B: dS and dK).
 constexpr int KV_BQ = KV_QTILE_ROWS;                             // query rows per tile
 constexpr int KV_NSB = KV_BQ / 32;                               // 32-row sub-blocks per tile
 constexpr int KV_VEC = 128;                                      // LDS slots per vector (LSE2, D)
@@ -219,48 +199,57 @@ constexpr int KV_OBYTES = KV_BQ * DV * 2;                        // 24 KB
 constexpr int KV_STAGE = KV_QBYTES + KV_OBYTES + 2 * KV_VEC * 4;  // + LSE2 and D
 constexpr int KV_NSTAGE = 2;  // measured faster than three stages
 constexpr int KV_PBYTES = 4 * KV_NSB * 2048;                     // P: 4 pairs x sub-blocks x 32x32 bf16
-// The copies are issued by the four role-B waves only (role A's first phase is the longer
-// one).  Vector-memory instructions one kv_issue adds per issuing wave: (3 + 2) column
-// blocks x KV_BQ/32 copies of 1 KB (Q, dO), plus one vector copy (LSE2 or D) on each wave
-// that has one.  With three stages, waiting for vmcnt <= KV_VMCNT_ONE_TILE completes tile
-// t while tile t+1 may stay in flight; with two, tile t's copies are the only ones in flight.
-constexpr int KV_VMCNT_ONE_TILE = (DQK / 64 + DV / 64) * (KV_BQ / 32);
+constexpr int KV_LDS = KV_NSTAGE * KV_STAGE + KV_PBYTES;
+// The copies are issued by the four role-B waves only (role A's first phase is the longer one).
 
-// The query tile of flat tile index t = member * nt + i (member: query head of the group):
-// each member's tiles are walked last first.  Every range of a key item ends where its
-// document or segment ends, which is the same row for most items, so the workgroups running
-// together start at the same query tiles and stream them through the L2 together (walked
-// first to last, they would start at their own key positions, each on its own tiles).
-__device__ __forceinline__ int kv_tile(const TileRanges& qr, int t, int member) { return qr.nt - 1 - (t - member * qr.nt); }
+// One tile of a key item's walk: query tile qt of query head `member` of the group.  Each
+// member's tiles are walked last first.  Every range of a key item ends where its document or
+// segment ends, which is the same row for most items, so the workgroups running together start
+// at the same query tiles and stream them through the L2 together (walked first to last, they
+// would start at their own key positions, each on its own tiles).
+struct KvTile {
+  int member, qt;
+  Tile q;
+};
+__device__ __forceinline__ KvTile kv_tile(const TileRanges qr, int member, int qt) {
+  return {member, qt, tile_at(qr, qt, KV_BQ)};
+}
+__device__ __forceinline__ KvTile kv_next(const TileRanges qr, const KvTile& t) {
+  return t.qt > 0 ? kv_tile(qr, t.member, t.qt - 1) : kv_tile(qr, t.member + 1, qr.nt - 1);
+}
 
-// Flat tile index t covers (query head of the group, query tile): t = member * nt + tile.
-// wave_b: 0 .. 3, the issuing wave among the role-B waves.
-__device__ __forceinline__ void kv_issue(lds_char* smem, const AttnArgs& a, const TileRanges qr, int t, int qoff,
-                                         int ooff, int head0, int wave_b, int lane) {
-  const int member = t / qr.nt, qt = kv_tile(qr, t, member);
-  int row0, pos0, n;
-  tile_at(qr, qt, KV_BQ, row0, pos0, n);
-  lds_char* dst = smem + (t % KV_NSTAGE) * KV_STAGE;
-  dma_tile<DQK, KV_BQ, 4>(dst, tile_rsrc(a.q, row0, n, a.q_s), qoff + member * (DQK * 2), a.q_s, wave_b);
-  dma_tile<DV, KV_BQ, 4>(dst + KV_QBYTES, tile_rsrc(a.dO, row0, n, a.H * DV), ooff + member * (DV * 2), a.H * DV,
+// Starts the copy of tile t into an LDS stage.  wave_b: 0 .. 3, the issuing wave among the
+// role-B waves.
+__device__ __forceinline__ void kv_issue(lds_char* dst, const AttnArgs& a, const KvTile& t, int qoff, int ooff, int head0,
+                                         int wave_b, int lane) {
+  const int row0 = t.q.row0, n = t.q.n;
+  dma_tile<DQK, KV_BQ, 4>(dst, tile_rsrc(a.q, row0, n, a.q_s), qoff + t.member * (DQK * 2), a.q_s, wave_b);
+  dma_tile<DV, KV_BQ, 4>(dst + KV_QBYTES, tile_rsrc(a.dO, row0, n, a.H * DV), ooff + t.member * (DV * 2), a.H * DV,
                          wave_b);
-  const int64_t li = (int64_t)(head0 + member) * a.nq + row0;
-  // LSE2 and D of the tile's rows, 64 per copy; rows past the tile's end read as zero
-  static_assert(KV_BQ <= 2 * 64 && KV_BQ <= KV_VEC, "two 64-row copies per vector");
-  lds_char* vec = dst + KV_QBYTES + KV_OBYTES;
-  if (wave_b == 0) dma_vec64(vec, a.lse2 + li, min(n, 64), lane);
-  if (wave_b == 1) dma_vec64(vec + KV_VEC * 4, a.Dvec + li, min(n, 64), lane);
-  if constexpr (KV_BQ > 64) {
-    if (wave_b == 2) dma_vec64(vec + 256, a.lse2 + li + 64, max(n - 64, 0), lane);
-    if (wave_b == 3) dma_vec64(vec + KV_VEC * 4 + 256, a.Dvec + li + 64, max(n - 64, 0), lane);
-  }
+  // LSE2 (waves 0, 2) and D (waves 1, 3) of the tile's rows, 64 per copy; rows past the tile's
+  // end are not copied
+  static_assert(KV_BQ > 64 && KV_BQ <= 2 * 64 && KV_BQ <= KV_VEC, "two 64-row copies per vector");
+  const float* vec = (wave_b & 1) ? a.Dvec : a.lse2;
+  const int r0 = 32 * (wave_b & 2);  // 0 or 64
+  dma_vec64(dst + KV_QBYTES + KV_OBYTES + (wave_b & 1) * (KV_VEC * 4) + r0 * 4,
+            vec + (int64_t)(head0 + t.member) * a.nq + row0 + r0, min(max(n - r0, 0), 64), lane);
+}
+
+// clear_tail of the four role-B waves' copies of a short tile (Q, dO and D; a masked row's LSE
+// never enters a product).
+__device__ __forceinline__ void kv_clear_tail(lds_char* stage, int n, int wave_b, int lane) {
+  clear_tail<DQK, KV_BQ, 4>(stage, n, wave_b, lane);
+  clear_tail<DV, KV_BQ, 4>(stage + KV_QBYTES, n, wave_b, lane);
+  const int r = 32 * (wave_b & 2) + lane;  // waves 1 and 3 copied D, 64 rows each
+  if ((wave_b & 1) && r >= n && r < KV_BQ)
+    *reinterpret_cast<__attribute__((address_space(3))) float*>(stage + KV_QBYTES + KV_OBYTES + KV_VEC * 4 + 4 * r) = 0.f;
 }
 
 // STORE_DS: also store dS (bf16, as the MFMA operand registers hold it) for the query-
 // stationary dQ kernel that reads it back instead of recomputing S and dP.
 template <bool STORE_DS>
 __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[KV_NSTAGE * KV_STAGE + KV_PBYTES];
+  __shared__ __attribute__((aligned(1024))) char smem_raw[KV_LDS];
   lds_char* smem = (lds_char*)smem_raw;
   lds_char* pbuf = smem + KV_NSTAGE * KV_STAGE;
 
@@ -279,26 +268,22 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
   if (n_tiles == 0) return;  // uniform over the workgroup
   const int k_row0 = it.row0, k_pos0 = it.pos0, k_n = it.n;
 
-  lds_clear<512>(smem, KV_NSTAGE * KV_STAGE + KV_PBYTES, tid);
   const int kj = pair * 32 + m;
   const bool k_valid = kj < k_n;
   const int pos_k = k_valid ? k_pos0 + kj : 0x7fffffff;
-  int hi_k = k_valid ? a.cu[doc_of(a.cu, a.n_docs, pos_k) + 1] : 0;
-  // finish these loads here: left pending, the tile loop would wait for all copies in flight
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(hi_k)::"memory");
+  const int hi_k = doc_edge<true>(a.cu, it.d0, it.d1, it.edge0, k_pos0 + min(kj, k_n - 1));
   const int kn_w = min(32, max(0, k_n - pair * 32));  // valid keys of this pair
-  const int wk_first = k_pos0 + pair * 32;
-  const int wk_last = wk_first + kn_w - 1;
-  const int hi_first =
-      __builtin_amdgcn_readfirstlane(kn_w > 0 ? a.cu[doc_of(a.cu, a.n_docs, wk_first) + 1] : 0);
+  const int wk_first = k_pos0 + pair * 32, wk_last = wk_first + kn_w - 1;
+  // document ends of the pair's first and last key (lanes past the end repeat the last one)
+  const int hi_first = __builtin_amdgcn_readfirstlane(hi_k);
+  const int hi_last = __builtin_amdgcn_readlane(hi_k, 31);
   const float sl2 = a.scale * LOG2E;
-  const int64_t krow = k_row0 + (k_valid ? kj : 0);
   const int qoff = dma_lane_off<DQK>(a.q_s, head0, pair, lane);  // role B's copy lanes (wave b = pair)
   const int ooff = dma_lane_off<DV>(a.H * DV, head0, pair, lane);
   const int poff = pair * (KV_NSB * 2048) + lane * 16;  // this lane's P slot: + sb*2048 + half*1024
   const bool active = kn_w > 0;               // uniform over the pair
   // first dS slot of this key item (stored-dS backward only)
-  const int ds_slot0 = STORE_DS ? __builtin_amdgcn_readfirstlane(a.kbase[item_idx]) : 0;
+  const int ds_slot0 = it.x0, ds_head0 = kvl * a.grp;
 
   // The two roles run separate copies of the tile loop, with the same copies and the same
   // two barriers per tile: each copy keeps only its own role's operands and accumulators
@@ -309,24 +294,22 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
     // of dP) and dK^T
     constexpr int NF = ROLE == 0 ? DQK / 16 : DV / 16;
     constexpr int NACC = ROLE == 0 ? DV / 32 : DQK / 32;
+    KvTile cur = kv_tile(qr, 0, qr.nt - 1);
+    // the pair's K (role A) and V rows (role B) come through LDS, from the start of stage 1 on
+    static_assert(KV_STAGE + 4 * (own_bytes<DQK>() + own_bytes<DV>()) <= KV_LDS, "LDS");
     bf16x8 bf[NF];
-    {
-      const uint16_t* src = ROLE == 0 ? a.k + krow * a.k_s + kv_head * DQK + 8 * hh
-                                      : a.v + krow * a.v_s + kv_head * DV + 8 * hh;
-      u32x4 u[12];
-#pragma unroll
-      for (int t = 0; t < 12; ++t) u[t] = u32x4{0u, 0u, 0u, 0u};
-      if (k_valid) {
-        ldg_x4(src, u[0], u[1], u[2], u[3]);
-        ldg_x4(src + 64, u[4], u[5], u[6], u[7]);
-        if (ROLE == 0) ldg_x4(src + 128, u[8], u[9], u[10], u[11]);
-      }
-#pragma unroll
-      for (int t = 0; t < NF; ++t) bf[t] = __builtin_bit_cast(bf16x8, u[t]);
+    if constexpr (ROLE == 0) {
+      lds_char* own = smem + KV_STAGE + pair * own_bytes<DQK>();
+      own_rows_issue<DQK>(own, a.k, k_row0 + pair * 32, kn_w, a.k_s, kv_head, lane);
+      wait_dma();
+      own_rows_read<DQK>(own, lane, bf);
+    } else {
+      lds_char* own = smem + KV_STAGE + 4 * own_bytes<DQK>() + pair * own_bytes<DV>();
+      own_rows_issue<DV>(own, a.v, k_row0 + pair * 32, kn_w, a.v_s, kv_head, lane);
+      kv_issue(smem, a, cur, qoff, ooff, head0, pair, lane);
+      wait_dma();
+      own_rows_read<DV>(own, lane, bf);
     }
-    __syncthreads();  // LDS cleared before the first copies land
-    if constexpr (ROLE == 1)
-      for (int t = 0; t < KV_NSTAGE - 1 && t < n_tiles; ++t) kv_issue(smem, a, qr, t, qoff, ooff, head0, pair, lane);
 
     f32x16 acc[NACC];
 #pragma unroll
@@ -335,17 +318,20 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
 
     for (int t = 0; t < n_tiles; ++t) {
       refresh(o);
-      int q_row0, qpos, qn;
-      tile_at(qr, kv_tile(qr, t, t / qr.nt), KV_BQ, q_row0, qpos, qn);
-      // copies of tile t are done once at most the later tiles' copies issued so far (with
-      // two stages: none) are still in flight
+      const int qpos = cur.q.pos0, qn = cur.q.n;
+      const int64_t ds_off = (int64_t)(ds_head0 + cur.member) * a.ds_head_bytes +
+                             (int64_t)(ds_slot0 + cur.qt) * DS_TILE_BYTES;  // this tile's dS slot
+      const bool more = t + 1 < n_tiles;
+      if (more) cur = kv_next(qr, cur);
+      // a pair whose keys no row of the tile sees leaves the matrix cores to the others
+      const bool sees = active && qpos + qn > wk_first && qpos < hi_last;
       if constexpr (ROLE == 1) {
-        if (KV_NSTAGE > 2 && t + 1 < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KV_VMCNT_ONE_TILE) : "memory");
-        else wait_dma();
+        wait_dma();  // tile t's copies, the only ones in flight
+        if (qn < KV_BQ) kv_clear_tail(smem + (t % KV_NSTAGE) * KV_STAGE, qn, pair, lane_now());
       }
       barrier_lds();
       if constexpr (ROLE == 1)
-        if (t + KV_NSTAGE - 1 < n_tiles) kv_issue(smem, a, qr, t + KV_NSTAGE - 1, qoff, ooff, head0, pair, lane);
+        if (more) kv_issue(smem + ((t + 1) % KV_NSTAGE) * KV_STAGE, a, cur, qoff, ooff, head0, pair, lane);
       const lds_char* Qs = smem + (t % KV_NSTAGE) * KV_STAGE;
       const lds_char* Os = lds_opaque(Qs + KV_QBYTES);
       const lds_char* vec_s = lds_opaque(Qs + KV_QBYTES + KV_OBYTES);  // LSE2 then D, KV_VEC slots each
@@ -353,7 +339,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
       if constexpr (ROLE == 0) {
         // ---------------- phase 1: S, P = exp(S - LSE) (masked), P to LDS for role B
         bf16x8 pk[KV_BQ / 16];  // P of this tile, bf16: rows 16*g .. 16*g+15 in pk[g]
-        if (active) {
+        if (sees) {
           // S of the 32-row sub-blocks.  Left to itself the compiler issues each read just
           // before its product and waits for it there; instead sub-block 0's reads are all
           // issued first, and each next sub-block's as the current one's products free
@@ -393,7 +379,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
               // is this lane's first row relative to its key position; masked entries get
               // exp2(-inf)
               const int base = qpos - pos_k + 32 * sb + 8 * hh;
-              const int lim = k_valid ? max(0, min(qpos + qn, hi_k) - pos_k) : 0;
+              const int lim = max(0, min(qpos + qn, hi_k) - pos_k);
 #pragma unroll
               for (int e = 0; e < 16; ++e) {
                 const int r = base + 16 * (e >> 3) + (e & 7);
@@ -411,7 +397,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
         // ---------------- phase 2: dV^T[dv][key] += dO^T[dv][q] P[q][key]; groups of four
         // dO^T fragments, one per 16 query rows; a group's products are issued before the
         // next group loads
-        if (active) {
+        if (sees) {
           bf16x8 f[2][4];
           op_tr_x4<KV_BQ, 0, 0>(Os, o, f[0]);
           static_for<KV_BQ / 16>([&](auto g_) {
@@ -423,9 +409,18 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
           });
         }
       } else {
-        // ---------------- phase 1: dP = dO V^T of both sub-blocks
+        // ---------------- phase 1: dP - D = dO V^T - D of every sub-block
         f32x16 dp[KV_NSB];
-        if (active) {
+        if (sees) {
+          // the products accumulate onto -D of this lane's rows, 32*sb + 8*hh + {0..7, 16..23}
+          static_for<KV_NSB>([&](auto sb_) {
+            constexpr int sb = decltype(sb_)::value;
+            f32x4 d0, d1, d2, d3;
+            lds_x4_f32<KV_VEC * 4 + 128 * sb, KV_VEC * 4 + 128 * sb + 16, KV_VEC * 4 + 128 * sb + 64,
+                       KV_VEC * 4 + 128 * sb + 80>(vec_s, 32 * hh, d0, d1, d2, d3);
+            dp[sb] = f32x16{d0[0], d0[1], d0[2], d0[3], d1[0], d1[1], d1[2], d1[3],
+                            d2[0], d2[1], d2[2], d2[3], d3[0], d3[1], d3[2], d3[3]};
+          });
           // reads issued ahead as in role A's S
           const RowBases or_b = row_bases(Os, o);
           bf16x8 ob[DV / 16];
@@ -434,7 +429,6 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
           sched_fence();
           static_for<KV_NSB>([&](auto sb_) {
             constexpr int sb = decltype(sb_)::value;
-            dp[sb] = f32x16{};
 #pragma unroll
             for (int t2 = 0; t2 < DV / 16; ++t2) {
               dp[sb] = mfma(ob[t2], bf[t2], dp[sb]);
@@ -444,24 +438,28 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
           });
         }
         barrier_lds();  // P of this tile is in LDS
+        typedef __attribute__((address_space(1))) u32x4 gu32x4;
+        auto store_ds = [&](int sb, bf16x8 d0, bf16x8 d1) {
+          char* dst = a.ds + ds_off + (sb * 4 + pair) * DS_BLOCK_BYTES + lane * 16;
+          __builtin_nontemporal_store(__builtin_bit_cast(u32x4, d0), (gu32x4*)(dst));
+          __builtin_nontemporal_store(__builtin_bit_cast(u32x4, d1), (gu32x4*)(dst + DS_BLOCK_BYTES / 2));
+        };
         // ---------------- phase 2: dS = P o (dP - D) of every sub-block first (its vector
         // work overlaps role A's dV products), then dK^T[c][key] += Q^T[c][q] dS[q][key]
-        if (active) {
-          bf16x8 sf[KV_NSB][2];
+        if (sees) {
+          bf16x8 sf[KV_NSB][2], pr[KV_NSB][2];
+          static_for<KV_NSB>([&](auto sb_) {
+            constexpr int sb = decltype(sb_)::value;
+            lds_x2_bf16<2048 * sb, 2048 * sb + 1024>(pbuf, poff, pr[sb][0], pr[sb][1]);
+          });
+          sched_fence();
           static_for<KV_BQ / 32>([&](auto sb_) {
             constexpr int sb = decltype(sb_)::value;
-            bf16x8 p0, p1;
-            lds_x2_bf16<2048 * sb, 2048 * sb + 1024>(pbuf, poff, p0, p1);
-            f32x4 d0, d1, d2, d3;
-            lds_x4_f32<KV_VEC * 4 + 128 * sb, KV_VEC * 4 + 128 * sb + 16, KV_VEC * 4 + 128 * sb + 64,
-                       KV_VEC * 4 + 128 * sb + 80>(vec_s, 32 * hh, d0, d1, d2, d3);
-            const float D_r[16] = {d0[0], d0[1], d0[2], d0[3], d1[0], d1[1], d1[2], d1[3],
-                                   d2[0], d2[1], d2[2], d2[3], d3[0], d3[1], d3[2], d3[3]};
             float ds[16];
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-              const float pv = (float)(e < 8 ? p0[e] : p1[e - 8]);
-              ds[e] = pv * (dp[sb][e] - D_r[e]);
+              const float pv = (float)pr[sb][e >> 3][e & 7];
+              ds[e] = pv * dp[sb][e];
             }
             sf[sb][0] = to_bf16x8(ds);
             sf[sb][1] = to_bf16x8(ds + 8);
@@ -469,12 +467,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
               // this pair's 32 keys x sub-block sb's 32 queries, 2 KB: two 1 KB stores in the
               // register layout (lane 32h + m: key m, queries 16*half + 8h .. +7), non-temporal
               // (read once, by the dQ kernel)
-              typedef __attribute__((address_space(1))) u32x4 gu32x4;
-              const int member = t / qr.nt, tl = kv_tile(qr, t, member);
-              char* dst = a.ds + (int64_t)((kv_head - a.kv_head0) * a.grp + member) * a.ds_head_bytes +
-                          (int64_t)(ds_slot0 + tl) * DS_TILE_BYTES + (sb * 4 + pair) * DS_BLOCK_BYTES + lane * 16;
-              __builtin_nontemporal_store(__builtin_bit_cast(u32x4, sf[sb][0]), (gu32x4*)(dst));
-              __builtin_nontemporal_store(__builtin_bit_cast(u32x4, sf[sb][1]), (gu32x4*)(dst + DS_BLOCK_BYTES / 2));
+              store_ds(sb, sf[sb][0], sf[sb][1]);
             }
           });
           static_for<KV_BQ / 32>([&](auto sb_) {
@@ -491,41 +484,19 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
               sched_fence();
             });
           });
+        } else if (STORE_DS && active) {  // dQ reads 64 keys at a time: the other pair's may be visible
+#pragma unroll
+          for (int sb = 0; sb < KV_NSB; ++sb) store_ds(sb, bf16x8{}, bf16x8{});
         }
       }
     }
 
-    if (k_valid) {
-      if constexpr (ROLE == 0) {
-        float* dv = a.dv + (krow * a.Hkv + kv_head) * DV + 4 * hh;
-#pragma unroll
-        for (int d = 0; d < DV / 32; ++d)
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            f32x4* p = reinterpret_cast<f32x4*>(dv + 32 * d + 8 * rr);
-            f32x4 old = *p;
-            old[0] += acc[d][4 * rr];
-            old[1] += acc[d][4 * rr + 1];
-            old[2] += acc[d][4 * rr + 2];
-            old[3] += acc[d][4 * rr + 3];
-            *p = old;
-          }
-      } else {
-        float* dk = a.dk + (krow * a.Hkv + kv_head) * DQK + 4 * hh;
-#pragma unroll
-        for (int c = 0; c < DQK / 32; ++c)
-#pragma unroll
-          for (int rr = 0; rr < 4; ++rr) {
-            f32x4* p = reinterpret_cast<f32x4*>(dk + 32 * c + 8 * rr);
-            f32x4 old = *p;
-            old[0] += a.scale * acc[c][4 * rr];
-            old[1] += a.scale * acc[c][4 * rr + 1];
-            old[2] += a.scale * acc[c][4 * rr + 2];
-            old[3] += a.scale * acc[c][4 * rr + 3];
-            *p = old;
-          }
-      }
-    }
+    barrier_lds();  // every wave is past its last tile
+    const int64_t krow = (int64_t)(k_row0 + pair * 32) * a.Hkv + kv_head;
+    if constexpr (ROLE == 0)
+      rows_add<DV / 64>(smem + wave * ROWS_OUT_BYTES, lane_now(), acc, 1.0f, a.dv + krow * DV, a.Hkv * DV, kn_w);
+    else
+      rows_add<DQK / 64>(smem + wave * ROWS_OUT_BYTES, lane_now(), acc, a.scale, a.dk + krow * DQK, a.Hkv * DQK, kn_w);
   };
   if (role == 0) run(IntC<0>{});
   else run(IntC<1>{});
@@ -552,7 +523,7 @@ constexpr int DQS_LDS = DQS_KSTAGES * DQS_KBYTES + DQS_DSTAGES * DQS_DBYTES;
 // them sits (off < 0: the wave's rows do not see the item).  valid = 0 once the walk is over.
 struct DsTile {
   int valid, krow0, kn;
-  int64_t off;
+  int64_t off;  // < 0: none of the wave's rows sees the keys
 };
 
 // The walk over the key items that a query item's ranges touch, in row order, 64 keys at a
@@ -561,30 +532,31 @@ struct DsTile {
 // loads that the compiler waits for where they are used (never together with the copies in
 // flight, as vector loads after the copies' memory-clobbering assembly would be).
 struct DsWalk {
-  int rr, r, j;
+  int rr, r, end, kpos_r, j;  // range, next key row, the range's end, key position - key row, record
+  int lo_first, q_last;       // document start of the wave's first row, position of its last (-1: no rows)
   i32x16 rec;
 };
 
-typedef const __attribute__((address_space(4))) int cint;
 typedef const __attribute__((address_space(4))) i32x16 crec16;
 
-__device__ __forceinline__ DsTile ds_next(const AttnArgs& a, const Item& it, DsWalk& w, bool wave_rows, int qrow) {
+// The item's ranges, a value type of scalars like TileRanges.
+struct DsRanges {
+  int nr, r0, p0, c0, x0, r1, p1, c1, x1, r2, p2, c2, x2, r3, p3, c3, x3;
+};
+
+__device__ __forceinline__ DsTile ds_next(const AttnArgs& a, const DsRanges R, DsWalk& w, int qrow) {
   DsTile d;
   d.valid = 0;
-  bool jump = w.j < 0;
-  while (w.rr < it.nr) {
-    const int kr = w.rr == 0 ? it.r0 : w.rr == 1 ? it.r1 : w.rr == 2 ? it.r2 : it.r3;
-    const int kc = w.rr == 0 ? it.c0 : w.rr == 1 ? it.c1 : w.rr == 2 ? it.c2 : it.c3;
-    if (w.r < kr) {
-      w.r = kr;
-      jump = true;
-    }
-    if (w.r < kr + kc) break;
-    ++w.rr;
-  }
-  if (w.rr >= it.nr) return d;
-  if (jump) {
-    w.j = ((cint*)a.kmap32)[w.r >> 5];
+  if (w.r >= w.end) {  // the next range; ranges lie in segments of their own, so in other key items
+    if (++w.rr >= R.nr) return d;
+    int rr = R.r0, pp = R.p0, cc = R.c0, xx = R.x0;
+    if (w.rr >= 1) { rr = R.r1; pp = R.p1; cc = R.c1; xx = R.x1; }
+    if (w.rr >= 2) { rr = R.r2; pp = R.p2; cc = R.c2; xx = R.x2; }
+    if (w.rr >= 3) { rr = R.r3; pp = R.p3; cc = R.c3; xx = R.x3; }
+    w.r = rr;
+    w.end = rr + cc;
+    w.kpos_r = pp - rr;
+    w.j = xx;
     w.rec = *(crec16*)(a.krec + w.j * ITEM_INTS);
   } else if (w.r >= w.rec[0] + w.rec[1]) {  // past this item: the next one in row order
     ++w.j;
@@ -597,7 +569,8 @@ __device__ __forceinline__ DsTile ds_next(const AttnArgs& a, const Item& it, DsW
   w.r = d.krow0 + DQS_BK;
   // the sub-block of the item's query tiling that holds the wave's rows [qrow, qrow + 32)
   d.off = -1;
-  if (wave_rows) {
+  const int kpos = d.krow0 + w.kpos_r;  // a key item lies in one segment: its rows' positions are consecutive
+  if (kpos <= w.q_last && kpos + d.kn > w.lo_first) {
     int slot = w.rec[3];
 #pragma unroll
     for (int k = 0; k < MAX_RANGES; ++k) {
@@ -629,11 +602,16 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
   const Item it(a.items, item);
   const bool wave_rows = 32 * wave < it.n;  // the wave's 32 query rows (all valid or none)
   const int qrow0 = it.row0 + 32 * wave;
+  const DsRanges R = {it.nr,  it.r0, it.p0, it.c0, it.x0, it.r1, it.p1, it.c1, it.x1,
+                      it.r2, it.p2, it.c2, it.x2, it.r3, it.p3, it.c3, it.x3};
   DsWalk walk;
-  walk.rr = 0;
+  walk.rr = -1;
   walk.r = 0;
-  walk.j = -1;
-  DsTile t0 = ds_next(a, it, walk, wave_rows, qrow0);
+  walk.end = 0;
+  walk.q_last = wave_rows ? it.pos0 + 32 * wave + 31 : -1;
+  walk.lo_first = __builtin_amdgcn_readfirstlane(
+      doc_edge<false>(a.cu, it.d0, it.d1, it.edge0, it.pos0 + (wave_rows ? 32 * wave : 0)));
+  DsTile t0 = ds_next(a, R, walk, qrow0);
   if (!t0.valid) return;  // uniform over the workgroup
   const int kv_head = head / a.grp;
   const char* ds_head = a.ds + (int64_t)(head - a.q_head0) * a.ds_head_bytes;
@@ -644,8 +622,8 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
   // transpose read of the B operand: keys 8h' + 4v + j at query 16*(g%2) + i
   const int ds_rd = 512 * (lane >> 5) + 32 * ((lane >> 4) & 1) + 64 * ((lane >> 2) & 3) + 8 * (lane & 3);
 
-  lds_clear<512>(smem, DQS_LDS, tid);
-  __syncthreads();  // LDS cleared before the first copy lands
+  // no row of LDS is read that a copy has not written: a tile has 64 keys or 32 (segments are
+  // 32-aligned), and of the latter only the first 32 are read
 
   // copies of tile d's K rows into K stage st (every wave its share)
   auto issue_k = [&](const DsTile& d, int st) {
@@ -658,11 +636,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
     const int bytes = d.kn > 32 ? 2 * DS_BLOCK_BYTES : DS_BLOCK_BYTES;
     const u32x4 desc = tile_desc(ds_head, d.off, bytes);
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr(dsmem + st * DQS_DBYTES + wave * DQS_WAVE_BYTES));
-    dma16_stream(m0, desc, ds_voff, 0);
-    dma16_stream(m0 + 1024, desc, ds_voff, 256);
+    dma_cols<2, 256, 1024, true>(m0, desc, ds_voff);
     if (d.kn <= 32) return 2;
-    dma16_stream(m0 + 2048, desc, ds_voff, 2048);
-    dma16_stream(m0 + 3072, desc, ds_voff, 2048 + 256);
+    dma_cols<2, 256, 1024, true>(m0 + 2048, desc, ds_voff + 2048);
     return 4;
   };
 
@@ -673,13 +649,13 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
 
   // issue order per wave: K(0) D(0) D(1) | K(1) D(2) | K(2) D(3) | ...: at the top of tile u
   // only D(u+1) (issued after K(u)) may still be in flight
-  DsTile t1 = ds_next(a, it, walk, wave_rows, qrow0);
+  DsTile t1 = ds_next(a, R, walk, qrow0);
   issue_k(t0, 0);
   int n_cur = issue_ds(t0, 0);
   int n_1 = t1.valid ? issue_ds(t1, 1) : 0;
   DsTile t2;
   t2.valid = 0;
-  if (t1.valid) t2 = ds_next(a, it, walk, wave_rows, qrow0);
+  if (t1.valid) t2 = ds_next(a, R, walk, qrow0);
   for (int u = 0;; ++u) {
     refresh(o);
     if (n_1 == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
@@ -715,24 +691,12 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
     t1 = t2;
     n_cur = n_1;
     n_1 = n_2;
-    if (t2.valid) t2 = ds_next(a, it, walk, wave_rows, qrow0);
+    if (t2.valid) t2 = ds_next(a, R, walk, qrow0);
   }
 
-  if (wave_rows) {
-    float* dq = a.dq + ((int64_t)(qrow0 + m) * a.H + head) * DQK + 4 * hh;
-#pragma unroll
-    for (int c = 0; c < DQK / 32; ++c)
-#pragma unroll
-      for (int rr2 = 0; rr2 < 4; ++rr2) {
-        f32x4* p = reinterpret_cast<f32x4*>(dq + 32 * c + 8 * rr2);
-        f32x4 old = *p;
-        old[0] += a.scale * acc[c][4 * rr2];
-        old[1] += a.scale * acc[c][4 * rr2 + 1];
-        old[2] += a.scale * acc[c][4 * rr2 + 2];
-        old[3] += a.scale * acc[c][4 * rr2 + 3];
-        *p = old;
-      }
-  }
+  barrier_lds();  // every wave is past its last tile
+  rows_add<DQK / 64>(smem + wave * ROWS_OUT_BYTES, lane_now(), acc, a.scale, a.dq + ((int64_t)qrow0 * a.H + head) * DQK,
+                     a.H * DQK, wave_rows ? 32 : 0);
 }
 
 // kv_heads_per_pass = 0: recompute path (bwd_dq + bwd_dkdv over all heads).  Otherwise the

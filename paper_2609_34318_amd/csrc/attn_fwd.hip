@@ -25,24 +25,21 @@ constexpr int FWD_KBYTES = FWD_BK * DQK * 2;             // 24 KB
 constexpr int FWD_STAGE = FWD_KBYTES + FWD_BK * DV * 2;  // 40 KB
 constexpr int FWD_NSTAGE = 2;  // measured faster than three stages
 constexpr int FWD_WAVES = 8;
-// Copy instructions one fwd_issue adds per wave: 3 (K) + 2 (V).  With three stages,
-// waiting for vmcnt <= 5 completes tile t while tile t+1 may stay in flight; with two,
-// tile t's copies are the only ones in flight.
-constexpr int FWD_VMCNT_ONE_TILE = 5;
+constexpr int FWD_AHEAD = 6;  // operand reads of S in flight ahead of the products
 constexpr float RESCALE_SLACK = 8.0f;
 
-// Starts the copy of key/value tile t into LDS stage t % FWD_NSTAGE.
-__device__ __forceinline__ void fwd_issue(lds_char* smem, const AttnArgs& a, const TileRanges kr, int t, int koff,
-                                          int voff, int head, int wave) {
-  int row0, pos0, n;
-  tile_at(kr, t, FWD_BK, row0, pos0, n);
-  lds_char* dst = smem + (t % FWD_NSTAGE) * FWD_STAGE;
-  dma_tile<DQK, FWD_BK, FWD_WAVES>(dst, tile_rsrc(a.k, row0, n, a.k_s), koff, a.k_s, wave);
-  dma_tile<DV, FWD_BK, FWD_WAVES>(dst + FWD_KBYTES, tile_rsrc(a.v, row0, n, a.v_s), voff, a.v_s, wave);
+// Starts the copy of key/value tile k into LDS stage `stage`.
+__device__ __forceinline__ void fwd_issue(lds_char* stage, const AttnArgs& a, const Tile k, int koff, int voff, int wave) {
+  dma_tile<DQK, FWD_BK, FWD_WAVES>(stage, tile_rsrc(a.k, k.row0, k.n, a.k_s), koff, a.k_s, wave);
+  dma_tile<DV, FWD_BK, FWD_WAVES>(stage + FWD_KBYTES, tile_rsrc(a.v, k.row0, k.n, a.v_s), voff, a.v_s, wave);
 }
 
 __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[FWD_NSTAGE * FWD_STAGE];
+  // stage 0 | stage 1; before the loop the waves' Q rows from the start of stage 1, after it
+  // their outputs
+  constexpr int LDS_BYTES = FWD_STAGE + FWD_WAVES * own_bytes<DQK>();
+  static_assert(LDS_BYTES >= FWD_NSTAGE * FWD_STAGE && LDS_BYTES >= FWD_WAVES * ROWS_OUT_BYTES, "LDS");
+  __shared__ __attribute__((aligned(1024))) char smem_raw[LDS_BYTES];
   lds_char* smem = (lds_char*)smem_raw;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -51,38 +48,31 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
   int head, item;
   xcd_head_item(blockIdx.x, a.H, a.n_items, head, item);
   const Item it(a.items, item);
-  const int q_row0 = it.row0, q_pos0 = it.pos0, q_n = it.n;
   const TileRanges kr = tile_ranges(it, FWD_BK);
   const int n_tiles = kr.nt;
-
-  lds_clear<64 * FWD_WAVES>(smem, FWD_NSTAGE * FWD_STAGE, tid);
-
-  const int qi = wave * 32 + m;
-  const bool q_valid = qi < q_n;
-  const int pos_q = q_valid ? q_pos0 + qi : -1;
-  int lo_q = q_valid ? a.cu[doc_of(a.cu, a.n_docs, pos_q)] : 0;
-  // finish this load here: left pending, the tile loop would wait for all copies in flight
-  asm volatile("s_waitcnt vmcnt(0)" : "+v"(lo_q)::"memory");
-  const int lo_last = a.cu[doc_of(a.cu, a.n_docs, q_pos0 + q_n - 1)];
-  const float sl2 = a.scale * LOG2E;
   const int kv_head = head / a.grp;  // grouped K/V heads: contiguous groups of query heads
   const int koff = dma_lane_off<DQK>(a.k_s, kv_head, wave, lane);
   const int voff = dma_lane_off<DV>(a.v_s, kv_head, wave, lane);
+  const float sl2 = a.scale * LOG2E;
 
+  // this wave's rows: [q_row0, q_row0 + q_n) at positions from q_pos0 on (q_n <= 0: none)
+  const int q_row0 = it.row0 + 32 * wave, q_pos0 = it.pos0 + 32 * wave, q_n = min(32, it.n - 32 * wave);
+  const int q_last = q_n > 0 ? q_pos0 + q_n - 1 : -1;
+  const bool q_valid = m < q_n;
+  const int pos_q = q_valid ? q_pos0 + m : -1;  // -1: sees nothing
+
+  lds_char* qbuf = smem + FWD_STAGE + wave * own_bytes<DQK>();
+  own_rows_issue<DQK>(qbuf, a.q, q_row0, max(q_n, 0), a.q_s, head, lane);
+  Tile cur = tile_at(kr, 0, FWD_BK);  // with no tile: of no rows
+  fwd_issue(smem, a, cur, koff, voff, wave);
+
+  // document starts: of this lane's row, of the wave's first and last row
+  const int lo_q = doc_edge<false>(a.cu, it.d0, it.d1, it.edge0, q_pos0 + min(m, max(q_n, 1) - 1));
+  const int lo_first = __builtin_amdgcn_readfirstlane(lo_q);
+  const int lo_last = __builtin_amdgcn_readlane(lo_q, 31);  // rows past the end repeat the last one
   bf16x8 qf[DQK / 16];
-  {
-    const uint16_t* qrow = a.q + (int64_t)(q_row0 + (q_valid ? qi : 0)) * a.q_s + head * DQK + 8 * hh;
-#pragma unroll
-    for (int t = 0; t < DQK / 16; ++t) {
-      u32x4 u = {0u, 0u, 0u, 0u};
-      if (q_valid) u = ldg16(qrow + 16 * t);
-      settle(u);
-      qf[t] = __builtin_bit_cast(bf16x8, u);
-    }
-  }
-  __syncthreads();  // LDS cleared before the first copy lands
-
-  for (int t = 0; t < FWD_NSTAGE - 1 && t < n_tiles; ++t) fwd_issue(smem, a, kr, t, koff, voff, head, wave);
+  wait_dma();
+  own_rows_read<DQK>(qbuf, lane, qf);
 
   f32x16 acc[DV / 32];
 #pragma unroll
@@ -93,16 +83,19 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
 
   for (int t = 0; t < n_tiles; ++t) {
     refresh(o);
-    int k_row0, kpos, kn;
-    tile_at(kr, t, FWD_BK, k_row0, kpos, kn);
-    // copies of tile t are done once at most the later tiles' copies issued so far (with
-    // two stages: none) are still in flight
-    if (FWD_NSTAGE > 2 && t + 1 < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FWD_VMCNT_ONE_TILE) : "memory");
-    else wait_dma();
+    const int kpos = cur.pos0, kn = cur.n;
+    lds_char* Ks = smem + (t % FWD_NSTAGE) * FWD_STAGE;
+    lds_char* Vs = Ks + FWD_KBYTES;
+    wait_dma();  // tile t's copies, the only ones in flight
+    if (kn < FWD_BK) clear_tail<DV, FWD_BK, FWD_WAVES>(Vs, kn, wave, lane_now());
     barrier_lds();
-    if (t + FWD_NSTAGE - 1 < n_tiles) fwd_issue(smem, a, kr, t + FWD_NSTAGE - 1, koff, voff, head, wave);
-    const lds_char* Ks = smem + (t % FWD_NSTAGE) * FWD_STAGE;
-    const lds_char* Vs = Ks + FWD_KBYTES;
+    if (t + 1 < n_tiles) {
+      cur = tile_at(kr, t + 1, FWD_BK);
+      fwd_issue(smem + ((t + 1) % FWD_NSTAGE) * FWD_STAGE, a, cur, koff, voff, wave);
+    }
+    // a wave none of whose rows sees the tile (the diagonal's upper half, another document)
+    // leaves the matrix cores to the others
+    if (kpos > q_last || kpos + kn <= lo_first) continue;
 
     f32x16 s[2];
 #pragma unroll
@@ -112,13 +105,25 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
       for (int t2 = 0; t2 < DQK / 16; ++t2)
         s[kb] = mfma(op_b128<FWD_BK>(Ks, o, 32 * kb, t2), qf[t2], s[kb]);
     }
+    // operand reads six k-steps ahead of their products: left to itself the compiler runs one
+    // to two ahead, and how far changes with the code around it (256K ring step 14.29 against
+    // 14.51 ms, packed 32K 1.40 against 1.48 ms; eight ahead measures the same)
+    __builtin_amdgcn_sched_group_barrier(0x100, FWD_AHEAD, 0);
+#pragma unroll
+    for (int j = 0; j < 2 * (DQK / 16) - FWD_AHEAD; ++j) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, FWD_AHEAD, 0);
 
+    // per wave: in a window of short documents most 256-row tiles straddle a boundary, their
+    // 32-row waves seldom
     const bool full = (kn == FWD_BK) && (lo_last <= kpos) && (kpos + FWD_BK - 1 <= q_pos0);
     if (!full) {
       // key kpos + key(e) is visible iff lo_q <= it <= pos_q and key(e) < kn, i.e. iff
       // 0 <= base + c(e) < lim with base = kpos - lo_q + 8*hh
       const int base = kpos - lo_q + 8 * hh;
-      const int lim = q_valid ? max(0, min(pos_q + 1, kpos + kn) - lo_q) : 0;
+      const int lim = max(0, min(pos_q + 1, kpos + kn) - lo_q);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -178,26 +183,28 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
   }
 
   const float l_tot = xhalf_sum((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
-  if (q_valid) {
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    const int64_t base = ((int64_t)(q_row0 + qi) * a.H + head) * DV + 4 * hh;
-    float* orow = a.out_o + base;
+  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+  if (q_valid && hh == 0)
+    a.out_lse[(int64_t)head * a.nq + q_row0 + m] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
+  barrier_lds();  // every wave is past its last tile
+  lds_char* obuf = smem + wave * ROWS_OUT_BYTES;
+  const int64_t base = ((int64_t)q_row0 * a.H + head) * DV;
+  const int rows = max(q_n, 0), pitch = a.H * DV;
+  const rows_rsrc ro = rows_buffer(a.out_o + base, rows, pitch * 4);
+  const rows_rsrc rb = rows_buffer(o_bf16 + base, o_bf16 ? rows : 0, pitch * 2);
+  static_for<DV / 64>([&](auto g_) {
+    constexpr int g = decltype(g_)::value;
+    rows_stage<g>(obuf, lane, acc, inv);
 #pragma unroll
-    for (int d = 0; d < DV / 32; ++d)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        f32x4 val = {acc[d][4 * rr] * inv, acc[d][4 * rr + 1] * inv, acc[d][4 * rr + 2] * inv,
-                     acc[d][4 * rr + 3] * inv};
-        *reinterpret_cast<f32x4*>(orow + 32 * d + 8 * rr) = val;
-        if (o_bf16) {
-          uint32_t lo = pack_bf16x2(val[0], val[1]), hi = pack_bf16x2(val[2], val[3]);
-          *reinterpret_cast<uint2*>(o_bf16 + base + 32 * d + 8 * rr) = make_uint2(lo, hi);
-        }
-      }
-    if (hh == 0)
-      a.out_lse[(int64_t)head * a.nq + q_row0 + qi] =
-          l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
-  }
+    for (int i = 0; i < 8; ++i) {
+      const f32x4 val = rows_read(obuf, lane, i);
+      const int off = rows_row(lane, i) * pitch + rows_col(lane, i);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, off * 4 + 256 * g, 0, 0);
+      if (o_bf16)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])}, rb,
+                                              off * 2 + 128 * g, 0, 0);
+    }
+  });
 }
 
 hipError_t launch_attn_fwd(const AttnArgs& a, uint16_t* o_bf16, hipStream_t stream) {

@@ -29,12 +29,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int DQK = 192;
 constexpr int DV = 128;
 constexpr int ITEM_INTS = 16;
+constexpr int UNIT_INTS = 32;
 constexpr int MAX_RANGES = 4;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
@@ -74,14 +76,29 @@ __device__ __forceinline__ bf16x8 to_bf16x8(const float* v) {
 
 __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 
-// Largest d with cu[d] <= pos (cu has n_docs + 1 entries, pos inside the window).
-__device__ __forceinline__ int doc_of(const int* __restrict__ cu, int n_docs, int pos) {
-  int lo = 0, hi = n_docs;
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (cu[mid] <= pos) lo = mid; else hi = mid;
+// Start (END = false) or end (END = true) of the document that holds position pos, which lies
+// in one of documents d0 .. d1; edge0 is that boundary of document d0.  A tile usually lies in
+// one document (no load at all) or a few (their boundaries are scalar loads, the same for
+// every lane); tiles over many short documents search per lane.
+typedef const __attribute__((address_space(4))) int cint;
+template <bool END>
+__device__ __forceinline__ int doc_edge(const int* __restrict__ cu, int d0, int d1, int edge0, int pos) {
+  int edge = edge0;
+  if (d1 - d0 <= 8) {
+    for (int d = d0 + 1; d <= d1; ++d) {
+      const int b = ((cint*)cu)[d], e = END ? ((cint*)cu)[d + 1] : b;
+      edge = pos >= b ? e : edge;
+    }
+  } else {
+    int lo = d0, hi = d1 + 1;  // the largest d with cu[d] <= pos
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (cu[mid] <= pos) lo = mid; else hi = mid;
+    }
+    edge = cu[END ? lo + 1 : lo];
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(edge)::"memory");
   }
-  return lo;
+  return edge;
 }
 
 // ------------------------------------------------------------------ swizzled LDS tiles
@@ -264,20 +281,6 @@ __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0
 // first use inside the loop (where the wait would also cover every copy in flight).
 template <class T> __device__ __forceinline__ void settle(T& x) { asm volatile("" : "+v"(x)); }
 
-// Four 16-byte global loads from p + 0, 32, 64, 96 bytes, issued and completed in one
-// statement (operands loaded once before a tile loop).
-__device__ __forceinline__ void ldg_x4(const uint16_t* p, u32x4& a, u32x4& b, u32x4& c, u32x4& d) {
-  asm volatile(
-      "global_load_dwordx4 %0, %4, off\n\t"
-      "global_load_dwordx4 %1, %4, off offset:32\n\t"
-      "global_load_dwordx4 %2, %4, off offset:64\n\t"
-      "global_load_dwordx4 %3, %4, off offset:96\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
-      : "v"(p)
-      : "memory");
-}
-
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
 // ------------------------------------------------------------------ direct global -> LDS copies
@@ -285,8 +288,8 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 // buffer descriptor is built per tile with its base at the tile's first row and its record
 // count ending at the tile's last valid row, so rows past the end are out of range for the
 // hardware bounds check and never touch memory (all of the offset travels in the VGPR
-// operand, which is what the check covers) (the kernels mask those rows and clear LDS
-// once at start, so whatever the copy leaves there is finite).  Each copy instruction
+// operand, which is what the check covers) (the kernels mask those rows and clear them in
+// LDS, clear_tail).  Each copy instruction
 // writes 16 (or 4) bytes per lane at LDS address M0 + 16*lane (4*lane).
 __device__ __forceinline__ u32x4 tile_desc(const void* base, int64_t byte_off, int bytes) {
   const uint64_t b = (uint64_t)(uintptr_t)base + (uint64_t)byte_off;
@@ -302,31 +305,34 @@ __device__ __forceinline__ u32x4 tile_rsrc(const uint16_t* g, int64_t row0, int 
   return tile_desc(g, row0 * pitch * 2, valid * pitch * 2);
 }
 
-// One 16-byte-per-lane copy at voff + inc (s_nop: M0 and the descriptor are written by the
-// compiler just before; 5 wait states cover both the M0 and the SGPR-write hazards).
-__device__ __forceinline__ void dma16(uint32_t m0v, u32x4 desc, int voff, int inc) {
-  int tmp;
-  asm volatile(
-      "v_add_u32 %0, %1, %2\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 4\n\t"
-      "buffer_load_dwordx4 %0, %4, 0 offen lds"
-      : "=&v"(tmp)
-      : "s"(inc), "v"(voff), "s"(m0v), "s"(desc)
-      : "memory", "m0");
-}
-// dma16 for bytes read exactly once (the stored dS): the non-temporal hint keeps them from
-// displacing lines that other workgroups read again (the K tiles of the same head).
-__device__ __forceinline__ void dma16_stream(uint32_t m0v, u32x4 desc, int voff, int inc) {
-  int tmp;
-  asm volatile(
-      "v_add_u32 %0, %1, %2\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 4\n\t"
-      "buffer_load_dwordx4 %0, %4, 0 offen nt lds"
-      : "=&v"(tmp)
-      : "s"(inc), "v"(voff), "s"(m0v), "s"(desc)
-      : "memory", "m0");
+// N copies of 16 bytes per lane, at global offsets voff + STEP * j and LDS addresses
+// m0v + LSTEP * j, in one statement.  The instruction's immediate offset moves both addresses,
+// so M0 advances by the difference; no copy needs an address add of its own, and the wait
+// states between the descriptor's last scalar write (v_readfirstlane) and its first use are paid
+// once, not per copy (M0 itself needs one state before an LDS copy reads it).  STREAM: bytes read
+// exactly once (the stored dS): the non-temporal hint keeps them from displacing lines that
+// other workgroups read again (the K tiles of the same head).
+#define HYDRA_DMA_FIRST(hint) "s_mov_b32 m0, %1\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %2, 0 offen " hint "lds\n\t"
+#define HYDRA_DMA_NEXT(off, hint) \
+  "s_add_u32 m0, m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen offset:%c" off " " hint "lds\n\t"
+template <int N, int STEP, int LSTEP, bool STREAM = false>
+__device__ __forceinline__ void dma_cols(uint32_t m0v, u32x4 desc, int voff) {
+  static_assert((N == 2 || N == 3) && (N - 1) * STEP < 4096, "immediate offsets");
+  if constexpr (N == 3)
+    asm volatile(HYDRA_DMA_FIRST("") HYDRA_DMA_NEXT("4", "") HYDRA_DMA_NEXT("5", "")
+                 :
+                 : "v"(voff), "s"(m0v), "s"(desc), "n"(LSTEP - STEP), "n"(STEP), "n"(2 * STEP)
+                 : "memory", "m0", "scc");
+  else if constexpr (STREAM)
+    asm volatile(HYDRA_DMA_FIRST("nt ") HYDRA_DMA_NEXT("4", "nt ")
+                 :
+                 : "v"(voff), "s"(m0v), "s"(desc), "n"(LSTEP - STEP), "n"(STEP)
+                 : "memory", "m0", "scc");
+  else
+    asm volatile(HYDRA_DMA_FIRST("") HYDRA_DMA_NEXT("4", "")
+                 :
+                 : "v"(voff), "s"(m0v), "s"(desc), "n"(LSTEP - STEP), "n"(STEP)
+                 : "memory", "m0", "scc");
 }
 __device__ __forceinline__ void dma4(uint32_t m0v, u32x4 desc, int voff) {
   asm volatile(
@@ -355,11 +361,103 @@ __device__ __forceinline__ void dma_tile(lds_char* lds, u32x4 desc, int voff, in
   constexpr int NINS = ROWS / 8;  // per column block
   static_assert(NINS % NW == 0, "tile must split evenly over the waves");
   const uint32_t base = __builtin_amdgcn_readfirstlane(lds_addr(lds) + wave * 1024);
+  // opaque, so that the sums below are not kept in registers through the tile loop
+  if constexpr (NINS > NW) asm volatile("" : "+v"(voff));
 #pragma unroll
-  for (int b = 0; b < DIM / 64; ++b)
+  for (int i = 0; i < NINS / NW; ++i)
+    dma_cols<DIM / 64, 128, block_bytes<ROWS>()>(base + NW * i * 1024, desc, voff + 8 * NW * i * pitch * 2);
+}
+
+// A wave's own 32 rows x DIM, loaded once before its tile loop: copied into LDS by rows (one
+// instruction covers 8 rows x 128 contiguous bytes) and read from there as operand fragments.
+// Loading the fragments straight from global memory costs far more: each instruction then
+// touches 32 rows, and the 96 of a workgroup took about 6000 cycles.  The 16-byte chunk c of a
+// row's 64-column block lies at chunk c ^ (row & 7), which spreads both the copy and the reads
+// over the banks.  buf: OWN_BYTES<DIM> of LDS that only this wave uses.  Rows past `valid`
+// stay as they were in LDS: the caller masks them or does not store them.
+template <int DIM> constexpr int own_bytes() { return 32 * DIM * 2; }
+template <int DIM>
+__device__ __forceinline__ void own_rows_issue(lds_char* buf, const uint16_t* g, int64_t row0, int valid, int pitch,
+                                               int head, int lane) {
+  const u32x4 desc = tile_rsrc(g, row0, valid, pitch);
+  const uint32_t base = __builtin_amdgcn_readfirstlane(lds_addr(buf));
+  const int q = lane >> 3;
+  const int voff = (q * pitch + head * DIM + (((lane & 7) ^ q) << 3)) * 2;
 #pragma unroll
-    for (int i = 0; i < NINS / NW; ++i)
-      dma16(base + b * block_bytes<ROWS>() + NW * i * 1024, desc, voff, 8 * NW * i * pitch * 2 + b * 128);
+  for (int i = 0; i < 4; ++i) dma_cols<DIM / 64, 128, 4096>(base + i * 1024, desc, voff + 8 * i * pitch * 2);
+}
+// f[t]: columns 16 t + 8 h .. + 7 of row m.  After the wave has waited for its copies.
+template <int DIM>
+__device__ __forceinline__ void own_rows_read(const lds_char* buf, int lane, bf16x8 (&f)[DIM / 16]) {
+  const int m = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int t = 0; t < DIM / 16; ++t)
+    f[t] = lds_ld16(buf, (t >> 2) * 4096 + m * 128 + (((2 * (t & 3) + h) ^ (m & 7)) << 4));
+#pragma unroll
+  for (int t = 0; t < DIM / 16; ++t) settle(f[t]);
+}
+
+// ------------------------------------------------------------------ accumulators -> rows
+// Writes a wave's 32 rows x 64*G accumulated columns (acc[c] of column block c, transposed: the
+// lane holds row m) to memory through 8 KB of LDS of its own, 64 columns at a time, so that one
+// instruction stores 4 rows x 256 contiguous bytes.  Stored straight from the accumulators an
+// instruction covers 32 bytes of each of 32 rows, and the output of a forward workgroup took
+// 8000 cycles.  16-byte chunk c of a row lies at chunk c ^ (row & 15).  The caller has seen
+// every wave past its last read of the LDS that holds buf.
+constexpr int ROWS_OUT_BYTES = 32 * 256;
+
+template <int G, int N>
+__device__ __forceinline__ void rows_stage(lds_char* buf, int lane, const f32x16 (&acc)[N], float scale) {
+  const int m = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const f32x16& x = acc[2 * G + d];
+      const f32x4 v = {x[4 * rr] * scale, x[4 * rr + 1] * scale, x[4 * rr + 2] * scale, x[4 * rr + 3] * scale};
+      *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(buf + m * 256 +
+                                                                   (((8 * d + 2 * rr + h) ^ (m & 15)) << 4)) = v;
+    }
+}
+// Row and first column (of the 64) of the 16 bytes that this lane handles in step i of 8.
+__device__ __forceinline__ int rows_row(int lane, int i) { return 4 * i + (lane >> 4); }
+__device__ __forceinline__ int rows_col(int lane, int i) { return ((lane & 15) ^ (rows_row(lane, i) & 15)) * 4; }
+__device__ __forceinline__ f32x4 rows_read(const lds_char* buf, int lane, int i) {
+  return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(buf + i * 1024 + lane * 16);
+}
+
+// A wave's output rows as a buffer of `valid` rows, `pitch_bytes` apart: the hardware's bounds
+// check drops the rows past the end, with no branch per row.  All of an access's offset travels in
+// its address operand and its immediate, which that check covers whatever the row count.
+typedef __amdgpu_buffer_rsrc_t rows_rsrc;
+__device__ __forceinline__ rows_rsrc rows_buffer(void* out, int valid, int pitch_bytes) {
+  const uint64_t p = (uint64_t)(uintptr_t)out;
+  // readfirstlane returns a signed int: widened as such, a low half with its top bit set would
+  // fill the high half with ones
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)((uint64_t)hi << 32 | lo), 0, valid * pitch_bytes,
+                                           0x00020000);
+}
+
+// out[row][col] += scale * acc, rows [0, valid), `pitch` elements apart.
+template <int NG>
+__device__ __forceinline__ void rows_add(lds_char* buf, int lane, const f32x16 (&acc)[2 * NG], float scale, float* out,
+                                         int pitch, int valid) {
+  const rows_rsrc rs = rows_buffer(out, valid, pitch * 4);
+  static_for<NG>([&](auto g_) {
+    constexpr int g = decltype(g_)::value;
+    f32x4 old[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      old[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             rs, (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0));
+    rows_stage<g>(buf, lane, acc, scale);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, old[i] + rows_read(buf, lane, i)), rs,
+                                             (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0);
+  });
 }
 
 // 64 fp32 values (valid of them in range) -> LDS, one wave.
@@ -374,11 +472,28 @@ __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" :
 // unlike __syncthreads it does not also wait for the copies still in flight for later tiles.
 __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Clears `bytes` (multiple of 16 * threads) of LDS.
-template <int THREADS>
-__device__ __forceinline__ void lds_clear(lds_char* lds, int bytes, int tid) {
-  for (int o = tid * 16; o < bytes; o += THREADS * 16)
-    *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(lds + o) = u32x4{0u, 0u, 0u, 0u};
+// This lane's index, computed afresh: code outside the tile loop (or rare in it) that uses it
+// keeps no register alive through the loop.
+__device__ __forceinline__ int lane_now() {
+  int ones = -1;
+  asm volatile("" : "+s"(ones));
+  return __builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0));
+}
+
+// Zeroes rows >= n of a short tile that dma_tile<DIM, ROWS, NW> copied, each wave the rows of
+// its own copies, after it has waited for them: a masked entry's P or dS is 0, and 0 times
+// whatever LDS held in those rows need not be.
+template <int DIM, int ROWS, int NW>
+__device__ __forceinline__ void clear_tail(lds_char* tile, int n, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < ROWS / 8 / NW; ++i) {
+    const int r = 8 * (wave + NW * i) + (lane >> 3);
+    if (r < n) continue;
+#pragma unroll
+    for (int b = 0; b < DIM / 64; ++b)
+      *reinterpret_cast<__attribute__((address_space(3))) u32x4*>(tile + b * block_bytes<ROWS>() + r * 128 +
+                                                                  (lane & 7) * 16) = u32x4{0u, 0u, 0u, 0u};
+  }
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on XCD b % 8), each
@@ -399,14 +514,17 @@ __device__ __forceinline__ void xcd_head_item(int b, int n_heads, int n_items, i
   }
 }
 
-// A work item (16 ints, see the plan), read once into scalar registers.  Plain scalar
-// members only: an array here would be placed in scratch memory and indexed dynamically.
+// A work item's launch record (32 ints, see launch_units), read once into scalar registers.
+// Plain scalar members only: an array here would be placed in scratch memory and indexed
+// dynamically.
 struct Item {
   int row0, pos0, n, nr;
   int r0, p0, c0, r1, p1, c1, r2, p2, c2, r3, p3, c3;
+  int edge0, lo_last, d0, d1;  // document boundary of the first row, start of the last row's, their indices
+  int x0, x1, x2, x3;          // query items: first key record of each range; key items: x0 = first dS slot
 
   __device__ __forceinline__ Item(const int* items, int idx) {
-    const int* s = items + idx * ITEM_INTS;
+    const int* s = items + (int64_t)idx * UNIT_INTS;
     row0 = __builtin_amdgcn_readfirstlane(s[0]);
     pos0 = __builtin_amdgcn_readfirstlane(s[1]);
     n = __builtin_amdgcn_readfirstlane(s[2]);
@@ -423,6 +541,14 @@ struct Item {
     r3 = __builtin_amdgcn_readfirstlane(s[13]);
     p3 = __builtin_amdgcn_readfirstlane(s[14]);
     c3 = nr > 3 ? __builtin_amdgcn_readfirstlane(s[15]) : 0;
+    edge0 = __builtin_amdgcn_readfirstlane(s[16]);
+    lo_last = __builtin_amdgcn_readfirstlane(s[17]);
+    d0 = __builtin_amdgcn_readfirstlane(s[18]);
+    d1 = __builtin_amdgcn_readfirstlane(s[19]);
+    x0 = __builtin_amdgcn_readfirstlane(s[20]);
+    x1 = __builtin_amdgcn_readfirstlane(s[21]);
+    x2 = __builtin_amdgcn_readfirstlane(s[22]);
+    x3 = __builtin_amdgcn_readfirstlane(s[23]);
   }
 };
 
@@ -448,16 +574,21 @@ __device__ __forceinline__ TileRanges tile_ranges(const Item& it, int B) {
   return R;
 }
 
-// Rows [row0, row0 + n) at global positions [pos0, pos0 + n) of tile t < R.nt.
-__device__ __forceinline__ void tile_at(const TileRanges R, int t, int B, int& row0, int& pos0, int& n) {
+// Rows [row0, row0 + n) at global positions [pos0, pos0 + n).
+struct Tile {
+  int row0, pos0, n;
+};
+
+// Tile t < R.nt.  The kernels look a tile up once, when they start its copy, and carry it to the
+// iteration that computes it: scalar work in the loops costs time of its own (all waves wait for
+// the slowest at the tile's barrier).
+__device__ __forceinline__ Tile tile_at(const TileRanges R, int t, int B) {
   int rr = R.r0, pp = R.p0, cc = R.c0, ff = 0;
   if (t >= R.f1) { rr = R.r1; pp = R.p1; cc = R.c1; ff = R.f1; }
   if (t >= R.f2) { rr = R.r2; pp = R.p2; cc = R.c2; ff = R.f2; }
   if (t >= R.f3) { rr = R.r3; pp = R.p3; cc = R.c3; ff = R.f3; }
   const int off = (t - ff) * B;
-  row0 = rr + off;
-  pos0 = pp + off;
-  n = min(B, cc - off);
+  return {rr + off, pp + off, min(B, cc - off)};
 }
 
 struct AttnArgs {
@@ -472,11 +603,10 @@ struct AttnArgs {
   float* dq;           // bwd accumulators
   float* dk;
   float* dv;
-  float* Dvec;         // bwd: [H][nq] rowsum(dO * O)
+  float* Dvec;         // bwd: [H][nq] -rowsum(dO * O)
   float* lse2;         // bwd: [H][nq] final LSE * log2(e)
   const int* items;    // work items
   const int* cu;       // document boundaries
-  int n_docs;
   int n_items;
   int H;               // query heads
   int Hkv;             // K/V heads; query head h uses K/V head h / grp
@@ -488,13 +618,10 @@ struct AttnArgs {
   // q_head0 .. +q_heads (query-stationary kernels)
   int kv_head0, kv_heads;
   int q_head0, q_heads;
-  // stored-dS backward: dS blocks of the launch's query heads, ds_head_bytes apart; per key
-  // item (launch order) its first tile slot; the key items in row order as records (row0,
-  // rows, ranges, first slot) and the record index of each 32-row key block
+  // stored-dS backward: dS blocks of the launch's query heads, ds_head_bytes apart; the key
+  // items in row order as records (row0, rows, ranges, first slot, ranges)
   char* ds;
   int64_t ds_head_bytes;
-  const int* kbase;
-  const int* kmap32;
   const int* krec;
   const int* kitems;   // key-stationary items
 };

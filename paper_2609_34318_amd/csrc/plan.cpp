@@ -179,6 +179,27 @@ void plan_items(const Problem& pr, int which, std::vector<int32_t>* items) {
     std::copy(&raw[order[i] * kItemInts], &raw[order[i] * kItemInts] + kItemInts, &(*items)[i * kItemInts]);
 }
 
+void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
+                  const std::vector<int32_t>& table, std::vector<int32_t>* units) {
+  const size_t n = items.size() / kItemInts;
+  units->assign(n * kUnitInts, 0);
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t* it = &items[i * kItemInts];
+    int32_t* u = &(*units)[i * kUnitInts];
+    std::copy(it, it + kItemInts, u);
+    const int d0 = doc_index(pr.cu, it[1]), d1 = doc_index(pr.cu, int64_t(it[1]) + it[2] - 1);
+    u[16] = which == 0 ? pr.cu[d0] : pr.cu[d0 + 1];
+    u[17] = pr.cu[d1];
+    u[18] = d0;
+    u[19] = d1;
+    if (table.empty()) continue;
+    if (which == 0)
+      for (int r = 0; r < it[3]; ++r) u[20 + r] = table[size_t(it[4 + 3 * r]) / 32];
+    else
+      u[20] = table[i];
+  }
+}
+
 int64_t visible_pairs(const Problem& pr) {
   int64_t total = 0;
   const int n_docs = int(pr.cu.size()) - 1;
@@ -240,32 +261,35 @@ int64_t ds_tables(const Problem& pr, const std::vector<int32_t>& kitems, std::ve
   return slots;
 }
 
+namespace {
+int64_t n_tiles(const hydra_chunk_t& c, int rows_per_tile) {
+  int64_t n = 0;
+  for (int s = 0; s < c.n_segs; ++s) n += (c.len[s] + rows_per_tile - 1) / rows_per_tile;
+  return n;
+}
+}  // namespace
+
+uint64_t noalloc_bytes(const Problem& pr) {
+  const size_t nq = size_t(n_tiles(pr.q, kQTile)), nk = size_t(n_tiles(pr.kv, kKvTile));
+  size_t n = 0;
+  for (size_t part : {pr.cu.size() * 4, nq * 64, nk * 64, nk * 4, size_t((pr.nk + 31) / 32) * 4, nk * 64,
+                      size_t(pr.H) * size_t(pr.nq) * 4, size_t(pr.H) * size_t(pr.nq) * 4})
+    n = align_up(n + part, 256);
+  return n;
+}
+
 WsLayout ws_layout(const Problem& pr) {
   WsLayout w{};
-  const int64_t nqt = [&] {
-    int64_t n = 0;
-    for (int s = 0; s < pr.q.n_segs; ++s) n += (pr.q.len[s] + kQTile - 1) / kQTile;
-    return n;
-  }();
-  const int64_t nkt = [&] {
-    int64_t n = 0;
-    for (int s = 0; s < pr.kv.n_segs; ++s) n += (pr.kv.len[s] + kKvTile - 1) / kKvTile;
-    return n;
-  }();
+  const int64_t nqt = n_tiles(pr.q, kQTile), nkt = n_tiles(pr.kv, kKvTile);
   w.n_qitems = nqt;
   w.n_kitems = nkt;
   size_t off = 0;
   w.cu_off = off;
   off = align_up(off + pr.cu.size() * sizeof(int32_t), 256);
   w.qitems_off = off;
-  off = align_up(off + size_t(nqt) * kItemInts * sizeof(int32_t), 256);
+  off = align_up(off + size_t(nqt) * kUnitInts * sizeof(int32_t), 256);
   w.kitems_off = off;
-  off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
-  w.n_kblocks = (pr.nk + 31) / 32;
-  w.kbase_off = off;
-  off = align_up(off + size_t(nkt) * sizeof(int32_t), 256);
-  w.kmap_off = off;
-  off = align_up(off + size_t(w.n_kblocks) * sizeof(int32_t), 256);
+  off = align_up(off + size_t(nkt) * kUnitInts * sizeof(int32_t), 256);
   w.krec_off = off;
   off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
   w.d_off = off;

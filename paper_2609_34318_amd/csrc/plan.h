@@ -13,6 +13,7 @@ constexpr int kDv = 128;
 constexpr int kQTile = 256;    // query rows per query-stationary workgroup (8 waves x 32)
 constexpr int kKvTile = 128;   // key rows per key-stationary workgroup (4 waves x 32)
 constexpr int kItemInts = 16;  // int32 per work item
+constexpr int kUnitInts = 32;  // int32 per launch record: a work item and what its kernel would else look up
 
 // Checked and normalised view of a hydra_problem_t.
 struct Problem {
@@ -35,12 +36,31 @@ void plan_items(const Problem& pr, int which, std::vector<int32_t>* items);
 
 int64_t visible_pairs(const Problem& pr);
 
+// The launch records of plan_items' work items, in the same order (kUnitInts each): the
+// item's 16 ints, then [16] the document boundary of its first row (its start for query
+// items, its end for key items), [17] the start of its last row's document, [18], [19] the
+// document indices of its first and last row, [20..23] per visible range of a query item the
+// row-order index of the key item that holds the range's first row (see ds_tables), or [20]
+// of a key item its first dS slot.  A kernel that reads one record instead of searching
+// cu_seqlens and the tables has one memory round trip before its first copy, not several.
+void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
+                  const std::vector<int32_t>& table, std::vector<int32_t>* units);
+
 // Byte offsets of the workspace regions.
 struct WsLayout {
-  size_t cu_off, qitems_off, kitems_off, kbase_off, kmap_off, krec_off, d_off, lse2_off, total;
-  int64_t n_qitems, n_kitems, n_kblocks;
+  size_t cu_off, qitems_off, kitems_off, krec_off, d_off, lse2_off, total;
+  int64_t n_qitems, n_kitems;
 };
 WsLayout ws_layout(const Problem& pr);
+
+// What the no-allocation backward's 32 MiB limit is counted on: D, LSE*log2(e), the documents,
+// 64 bytes per query tile, 148 per key tile (its item, its record, its dS slot and its 32-key
+// blocks).  The launch records take more than that, at most 64 bytes per query tile and 48 per
+// key tile: kNoAllocExtraBytes holds them for every problem within the limit, so that a record
+// may grow without a call that was accepted being refused.
+uint64_t noalloc_bytes(const Problem& pr);
+constexpr size_t kNoAllocLimitBytes = size_t(32) << 20;
+constexpr size_t kNoAllocExtraBytes = size_t(12) << 20;
 
 // The stored-dS backward applies when every segment of both chunks starts and ends on a
 // multiple of 32 positions: the key-stationary tiles then cut the query rows into 32-row
