@@ -15,9 +15,9 @@
 #include "prof.h"
 
 namespace hydra {
-hipError_t launch_attn_fwd(const AttnArgs& a, uint16_t* o_bf16, hipStream_t stream);
-hipError_t launch_attn_bwd(const AttnArgs& a, int n_qitems, int n_kitems, const int* kitems, int kv_heads_per_pass,
-                           hipStream_t stream);
+hipError_t launch_attn_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, hipStream_t stream);
+hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
+                           int kv_heads_per_pass, hipStream_t stream);
 hipError_t launch_lse_merge(int64_t n_rows, int H, float* o_acc, float* lse_acc, const float* o_part,
                             const float* lse_part, uint16_t* o_bf16, hipStream_t stream);
 }  // namespace hydra
@@ -107,30 +107,12 @@ int check_ptr(const void* p, bool needed) {
   return aligned16(p) ? HYDRA_OK : HYDRA_ERR_ALIGN;
 }
 
-// Builds the host image of the workspace prefix (cu, query items, key items) and uploads it.
-int upload_plan(const Problem& pr, const WsLayout& w, bool with_kv_items, void* ws, hipStream_t stream,
-                std::vector<int32_t>* qitems, std::vector<int32_t>* kitems) {
-  plan_items(pr, 0, qitems);
-  if (with_kv_items) plan_items(pr, 1, kitems);
-  const size_t bytes = with_kv_items ? w.d_off : w.kitems_off;
-  std::vector<char> img(bytes, 0);
-  std::memcpy(img.data() + w.cu_off, pr.cu.data(), pr.cu.size() * sizeof(int32_t));
-  auto put = [&](size_t off, const std::vector<int32_t>& v) {
-    std::memcpy(img.data() + off, v.data(), v.size() * sizeof(int32_t));
-  };
-  std::vector<int32_t> units, kbase, kmap32, krec;
-  if (with_kv_items) {
-    ds_tables(pr, *kitems, &kbase, &kmap32, &krec);
-    launch_units(pr, 1, *kitems, kbase, &units);
-    put(w.kitems_off, units);
-    put(w.krec_off, krec);
-  }
-  launch_units(pr, 0, *qitems, kmap32, &units);
-  put(w.qitems_off, units);
-  // Pageable source: the runtime has consumed `img` when the call returns.
-  if (hipMemcpyAsync(ws, img.data(), bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return HYDRA_ERR_HIP;
-  return HYDRA_OK;
-}
+// A split list in the workspace, and how many heads its launches have; no units: the whole items
+// are launched.
+struct ListSize {
+  int units = 0, merges = 0, parts = 0, heads = 0;
+  size_t merges_off = 0, units_off = 0;
+};
 
 // Which problem's plan each workspace holds, as far as this library uploaded it: the
 // planned calls launch on the plan in the workspace, so they refuse a workspace whose
@@ -140,9 +122,66 @@ int upload_plan(const Problem& pr, const WsLayout& w, bool with_kv_items, void* 
 struct PlanRecord {
   std::vector<int64_t> key;  // what the plan depends on: heads, documents, both chunks
   bool has_kitems = false;
+  ListSize fwd, dq, kv;
 };
 std::mutex g_plans_mu;
 std::map<const void*, PlanRecord> g_plans;
+
+// Builds the host image of the workspace prefix (documents, records, split lists) and uploads it.
+// kv_heads: K/V heads per dK/dV launch (0: the forward's part only).
+int upload_plan(const Problem& pr, const WsLayout& w, int kv_heads, void* ws, hipStream_t stream, PlanRecord* rec) {
+  std::vector<int32_t> qitems, kitems, qrec, krecs, kbase, kmap32, krec;
+  std::vector<char> img;
+  auto put = [&](size_t off, const std::vector<int32_t>& v) {
+    if (img.size() < off + v.size() * sizeof(int32_t)) img.resize(off + v.size() * sizeof(int32_t), 0);
+    if (!v.empty()) std::memcpy(img.data() + off, v.data(), v.size() * sizeof(int32_t));
+  };
+  plan_items(pr, 0, &qitems);
+  put(w.cu_off, pr.cu);
+  if (kv_heads) {
+    plan_items(pr, 1, &kitems);
+    ds_tables(pr, kitems, &kbase, &kmap32, &krec);
+    launch_units(pr, 1, kitems, kbase, &krecs);
+    put(w.kitems_off, krecs);
+    put(w.krec_off, krec);
+  }
+  launch_units(pr, 0, qitems, kmap32, &qrec);
+  put(w.qitems_off, qrec);
+  // the split lists last, one after another, so that only what is there is copied
+  size_t end = w.lists_off;
+  auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads) {
+    UnitList l;
+    split_units(pr, kernel, records, heads, &l);
+    if (l.units.empty()) return ListSize{};
+    ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts, heads};
+    auto next = [&](const std::vector<int32_t>& v) {
+      const size_t at = end;
+      put(at, v);
+      end = (at + v.size() * sizeof(int32_t) + 255) / 256 * 256;
+      return at;
+    };
+    z.merges_off = next(l.merges);
+    z.units_off = next(l.units);
+    return z;
+  };
+  rec->fwd = put_list(Kernel::kFwd, qrec, pr.H);
+  if (kv_heads) {
+    rec->dq = put_list(Kernel::kDq, qrec, pr.H);
+    rec->kv = put_list(Kernel::kDkdv, krecs, kv_heads);
+  }
+  rec->has_kitems = kv_heads != 0;
+  if (end > w.d_off) return HYDRA_ERR_WORKSPACE;  // the lists' bound: never so
+  // Pageable source: the runtime has consumed `img` when the call returns.
+  if (hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, stream) != hipSuccess) return HYDRA_ERR_HIP;
+  return HYDRA_OK;
+}
+
+// A launch of the whole items at `whole`, or of the split list.
+Launch list_launch(void* ws, size_t whole, int64_t n_whole, const ListSize& l) {
+  auto at = [&](size_t off) { return reinterpret_cast<const int*>(static_cast<const char*>(ws) + off); };
+  if (l.units == 0) return {at(whole), int(n_whole), nullptr, 0, 0};
+  return {at(l.units_off), l.units, at(l.merges_off), l.merges, l.parts};
+}
 
 std::vector<int64_t> plan_key(const Problem& pr) {
   std::vector<int64_t> k = {pr.H, pr.Hkv, int64_t(pr.cu.size())};
@@ -157,20 +196,23 @@ std::vector<int64_t> plan_key(const Problem& pr) {
   return k;
 }
 
-void record_plan(const void* ws, const Problem& pr, bool has_kitems) {
+void record_plan(const void* ws, const Problem& pr, PlanRecord&& rec) {
+  rec.key = plan_key(pr);
   std::lock_guard<std::mutex> lock(g_plans_mu);
-  PlanRecord& r = g_plans[ws];
-  r.key = plan_key(pr);
-  r.has_kitems = has_kitems;
+  g_plans[ws] = std::move(rec);
 }
 
-// True if `ws` holds pr's plan, with the key-side items when `need_kitems`.
-bool plan_matches(const void* ws, const Problem& pr, bool need_kitems) {
+// True if `ws` holds pr's plan, with the key-side items when `need_kitems`; its lists in *out.
+bool plan_matches(const void* ws, const Problem& pr, bool need_kitems, PlanRecord* out) {
   std::lock_guard<std::mutex> lock(g_plans_mu);
   auto it = g_plans.find(ws);
   if (it == g_plans.end()) return false;
   if (need_kitems && !it->second.has_kitems) return false;
-  return it->second.key == plan_key(pr);
+  if (it->second.key != plan_key(pr)) return false;
+  out->fwd = it->second.fwd;
+  out->dq = it->second.dq;
+  out->kv = it->second.kv;
+  return true;
 }
 
 AttnArgs base_args(const Problem& pr, const WsLayout& w, void* ws) {
@@ -180,8 +222,8 @@ AttnArgs base_args(const Problem& pr, const WsLayout& w, void* ws) {
   a.items = reinterpret_cast<const int*>(base + w.qitems_off);
   a.Dvec = reinterpret_cast<float*>(base + w.d_off);
   a.lse2 = reinterpret_cast<float*>(base + w.lse2_off);
-  a.kitems = reinterpret_cast<const int*>(base + w.kitems_off);
   a.krec = reinterpret_cast<const int*>(base + w.krec_off);
+  a.split = base + w.split_off;
   a.H = pr.H;
   a.Hkv = pr.Hkv;
   a.grp = pr.H / pr.Hkv;
@@ -235,12 +277,12 @@ int attn_fwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
                         {{q, qb}, {k, kb}, {v, vb}}))
       return HYDRA_ERR_INVALID;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    PlanRecord plan;
     if (upload) {  // the forward needs only the query-stationary items
-      std::vector<int32_t> qitems, kitems;
-      rc = upload_plan(pr, w, false, workspace, s, &qitems, &kitems);
+      rc = upload_plan(pr, w, 0, workspace, s, &plan);
       if (rc != HYDRA_OK) return rc;
-      record_plan(workspace, pr, false);
-    } else if (!plan_matches(workspace, pr, false)) {
+      record_plan(workspace, pr, PlanRecord(plan));
+    } else if (!plan_matches(workspace, pr, false, &plan)) {
       return HYDRA_ERR_WORKSPACE;
     }
     AttnArgs a = base_args(pr, w, workspace);
@@ -249,8 +291,8 @@ int attn_fwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     a.v = static_cast<const uint16_t*>(v);
     a.out_o = o_part;
     a.out_lse = lse_part;
-    a.n_items = int(w.n_qitems);
-    if (launch_attn_fwd(a, static_cast<uint16_t*>(o_bf16), s) != hipSuccess) return HYDRA_ERR_HIP;
+    const Launch l = list_launch(workspace, w.qitems_off, w.n_qitems, plan.fwd);
+    if (launch_attn_fwd(a, l, static_cast<uint16_t*>(o_bf16), s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
     return HYDRA_ERR_INVALID;
@@ -300,14 +342,18 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
                          {d_o, qh * kDv * 2}}))
       return HYDRA_ERR_INVALID;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    PlanRecord plan;
+    const int kv_heads = kv_per_pass ? kv_per_pass : pr.Hkv;  // of one dK/dV launch
     if (upload) {
-      std::vector<int32_t> qitems, kitems;
-      rc = upload_plan(pr, w, true, workspace, s, &qitems, &kitems);
+      rc = upload_plan(pr, w, kv_heads, workspace, s, &plan);
       if (rc != HYDRA_OK) return rc;
-      record_plan(workspace, pr, true);
-    } else if (!plan_matches(workspace, pr, true)) {
+      record_plan(workspace, pr, PlanRecord(plan));
+    } else if (!plan_matches(workspace, pr, true, &plan)) {
       return HYDRA_ERR_WORKSPACE;
     }
+    // the workspace's last upload may have been for passes of fewer heads, whose parts would not
+    // fit the scratch in one launch over all of them
+    if (plan.kv.heads != kv_heads) plan.kv = ListSize{};
     AttnArgs a = base_args(pr, w, workspace);
     a.q = static_cast<const uint16_t*>(q);
     a.k = static_cast<const uint16_t*>(k);
@@ -320,9 +366,10 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     a.dv = dv_acc;
     a.ds = static_cast<char*>(kv_per_pass ? ds_buf : nullptr);
     a.ds_head_bytes = int64_t(ds_head);
-    const int* kitems_dev = reinterpret_cast<const int*>(static_cast<char*>(workspace) + w.kitems_off);
-    if (launch_attn_bwd(a, int(w.n_qitems), int(w.n_kitems), kitems_dev, kv_per_pass, s) != hipSuccess)
-      return HYDRA_ERR_HIP;
+    const Launch q_whole = list_launch(workspace, w.qitems_off, w.n_qitems, ListSize{});
+    const Launch dq = list_launch(workspace, w.qitems_off, w.n_qitems, plan.dq);
+    const Launch kv = list_launch(workspace, w.kitems_off, w.n_kitems, plan.kv);
+    if (launch_attn_bwd(a, q_whole, dq, kv, kv_per_pass, s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
     return HYDRA_ERR_INVALID;
@@ -341,9 +388,9 @@ int hydra_attn_plan(const hydra_problem_t* p, void* workspace, size_t workspace_
     const WsLayout w = ws_layout(pr);
     if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
-    std::vector<int32_t> qitems, kitems;
-    rc = upload_plan(pr, w, true, workspace, static_cast<hipStream_t>(stream), &qitems, &kitems);
-    if (rc == HYDRA_OK) record_plan(workspace, pr, true);
+    PlanRecord plan;
+    rc = upload_plan(pr, w, pr.Hkv, workspace, static_cast<hipStream_t>(stream), &plan);
+    if (rc == HYDRA_OK) record_plan(workspace, pr, std::move(plan));
     return rc;
   } catch (...) {
     return HYDRA_ERR_INVALID;

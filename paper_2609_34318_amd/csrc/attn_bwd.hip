@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void bwd_pre_kernel(const uint16_t* __restrict
 }
 
 // ------------------------------------------------------------------ dQ (query-stationary)
-constexpr int DQ_BK = 96;  // keys per tile: measured faster than 64 and 128
+constexpr int DQ_BK = DQ_TILE_ROWS;  // keys per tile: 96 measured faster than 64 and 128
 constexpr int DQ_KBYTES = DQ_BK * DQK * 2;            // 36 KB
 constexpr int DQ_STAGE = DQ_KBYTES + DQ_BK * DV * 2;  // 60 KB
 constexpr int DQ_NSTAGE = 2;  // measured faster than three stages
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
   const int head = a.q_head0 + hl;
   const Item it(a.items, item);
   const TileRanges kr = tile_ranges(it, DQ_BK);
-  const int n_tiles = kr.nt;
+  const int t0 = it.t0, n_tiles = (it.t1 < 0 ? kr.nt : it.t1) - t0;  // this unit's tiles
   if (n_tiles == 0) return;  // uniform over the workgroup
   const int kv_head = head / a.grp;  // grouped K/V heads: contiguous groups of query heads
   const float sl2 = a.scale * LOG2E;
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
 
   lds_char* own = smem + DQ_STAGE + wave * own_bytes<DQK>();
   own_rows_issue<DQK>(own, a.q, q_row0, q_n, a.q_s, head, lane);
-  Tile cur = tile_at(kr, 0, DQ_BK);
+  Tile cur = tile_at(kr, t0, DQ_BK);
   dq_issue(smem, a, cur, kv_head, wave);
   // rows past the end repeat the last one (an empty wave the item's first row)
   const int mc = q_n > 0 ? min(m, q_n - 1) : -32 * wave;
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
     }
     barrier_lds();
     if (t + 1 < n_tiles) {
-      cur = tile_at(kr, t + 1, DQ_BK);
+      cur = tile_at(kr, t0 + t + 1, DQ_BK);
       dq_issue(smem + ((t + 1) % DQ_NSTAGE) * DQ_STAGE, a, cur, kv_head, wave);
     }
     // a wave none of whose rows sees the tile leaves the matrix cores to the others
@@ -177,6 +177,10 @@ __global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
     });
   }
 
+  if (it.part >= 0) {
+    part_store(part_at(a, hl, it.part, DQ_PART_BYTES) + wave * PART_WAVE_192, lane_now(), acc);
+    return;
+  }
   barrier_lds();  // every wave is past its last tile
   rows_add<DQK / 64>(smem + wave * ROWS_OUT_BYTES, lane_now(), acc, a.scale, a.dq + ((int64_t)q_row0 * a.H + head) * DQK,
                      a.H * DQK, q_n);
@@ -264,7 +268,8 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
   const int head0 = kv_head * a.grp;
   const Item it(a.items, item_idx);
   const TileRanges qr = tile_ranges(it, KV_BQ);
-  const int n_tiles = qr.nt * a.grp;  // (query head, query tile) pairs
+  // this unit's (query head, query tile) pairs
+  const int t0 = it.t0, n_tiles = (it.t1 < 0 ? qr.nt * a.grp : it.t1) - t0;
   if (n_tiles == 0) return;  // uniform over the workgroup
   const int k_row0 = it.row0, k_pos0 = it.pos0, k_n = it.n;
 
@@ -294,7 +299,8 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
     // of dP) and dK^T
     constexpr int NF = ROLE == 0 ? DQK / 16 : DV / 16;
     constexpr int NACC = ROLE == 0 ? DV / 32 : DQK / 32;
-    KvTile cur = kv_tile(qr, 0, qr.nt - 1);
+    const int member0 = t0 / qr.nt;
+    KvTile cur = kv_tile(qr, member0, qr.nt - 1 - (t0 - member0 * qr.nt));
     // the pair's K (role A) and V rows (role B) come through LDS, from the start of stage 1 on
     static_assert(KV_STAGE + 4 * (own_bytes<DQK>() + own_bytes<DV>()) <= KV_LDS, "LDS");
     bf16x8 bf[NF];
@@ -491,6 +497,11 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
       }
     }
 
+    if (it.part >= 0) {
+      char* p = part_at(a, kvl, it.part, KV_PART_BYTES);
+      part_store(p + (ROLE == 0 ? pair * PART_WAVE_128 : 4 * PART_WAVE_128 + pair * PART_WAVE_192), lane_now(), acc);
+      return;
+    }
     barrier_lds();  // every wave is past its last tile
     const int64_t krow = (int64_t)(k_row0 + pair * 32) * a.Hkv + kv_head;
     if constexpr (ROLE == 0)
@@ -699,11 +710,70 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
                      a.H * DQK, wave_rows ? 32 : 0);
 }
 
+// ------------------------------------------------------------------ merges of split items
+// One workgroup of one wave per 32 rows x 64 columns: the sum of the parts in their order, added
+// to the accumulator.  DQ: three column groups of the eight waves' dQ rows of a query item;
+// otherwise two of the four pairs' dV rows and three of their dK rows of a key item.
+template <bool DQ> constexpr int merge_blocks() { return DQ ? 8 * (DQK / 64) : 4 * (DV / 64 + DQK / 64); }
+
+template <bool DQ>
+__global__ __launch_bounds__(64) void bwd_merge_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[ROWS_OUT_BYTES];
+  const int heads = DQ ? a.q_heads : a.kv_heads, lane = threadIdx.x;
+  const int piece = blockIdx.x % merge_blocks<DQ>(), rest = blockIdx.x / merge_blocks<DQ>();
+  const int hl = rest % heads;
+  const int* mg = a.merges + (rest / heads) * 4;
+  const bool dv = !DQ && piece < 4 * (DV / 64);
+  const int k = DQ || dv ? piece : piece - 4 * (DV / 64), block = DQ ? k % 8 : k % 4, g = DQ ? k / 8 : k / 4;
+  const int rows = min(32, mg[1] - 32 * block), n = mg[3];
+  if (rows <= 0) return;
+  const int64_t row0 = mg[0] + 32 * block;
+  const int part_bytes = DQ ? DQ_PART_BYTES : KV_PART_BYTES;
+  const char* p = part_at(a, hl, mg[2], part_bytes);
+  float* out;
+  int pitch;
+  if constexpr (DQ) {
+    p += block * PART_WAVE_192;
+    out = a.dq + (row0 * a.H + a.q_head0 + hl) * DQK;
+    pitch = a.H * DQK;
+  } else {
+    const int64_t at = row0 * a.Hkv + a.kv_head0 + hl;
+    p += dv ? block * PART_WAVE_128 : 4 * PART_WAVE_128 + block * PART_WAVE_192;
+    out = dv ? a.dv + at * DV : a.dk + at * DQK;
+    pitch = a.Hkv * (dv ? DV : DQK);
+  }
+  f32x16 acc[2];
+  parts_sum(p, part_bytes, n, g, lane, [](int) { return 1.0f; }, acc);
+  rows_add<1>((lds_char*)smem_raw, lane, acc, dv ? 1.0f : a.scale, out + 64 * g, pitch, rows);
+}
+
+namespace {
+
+// A launch of `kernel` over a list, then the merge of its split items.
+template <bool DQ, class K>
+hipError_t launch_list(K kernel, const char* name, AttnArgs a, const Launch& l, int heads, hipStream_t stream) {
+  if (l.n_units == 0) return hipSuccess;
+  a.items = l.units;
+  a.n_items = l.n_units;
+  a.merges = l.merges;
+  a.n_parts = l.parts;
+  int tok = prof_begin(name, stream);
+  hipLaunchKernelGGL(kernel, dim3(l.n_units * heads), dim3(512), 0, stream, a);
+  prof_end(tok, stream);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || l.n_merges == 0) return e;
+  tok = prof_begin(DQ ? "bwd_dq_merge" : "bwd_dkdv_merge", stream);
+  hipLaunchKernelGGL(bwd_merge_kernel<DQ>, dim3(l.n_merges * heads * merge_blocks<DQ>()), dim3(64), 0, stream, a);
+  prof_end(tok, stream);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 // kv_heads_per_pass = 0: recompute path (bwd_dq + bwd_dkdv over all heads).  Otherwise the
 // stored-dS path, in passes of that many K/V heads (the dS of one pass's query heads fits
 // a.ds): bwd_dkdv<true> stores dS, then bwd_dq_ds reads it back.
-hipError_t launch_attn_bwd(const AttnArgs& a, int n_qitems, int n_kitems, const int* kitems, int kv_heads_per_pass,
-                           hipStream_t stream) {
+hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
+                           int kv_heads_per_pass, hipStream_t stream) {
   const int64_t pairs = (int64_t)a.nq * a.H;
   const int64_t blocks = (pairs + 15) / 16 < (1 << 20) ? (pairs + 15) / 16 : (1 << 20);
   int tok = prof_begin("bwd_pre", stream);
@@ -713,49 +783,21 @@ hipError_t launch_attn_bwd(const AttnArgs& a, int n_qitems, int n_kitems, const 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (kv_heads_per_pass > 0) {
-    if (n_qitems == 0 || n_kitems == 0) return hipSuccess;
+    if (q_whole.n_units == 0 || kv.n_units == 0) return hipSuccess;
     for (int g0 = 0; g0 < a.Hkv; g0 += kv_heads_per_pass) {
       const int G = min(kv_heads_per_pass, a.Hkv - g0);
       AttnArgs b = a;
-      b.items = kitems;
-      b.n_items = n_kitems;
       b.kv_head0 = g0;
       b.kv_heads = G;
       b.q_head0 = g0 * a.grp;
       b.q_heads = G * a.grp;
-      tok = prof_begin("bwd_dkdv_ds", stream);
-      hipLaunchKernelGGL(bwd_dkdv_kernel<true>, dim3(n_kitems * G), dim3(512), 0, stream, b);
-      prof_end(tok, stream);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      AttnArgs c = b;
-      c.items = a.items;
-      c.n_items = n_qitems;
-      tok = prof_begin("bwd_dq_ds", stream);
-      hipLaunchKernelGGL(bwd_dq_ds_kernel, dim3(n_qitems * G * a.grp), dim3(512), 0, stream, c);
-      prof_end(tok, stream);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+      if ((e = launch_list<false>(bwd_dkdv_kernel<true>, "bwd_dkdv_ds", b, kv, G, stream)) != hipSuccess) return e;
+      if ((e = launch_list<true>(bwd_dq_ds_kernel, "bwd_dq_ds", b, q_whole, G * a.grp, stream)) != hipSuccess) return e;
     }
     return hipSuccess;
   }
-  if (n_qitems > 0) {
-    AttnArgs b = a;
-    b.n_items = n_qitems;
-    tok = prof_begin("bwd_dq", stream);
-    hipLaunchKernelGGL(bwd_dq_kernel, dim3(n_qitems * a.H), dim3(64 * DQ_WAVES), 0, stream, b);
-    prof_end(tok, stream);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (n_kitems > 0) {
-    AttnArgs b = a;
-    b.items = kitems;
-    b.n_items = n_kitems;
-    tok = prof_begin("bwd_dkdv", stream);
-    hipLaunchKernelGGL(bwd_dkdv_kernel<false>, dim3(n_kitems * a.Hkv), dim3(512), 0, stream, b);
-    prof_end(tok, stream);
-    e = hipGetLastError();
-  }
-  return e;
+  if ((e = launch_list<true>(bwd_dq_kernel, "bwd_dq", a, dq, a.H, stream)) != hipSuccess) return e;
+  return launch_list<false>(bwd_dkdv_kernel<false>, "bwd_dkdv", a, kv, a.Hkv, stream);
 }
 
 }  // namespace hydra

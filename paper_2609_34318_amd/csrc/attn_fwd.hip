@@ -20,7 +20,7 @@
 
 namespace hydra {
 
-constexpr int FWD_BK = 64;
+constexpr int FWD_BK = FWD_TILE_ROWS;
 constexpr int FWD_KBYTES = FWD_BK * DQK * 2;             // 24 KB
 constexpr int FWD_STAGE = FWD_KBYTES + FWD_BK * DV * 2;  // 40 KB
 constexpr int FWD_NSTAGE = 2;  // measured faster than three stages
@@ -32,6 +32,34 @@ constexpr float RESCALE_SLACK = 8.0f;
 __device__ __forceinline__ void fwd_issue(lds_char* stage, const AttnArgs& a, const Tile k, int koff, int voff, int wave) {
   dma_tile<DQK, FWD_BK, FWD_WAVES>(stage, tile_rsrc(a.k, k.row0, k.n, a.k_s), koff, a.k_s, wave);
   dma_tile<DV, FWD_BK, FWD_WAVES>(stage + FWD_KBYTES, tile_rsrc(a.v, k.row0, k.n, a.v_s), voff, a.v_s, wave);
+}
+
+// A wave's rows [q_row0, q_row0 + q_n), column groups G0 .. G0 + NG - 1 of 64, out: O = acc / l
+// (and its bf16 copy), and with the first group the LSE from the running max and sum.  obuf:
+// ROWS_OUT_BYTES of LDS of the wave's own.
+template <int G0, int NG>
+__device__ __forceinline__ void fwd_out(const AttnArgs& a, uint16_t* o_bf16, lds_char* obuf, int head, int q_row0,
+                                        int q_n, int lane, const f32x16 (&acc)[2 * NG], float m_run, float l_tot) {
+  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+  if (G0 == 0 && lane < q_n)
+    a.out_lse[(int64_t)head * a.nq + q_row0 + lane] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
+  const int64_t base = ((int64_t)q_row0 * a.H + head) * DV;
+  const int rows = max(q_n, 0), pitch = a.H * DV;
+  const rows_rsrc ro = rows_buffer(a.out_o + base, rows, pitch * 4);
+  const rows_rsrc rb = rows_buffer(o_bf16 + base, o_bf16 ? rows : 0, pitch * 2);
+  static_for<NG>([&](auto g_) {
+    constexpr int gi = decltype(g_)::value, g = G0 + gi;
+    rows_stage<gi>(obuf, lane, acc, inv);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const f32x4 val = rows_read(obuf, lane, i);
+      const int off = rows_row(lane, i) * pitch + rows_col(lane, i);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, off * 4 + 256 * g, 0, 0);
+      if (o_bf16)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])}, rb,
+                                              off * 2 + 128 * g, 0, 0);
+    }
+  });
 }
 
 __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
@@ -49,7 +77,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
   xcd_head_item(blockIdx.x, a.H, a.n_items, head, item);
   const Item it(a.items, item);
   const TileRanges kr = tile_ranges(it, FWD_BK);
-  const int n_tiles = kr.nt;
+  const int t0 = it.t0, n_tiles = (it.t1 < 0 ? kr.nt : it.t1) - t0;  // this unit's tiles
   const int kv_head = head / a.grp;  // grouped K/V heads: contiguous groups of query heads
   const int koff = dma_lane_off<DQK>(a.k_s, kv_head, wave, lane);
   const int voff = dma_lane_off<DV>(a.v_s, kv_head, wave, lane);
@@ -63,7 +91,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
 
   lds_char* qbuf = smem + FWD_STAGE + wave * own_bytes<DQK>();
   own_rows_issue<DQK>(qbuf, a.q, q_row0, max(q_n, 0), a.q_s, head, lane);
-  Tile cur = tile_at(kr, 0, FWD_BK);  // with no tile: of no rows
+  Tile cur = tile_at(kr, t0, FWD_BK);  // with no tile: of no rows
   fwd_issue(smem, a, cur, koff, voff, wave);
 
   // document starts: of this lane's row, of the wave's first and last row
@@ -90,7 +118,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
     if (kn < FWD_BK) clear_tail<DV, FWD_BK, FWD_WAVES>(Vs, kn, wave, lane_now());
     barrier_lds();
     if (t + 1 < n_tiles) {
-      cur = tile_at(kr, t + 1, FWD_BK);
+      cur = tile_at(kr, t0 + t + 1, FWD_BK);
       fwd_issue(smem + ((t + 1) % FWD_NSTAGE) * FWD_STAGE, a, cur, koff, voff, wave);
     }
     // a wave none of whose rows sees the tile (the diagonal's upper half, another document)
@@ -183,34 +211,55 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
   }
 
   const float l_tot = xhalf_sum((l_run[0] + l_run[1]) + (l_run[2] + l_run[3]));
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if (q_valid && hh == 0)
-    a.out_lse[(int64_t)head * a.nq + q_row0 + m] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
   barrier_lds();  // every wave is past its last tile
-  lds_char* obuf = smem + wave * ROWS_OUT_BYTES;
-  const int64_t base = ((int64_t)q_row0 * a.H + head) * DV;
-  const int rows = max(q_n, 0), pitch = a.H * DV;
-  const rows_rsrc ro = rows_buffer(a.out_o + base, rows, pitch * 4);
-  const rows_rsrc rb = rows_buffer(o_bf16 + base, o_bf16 ? rows : 0, pitch * 2);
-  static_for<DV / 64>([&](auto g_) {
-    constexpr int g = decltype(g_)::value;
-    rows_stage<g>(obuf, lane, acc, inv);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const f32x4 val = rows_read(obuf, lane, i);
-      const int off = rows_row(lane, i) * pitch + rows_col(lane, i);
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, off * 4 + 256 * g, 0, 0);
-      if (o_bf16)
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3])}, rb,
-                                              off * 2 + 128 * g, 0, 0);
-    }
-  });
+  if (it.part >= 0) {
+    char* p = part_at(a, head, it.part, FWD_PART_BYTES) + wave * PART_WAVE_O;
+    part_store(p, lane, acc);
+    *reinterpret_cast<float2*>(p + PART_WAVE_128 + lane * 8) = make_float2(m_run, l_tot);
+    return;
+  }
+  fwd_out<0, DV / 64>(a, o_bf16, smem + wave * ROWS_OUT_BYTES, head, q_row0, q_n, lane, acc, m_run, l_tot);
 }
 
-hipError_t launch_attn_fwd(const AttnArgs& a, uint16_t* o_bf16, hipStream_t stream) {
-  if (a.n_items == 0) return hipSuccess;
-  const int tok = prof_begin("attn_fwd", stream);
+// Merges the parts of a split item: one workgroup of one wave per 32 rows x 64 columns, in the
+// order of the parts.
+__global__ __launch_bounds__(64) void fwd_merge_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[ROWS_OUT_BYTES];
+  const int g = blockIdx.x % 2, wave = blockIdx.x / 2 % FWD_WAVES, rest = blockIdx.x / (2 * FWD_WAVES);
+  const int head = rest % a.H, lane = threadIdx.x;
+  const int* mg = a.merges + (rest / a.H) * 4;
+  const int q_n = min(32, mg[1] - 32 * wave), part0 = mg[2], n = mg[3];
+  if (q_n <= 0) return;
+  const char* p = part_at(a, head, part0, FWD_PART_BYTES) + wave * PART_WAVE_O;
+  auto ml = [&](int j) {
+    return *reinterpret_cast<const float2*>(p + (int64_t)j * FWD_PART_BYTES + PART_WAVE_128 + lane * 8);
+  };
+  float m = NEG_BIG, l = 0.f;
+#pragma unroll 4
+  for (int j = 0; j < n; ++j) m = fmax2(m, ml(j).x);
+#pragma unroll 4
+  for (int j = 0; j < n; ++j) l += __builtin_amdgcn_exp2f(ml(j).x - m) * ml(j).y;  // a part that saw nothing: l = 0
+  f32x16 acc[2];
+  parts_sum(p, FWD_PART_BYTES, n, g, lane, [&](int j) { return __builtin_amdgcn_exp2f(ml(j).x - m); }, acc);
+  if (g == 0)
+    fwd_out<0, 1>(a, o_bf16, (lds_char*)smem_raw, head, mg[0] + 32 * wave, q_n, lane, acc, m, l);
+  else
+    fwd_out<1, 1>(a, o_bf16, (lds_char*)smem_raw, head, mg[0] + 32 * wave, q_n, lane, acc, m, l);
+}
+
+hipError_t launch_attn_fwd(const AttnArgs& args, const Launch& l, uint16_t* o_bf16, hipStream_t stream) {
+  if (l.n_units == 0) return hipSuccess;
+  AttnArgs a = args;
+  a.items = l.units;
+  a.n_items = l.n_units;
+  a.merges = l.merges;
+  a.n_parts = l.parts;
+  int tok = prof_begin("attn_fwd", stream);
   hipLaunchKernelGGL(attn_fwd_kernel, dim3(a.n_items * a.H), dim3(64 * FWD_WAVES), 0, stream, a, o_bf16);
+  prof_end(tok, stream);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || l.n_merges == 0) return e;
+  tok = prof_begin("attn_fwd_merge", stream);
+  hipLaunchKernelGGL(fwd_merge_kernel, dim3(l.n_merges * a.H * FWD_WAVES * (DV / 64)), dim3(64), 0, stream, a, o_bf16);
   prof_end(tok, stream);
   return hipGetLastError();
 }

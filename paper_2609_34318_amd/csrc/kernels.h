@@ -460,6 +460,42 @@ __device__ __forceinline__ void rows_add(lds_char* buf, int lane, const f32x16 (
   });
 }
 
+// A wave's accumulators to and from its place in a part (see tiles.h).
+template <int N> __device__ __forceinline__ void part_store(char* p, int lane, const f32x16 (&acc)[N]) {
+#pragma unroll
+  for (int d = 0; d < N; ++d)
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr)
+      *reinterpret_cast<f32x4*>(p + (4 * d + rr) * 1024 + lane * 16) =
+          f32x4{acc[d][4 * rr], acc[d][4 * rr + 1], acc[d][4 * rr + 2], acc[d][4 * rr + 3]};
+}
+// Column blocks 2 g and 2 g + 1 of n parts, `part_bytes` apart, summed in the order of the parts
+// with weights w(j).  Four parts' loads are in flight at a time.
+template <class W>
+__device__ __forceinline__ void parts_sum(const char* p, int part_bytes, int n, int g, int lane, W&& w, f32x16 (&acc)[2]) {
+#pragma unroll
+  for (int d = 0; d < 2; ++d) acc[d] = f32x16{};
+  constexpr int AHEAD = 4;
+  for (int j0 = 0; j0 < n; j0 += AHEAD) {
+    f32x4 v[AHEAD][8];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)  // past the last part: that part again, not added
+        v[u][i] = *reinterpret_cast<const f32x4*>(p + (int64_t)min(j0 + u, n - 1) * part_bytes + (8 * g + i) * 1024 +
+                                                  lane * 16);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      if (j0 + u >= n) break;
+      const float x = w(j0 + u);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i >> 2][4 * (i & 3) + e] += x * v[u][i][e];
+    }
+  }
+}
+
 // 64 fp32 values (valid of them in range) -> LDS, one wave.
 __device__ __forceinline__ void dma_vec64(lds_char* lds, const float* g, int valid, int lane) {
   dma4(__builtin_amdgcn_readfirstlane(lds_addr(lds)), tile_desc(g, 0, valid * 4), lane * 4);
@@ -522,6 +558,7 @@ struct Item {
   int r0, p0, c0, r1, p1, c1, r2, p2, c2, r3, p3, c3;
   int edge0, lo_last, d0, d1;  // document boundary of the first row, start of the last row's, their indices
   int x0, x1, x2, x3;          // query items: first key record of each range; key items: x0 = first dS slot
+  int t0, t1, part;            // tiles of the walk (t1 < 0: to its end), part of a split item or -1
 
   __device__ __forceinline__ Item(const int* items, int idx) {
     const int* s = items + (int64_t)idx * UNIT_INTS;
@@ -549,6 +586,9 @@ struct Item {
     x1 = __builtin_amdgcn_readfirstlane(s[21]);
     x2 = __builtin_amdgcn_readfirstlane(s[22]);
     x3 = __builtin_amdgcn_readfirstlane(s[23]);
+    t0 = __builtin_amdgcn_readfirstlane(s[24]);
+    t1 = __builtin_amdgcn_readfirstlane(s[25]);
+    part = __builtin_amdgcn_readfirstlane(s[26]);
   }
 };
 
@@ -623,7 +663,23 @@ struct AttnArgs {
   char* ds;
   int64_t ds_head_bytes;
   const int* krec;
-  const int* kitems;   // key-stationary items
+  // split launches: the parts of all heads, parts per head, and the split items (merges)
+  char* split;
+  int n_parts;
+  const int* merges;
+};
+
+// Part `part` of the launch's head `hl`.
+__device__ __forceinline__ char* part_at(const AttnArgs& a, int hl, int part, int part_bytes) {
+  return a.split + ((int64_t)hl * a.n_parts + part) * part_bytes;
+}
+
+// A launch list on the device (host side of a launch).
+struct Launch {
+  const int* units;
+  int n_units;
+  const int* merges;
+  int n_merges, parts;
 };
 
 }  // namespace hydra

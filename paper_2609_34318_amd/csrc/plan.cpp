@@ -60,6 +60,12 @@ void tiles_of(const hydra_chunk_t& c, int rows_per_tile, std::vector<Tile>* out)
   }
 }
 
+int64_t n_tiles(const hydra_chunk_t& c, int rows_per_tile) {
+  int64_t n = 0;
+  for (int s = 0; s < c.n_segs; ++s) n += (c.len[s] + rows_per_tile - 1) / rows_per_tile;
+  return n;
+}
+
 // Ranges of local rows of chunk `c` whose positions fall in [lo, hi] (inclusive).
 int ranges_in(const hydra_chunk_t& c, int64_t lo, int64_t hi, int32_t* dst) {
   int n = 0;
@@ -192,12 +198,123 @@ void launch_units(const Problem& pr, int which, const std::vector<int32_t>& item
     u[17] = pr.cu[d1];
     u[18] = d0;
     u[19] = d1;
+    u[25] = u[26] = -1;
     if (table.empty()) continue;
     if (which == 0)
       for (int r = 0; r < it[3]; ++r) u[20 + r] = table[size_t(it[4 + 3 * r]) / 32];
     else
       u[20] = table[i];
   }
+}
+
+namespace {
+
+constexpr int kCus = 256;
+
+// Workgroups of a launch below which splitting is considered at all.  At two per CU and more the
+// heavy-first order fills the chip: no shape measured there gained.
+constexpr int64_t kSplitBelow = 2 * kCus;
+
+// In tiles of the kernel's loop: what a workgroup costs besides its tiles (its own rows in, the
+// first copies, its rows out), and the merge launch.  Measured, 2.4 GHz: a forward tile takes
+// 1.7 us, a dQ tile 3.0 us, a dK/dV tile 2.9 us; a workgroup's own cost 4-6 us, a merge 5-7 us.
+struct SplitCost {
+  double group, merge;
+};
+SplitCost split_cost(Kernel k) {
+  return k == Kernel::kFwd ? SplitCost{3.0, 4.0} : SplitCost{2.0, 2.5};
+}
+
+// Parts are of four tiles and more; items of fewer than eight stay whole.
+constexpr int64_t kMinPart = 4;
+
+int tile_rows(Kernel k) { return k == Kernel::kFwd ? FWD_TILE_ROWS : k == Kernel::kDq ? DQ_TILE_ROWS : KV_QTILE_ROWS; }
+
+// At least as many parts as any launch of this kernel can have over all its heads (0: none is
+// split): workspace sizes are asked for without a plan.
+int64_t parts_bound(const Problem& pr, Kernel kernel) {
+  const bool kv = kernel == Kernel::kDkdv;
+  const int64_t n = kv ? n_tiles(pr.kv, kKvTile) : n_tiles(pr.q, kQTile);
+  const int64_t most = kv ? n_tiles(pr.q, KV_QTILE_ROWS) * (pr.H / pr.Hkv) : n_tiles(pr.kv, tile_rows(kernel));
+  // a dK/dV launch may hold one K/V head only
+  if (n * (kv ? 1 : pr.H) >= kSplitBelow || most < 2 * kMinPart) return 0;
+  return std::min<int64_t>(MAX_PARTS, n * ((most + kMinPart - 1) / kMinPart) * (kv ? pr.Hkv : pr.H));
+}
+
+int64_t record_tiles(const Problem& pr, Kernel kernel, const int32_t* u) {
+  const int rows = tile_rows(kernel);
+  int64_t t = 0;
+  for (int r = 0; r < u[3]; ++r) t += (u[4 + 3 * r + 2] + rows - 1) / rows;
+  return kernel == Kernel::kDkdv ? t * (pr.H / pr.Hkv) : t;
+}
+
+}  // namespace
+
+void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out) {
+  *out = UnitList{};
+  const int64_t n = int64_t(records.size()) / kUnitInts;
+  if (n == 0 || heads <= 0 || n * heads >= kSplitBelow) return;
+  std::vector<int64_t> tiles(static_cast<size_t>(n));
+  int64_t longest = 0;
+  for (int64_t i = 0; i < n; ++i) {
+    tiles[size_t(i)] = record_tiles(pr, kernel, &records[size_t(i) * kUnitInts]);
+    longest = std::max(longest, tiles[size_t(i)]);
+  }
+  if (longest < 2 * kMinPart) return;
+  // The launch's time with items of more than `most` tiles cut into near-equal parts: one round
+  // ends with its longest workgroup; several are filled evenly but for about half a workgroup.
+  const SplitCost cost = split_cost(kernel);
+  auto parts_of = [](int64_t t, int64_t most) { return t > most ? (t + most - 1) / most : int64_t(1); };
+  auto time_of = [&](int64_t most, int64_t* parts) {
+    int64_t units = 0;
+    double sum = 0, top = 0;
+    *parts = 0;
+    for (int64_t t : tiles) {
+      const int64_t k = parts_of(t, most);
+      units += k;
+      if (k > 1) *parts += k;
+      sum += double(t) + double(k) * cost.group;
+      top = std::max(top, double((t + k - 1) / k) + cost.group);
+    }
+    if (units * heads <= kCus) return top;
+    return std::max(top, sum * heads / kCus + 0.5 * sum / double(units));
+  };
+  int64_t parts = 0, best_most = longest;
+  double best = time_of(longest, &parts);
+  for (int d = 2; d <= 32; ++d) {
+    const int64_t most = (longest + d - 1) / d;
+    if (most < kMinPart) break;
+    const double t = time_of(most, &parts) + cost.merge;
+    if (parts * heads > MAX_PARTS) break;
+    if (t < best) {
+      best = t;
+      best_most = most;
+    }
+  }
+  if (best_most == longest) return;
+  std::vector<std::pair<int64_t, size_t>> order;  // tiles, unit
+  for (int64_t i = 0; i < n; ++i) {
+    const int32_t* u = &records[size_t(i) * kUnitInts];
+    const int64_t t = tiles[size_t(i)], k = parts_of(t, best_most);
+    if (k > 1) {
+      const int32_t m[kMergeInts] = {u[0], u[2], int32_t(out->parts), int32_t(k)};
+      out->merges.insert(out->merges.end(), m, m + kMergeInts);
+    }
+    for (int64_t j = 0; j < k; ++j) {
+      const size_t at = out->units.size();
+      out->units.insert(out->units.end(), u, u + kUnitInts);
+      out->units[at + 24] = int32_t(t * j / k);
+      out->units[at + 25] = k > 1 ? int32_t(t * (j + 1) / k) : -1;
+      out->units[at + 26] = k > 1 ? out->parts++ : -1;
+      order.push_back({t * (j + 1) / k - t * j / k, at});
+    }
+  }
+  std::stable_sort(order.begin(), order.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  std::vector<int32_t> sorted;
+  sorted.reserve(out->units.size());
+  for (const auto& o : order)
+    sorted.insert(sorted.end(), out->units.begin() + int64_t(o.second), out->units.begin() + int64_t(o.second) + kUnitInts);
+  out->units.swap(sorted);
 }
 
 int64_t visible_pairs(const Problem& pr) {
@@ -261,14 +378,6 @@ int64_t ds_tables(const Problem& pr, const std::vector<int32_t>& kitems, std::ve
   return slots;
 }
 
-namespace {
-int64_t n_tiles(const hydra_chunk_t& c, int rows_per_tile) {
-  int64_t n = 0;
-  for (int s = 0; s < c.n_segs; ++s) n += (c.len[s] + rows_per_tile - 1) / rows_per_tile;
-  return n;
-}
-}  // namespace
-
 uint64_t noalloc_bytes(const Problem& pr) {
   const size_t nq = size_t(n_tiles(pr.q, kQTile)), nk = size_t(n_tiles(pr.kv, kKvTile));
   size_t n = 0;
@@ -292,10 +401,23 @@ WsLayout ws_layout(const Problem& pr) {
   off = align_up(off + size_t(nkt) * kUnitInts * sizeof(int32_t), 256);
   w.krec_off = off;
   off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
+  w.lists_off = off;
+  size_t split_bytes = 0;
+  auto list = [&](Kernel kernel, int64_t n, size_t part_bytes) {
+    const size_t parts = size_t(parts_bound(pr, kernel));
+    split_bytes = std::max(split_bytes, parts * part_bytes);
+    if (parts)
+      off = align_up(off + (size_t(kMaxMerges) * kMergeInts + (parts + size_t(n)) * kUnitInts) * sizeof(int32_t), 256);
+  };
+  list(Kernel::kFwd, nqt, FWD_PART_BYTES);
+  list(Kernel::kDq, nqt, DQ_PART_BYTES);
+  list(Kernel::kDkdv, nkt, KV_PART_BYTES);
   w.d_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
   w.lse2_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
+  w.split_off = off;
+  off += split_bytes;
   w.total = std::max<size_t>(off, 256);
   return w;
 }

@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "hydra_attn.h"
+#include "tiles.h"
 
 namespace hydra {
 
@@ -36,31 +37,51 @@ void plan_items(const Problem& pr, int which, std::vector<int32_t>* items);
 
 int64_t visible_pairs(const Problem& pr);
 
+// The kernel a launch list is for: what a tile of its loop costs, and how many it has.
+enum class Kernel { kFwd, kDq, kDkdv };
+
+// A launch list: the records of the units, and of the split items the merges.
+struct UnitList {
+  std::vector<int32_t> units;   // kUnitInts each, heaviest first; empty: no item is split
+  std::vector<int32_t> merges;  // kMergeInts each: the item's first row, rows, first part, parts
+  int parts = 0;                // parts per head
+};
+constexpr int kMergeInts = 4;
+constexpr int kMaxMerges = MAX_PARTS / 2;  // a split item has at least two parts
+
+// Splits the items of a launch over `heads` heads whose workgroups leave the chip idle (`records`
+// from launch_units).  A unit is a record with [24], [25] its first and last + 1 tile of the
+// item's walk (for dK/dV: of its group * tiles) and [26] its part, or -1 when it is the whole item.
+void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out);
+
 // The launch records of plan_items' work items, in the same order (kUnitInts each): the
 // item's 16 ints, then [16] the document boundary of its first row (its start for query
 // items, its end for key items), [17] the start of its last row's document, [18], [19] the
 // document indices of its first and last row, [20..23] per visible range of a query item the
 // row-order index of the key item that holds the range's first row (see ds_tables), or [20]
-// of a key item its first dS slot.  A kernel that reads one record instead of searching
+// of a key item its first dS slot; [24] = 0, [25] = -1 (all tiles), [26] = -1 (whole).  A kernel that reads one record instead of searching
 // cu_seqlens and the tables has one memory round trip before its first copy, not several.
 void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
                   const std::vector<int32_t>& table, std::vector<int32_t>* units);
 
-// Byte offsets of the workspace regions.
+// Byte offsets of the workspace regions.  lists holds the split lists that a plan has, one after
+// another (merges, then units), of no size for a problem none of whose launches can be split;
+// split the parts.
 struct WsLayout {
-  size_t cu_off, qitems_off, kitems_off, krec_off, d_off, lse2_off, total;
+  size_t cu_off, qitems_off, kitems_off, krec_off, lists_off, d_off, lse2_off, split_off, total;
   int64_t n_qitems, n_kitems;
 };
 WsLayout ws_layout(const Problem& pr);
 
 // What the no-allocation backward's 32 MiB limit is counted on: D, LSE*log2(e), the documents,
 // 64 bytes per query tile, 148 per key tile (its item, its record, its dS slot and its 32-key
-// blocks).  The launch records take more than that, at most 64 bytes per query tile and 48 per
-// key tile: kNoAllocExtraBytes holds them for every problem within the limit, so that a record
-// may grow without a call that was accepted being refused.
+// blocks).  The launch records and split lists take more than that, at most 64 bytes per query
+// tile and 48 per key tile and 128 KB: kNoAllocExtraBytes holds them and the parts for every
+// problem within the limit, so that a plan may grow without a call that was accepted being
+// refused, and the call splits as hydra_attn_bwd does.
 uint64_t noalloc_bytes(const Problem& pr);
 constexpr size_t kNoAllocLimitBytes = size_t(32) << 20;
-constexpr size_t kNoAllocExtraBytes = size_t(12) << 20;
+constexpr size_t kNoAllocExtraBytes = (size_t(12) << 20) + SPLIT_BYTES;
 
 // The stored-dS backward applies when every segment of both chunks starts and ends on a
 // multiple of 32 positions: the key-stationary tiles then cut the query rows into 32-row

@@ -1,0 +1,117 @@
+// Split launch lists of random problems: each item's tiles are covered once by its units, in
+// order; parts are numbered without gaps and fit the scratch; the merges name them; the list
+// fits its workspace region.  Built with g++ (no GPU code) by tests/test_split_units.py.
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <map>
+#include <random>
+#include <vector>
+
+#include "plan.h"
+
+using namespace hydra;
+
+namespace {
+std::mt19937_64 rng(11);
+int64_t uni(int64_t lo, int64_t hi) { return std::uniform_int_distribution<int64_t>(lo, hi)(rng); }
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s (trial %d)\n", #x, trial); return 1; } } while (0)
+}  // namespace
+
+int main() {
+  int split = 0, whole = 0;
+  for (int trial = 0; trial < 600; ++trial) {
+    const int n_docs = int(uni(1, 6));
+    std::vector<int32_t> cu(size_t(n_docs) + 1, 0);
+    for (int d = 0; d < n_docs; ++d) cu[size_t(d) + 1] = cu[size_t(d)] + int32_t(uni(0, trial % 3 ? 3000 : 20000));
+    hydra_problem_t p{};
+    const int grp = int(uni(1, 4));
+    p.n_kv_heads = int32_t(uni(1, 6));
+    p.n_heads = p.n_kv_heads * grp;
+    p.d_qk = 192;
+    p.d_v = 128;
+    p.cu_seqlens = cu.data();
+    p.n_docs = n_docs;
+    for (hydra_chunk_t* c : {&p.q, &p.kv}) {
+      c->n_segs = int32_t(uni(1, 3));
+      for (int s = 0; s < c->n_segs; ++s) {
+        const int64_t a = uni(0, cu.back()), b = uni(a, cu.back());
+        c->start[s] = int32_t(a);
+        c->len[s] = int32_t(b - a);
+      }
+    }
+    Problem pr;
+    CHECK(check_problem(&p, &pr) == HYDRA_OK);
+    const WsLayout w = ws_layout(pr);
+    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
+    size_t list_bytes = 0;
+    for (Kernel k : {Kernel::kFwd, Kernel::kDq, Kernel::kDkdv}) {
+      std::vector<int32_t> items, rec;
+      plan_items(pr, k == Kernel::kDkdv ? 1 : 0, &items);
+      launch_units(pr, k == Kernel::kDkdv ? 1 : 0, items, {}, &rec);
+      const int heads = k == Kernel::kDkdv ? int(uni(1, pr.Hkv)) : pr.H;
+      const int64_t rows = k == Kernel::kFwd ? FWD_TILE_ROWS : k == Kernel::kDq ? DQ_TILE_ROWS : KV_QTILE_ROWS;
+      UnitList l;
+      split_units(pr, k, rec, heads, &l);
+      if (l.units.empty()) {
+        CHECK(l.merges.empty() && l.parts == 0);
+        ++whole;
+        continue;
+      }
+      ++split;
+      CHECK(l.parts * heads <= MAX_PARTS && l.parts >= 2);
+      list_bytes += (l.merges.size() * 4 + 255) / 256 * 256 + (l.units.size() * 4 + 255) / 256 * 256;
+      CHECK(w.lists_off + list_bytes <= w.d_off);
+      CHECK(l.merges.size() <= size_t(kMaxMerges) * kMergeInts);
+      const size_t part = k == Kernel::kFwd ? FWD_PART_BYTES : k == Kernel::kDq ? DQ_PART_BYTES : KV_PART_BYTES;
+      CHECK(w.total >= w.split_off + size_t(l.parts) * size_t(heads) * part);
+      // the units of every item, by first row, in the order of their tiles
+      std::map<int32_t, std::vector<const int32_t*>> by_row;
+      for (size_t i = 0; i < l.units.size(); i += kUnitInts) by_row[l.units[i]].push_back(&l.units[i]);
+      std::vector<int> used(size_t(l.parts), 0);
+      int64_t longest = 0, last = INT64_MAX;
+      for (size_t i = 0; i < l.units.size(); i += kUnitInts) {  // heaviest first
+        const int32_t* u = &l.units[i];
+        int64_t t = 0;
+        for (int r = 0; r < u[3]; ++r) t += (u[4 + 3 * r + 2] + rows - 1) / rows;
+        if (k == Kernel::kDkdv) t *= pr.H / pr.Hkv;
+        const int64_t n = (u[25] < 0 ? t : u[25]) - u[24];
+        CHECK(n <= last);
+        last = n;
+        longest = std::max(longest, n);
+      }
+      size_t n_merges = 0;
+      for (size_t i = 0; i < rec.size(); i += kUnitInts) {
+        const int32_t* it = &rec[i];
+        auto& us = by_row[it[0]];
+        CHECK(!us.empty());
+        for (const int32_t* u : us) CHECK(std::equal(it, it + 24, u));
+        std::sort(us.begin(), us.end(), [](const int32_t* a, const int32_t* b) { return a[24] < b[24]; });
+        if (us.size() == 1) {
+          CHECK(us[0][24] == 0 && us[0][25] == -1 && us[0][26] == -1);
+          continue;
+        }
+        int64_t t = 0;
+        for (int r = 0; r < it[3]; ++r) t += (it[4 + 3 * r + 2] + rows - 1) / rows;
+        if (k == Kernel::kDkdv) t *= pr.H / pr.Hkv;
+        int32_t next = 0;
+        for (size_t j = 0; j < us.size(); ++j) {
+          CHECK(us[j][24] == next && us[j][25] > next && us[j][26] == us[0][26] + int32_t(j));
+          next = us[j][25];
+          ++used[size_t(us[j][26])];
+        }
+        CHECK(next == t);
+        bool named = false;
+        for (size_t g = 0; g < l.merges.size(); g += kMergeInts)
+          if (l.merges[g] == it[0])
+            named = l.merges[g + 1] == it[2] && l.merges[g + 2] == us[0][26] && l.merges[g + 3] == int32_t(us.size());
+        CHECK(named);
+        ++n_merges;
+      }
+      CHECK(n_merges * kMergeInts == l.merges.size());
+      CHECK(std::all_of(used.begin(), used.end(), [](int x) { return x == 1; }));
+    }
+  }
+  std::printf("split %d whole %d\n", split, whole);
+  return 0;
+}
