@@ -111,6 +111,15 @@ int hydra_attn_fwd(const hydra_problem_t* p, const void* q, const void* k, const
                    float* o_part, float* lse_part, void* o_part_bf16,
                    void* workspace, size_t workspace_bytes, void* stream);
 
+/* A later ring step: the partial that hydra_attn_fwd would write, merged into o_acc and lse_acc as
+ * hydra_lse_merge merges it, in the same kernel (o_acc and lse_acc hold the merge of the earlier
+ * steps; a row that sees no key of this chunk keeps its values).  o_bf16: NULL, or receives the
+ * merged O of every row.  planned != 0: the plan is in the workspace (hydra_attn_plan), as for
+ * hydra_attn_fwd_planned.  Arguments and checks as hydra_attn_fwd. */
+int hydra_attn_fwd_merge(const hydra_problem_t* p, const void* q, const void* k, const void* v,
+                         float* o_acc, float* lse_acc, void* o_bf16, void* workspace,
+                         size_t workspace_bytes, int32_t planned, void* stream);
+
 /* Backward of one ring step, given the FINAL merged output and LSE of the rows (the same
  * function is differentiated at every step):
  *   o_final [Nq][H][128] bf16, lse_final [H][Nq] fp32, d_o [Nq][H][128] bf16

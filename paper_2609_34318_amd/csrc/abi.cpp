@@ -15,7 +15,7 @@
 #include "prof.h"
 
 namespace hydra {
-hipError_t launch_attn_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, hipStream_t stream);
+hipError_t launch_attn_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, bool merge, hipStream_t stream);
 hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
                            int kv_heads_per_pass, hipStream_t stream);
 hipError_t launch_lse_merge(int64_t n_rows, int H, float* o_acc, float* lse_acc, const float* o_part,
@@ -255,8 +255,8 @@ size_t hydra_workspace_size(const hydra_problem_t* p) {
 namespace {
 
 // Forward of one ring step; `upload` = false launches only (the plan is already in the
-// workspace, from hydra_attn_plan).
-int attn_fwd_impl(bool upload, const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
+// workspace, from hydra_attn_plan); `merge` = true merges the partial into o_part and lse_part.
+int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
                   float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
   try {
     Problem pr;
@@ -292,7 +292,7 @@ int attn_fwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     a.out_o = o_part;
     a.out_lse = lse_part;
     const Launch l = list_launch(workspace, w.qitems_off, w.n_qitems, plan.fwd);
-    if (launch_attn_fwd(a, l, static_cast<uint16_t*>(o_bf16), s) != hipSuccess) return HYDRA_ERR_HIP;
+    if (launch_attn_fwd(a, l, static_cast<uint16_t*>(o_bf16), merge, s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
     return HYDRA_ERR_INVALID;
@@ -399,12 +399,18 @@ int hydra_attn_plan(const hydra_problem_t* p, void* workspace, size_t workspace_
 
 int hydra_attn_fwd(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
                    float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
-  return attn_fwd_impl(true, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
+  return attn_fwd_impl(true, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
 }
 
 int hydra_attn_fwd_planned(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
                            float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
-  return attn_fwd_impl(false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
+  return attn_fwd_impl(false, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
+}
+
+int hydra_attn_fwd_merge(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_acc,
+                         float* lse_acc, void* o_bf16, void* workspace, size_t workspace_bytes, int32_t planned,
+                         void* stream) {
+  return attn_fwd_impl(planned == 0, true, p, q, k, v, o_acc, lse_acc, o_bf16, workspace, workspace_bytes, stream);
 }
 
 int hydra_attn_bwd(const hydra_problem_t* p, const void* q, const void* k, const void* v, const void* o_final,

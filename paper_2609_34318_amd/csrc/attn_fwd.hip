@@ -34,25 +34,57 @@ __device__ __forceinline__ void fwd_issue(lds_char* stage, const AttnArgs& a, co
   dma_tile<DV, FWD_BK, FWD_WAVES>(stage + FWD_KBYTES, tile_rsrc(a.v, k.row0, k.n, a.v_s), voff, a.v_s, wave);
 }
 
+// LSE of the earlier steps for this lane's row m of a wave's rows (-inf past their end).
+__device__ __forceinline__ float fwd_old_lse(const AttnArgs& a, int head, int q_row0, int q_n, int lane) {
+  const int m = lane & 31;
+  return m < q_n ? a.out_lse[(int64_t)head * a.nq + q_row0 + m] : -INFINITY;
+}
+
 // A wave's rows [q_row0, q_row0 + q_n), column groups G0 .. G0 + NG - 1 of 64, out: O = acc / l
 // (and its bf16 copy), and with the first group the LSE from the running max and sum.  obuf:
 // ROWS_OUT_BYTES of LDS of the wave's own.
-template <int G0, int NG>
+// MERGE: O and LSE already hold the merge of the earlier ring steps (old_lse: that LSE), and this
+// step's partial is merged into them here.  Written out on its own and merged by a second kernel,
+// the partial costs a launch, its write and its read: 256K ring step, 32K rows x 16 heads, 170 us
+// per step against 10 to 20 here.
+template <bool MERGE, int G0, int NG>
 __device__ __forceinline__ void fwd_out(const AttnArgs& a, uint16_t* o_bf16, lds_char* obuf, int head, int q_row0,
-                                        int q_n, int lane, const f32x16 (&acc)[2 * NG], float m_run, float l_tot) {
+                                        int q_n, int lane, const f32x16 (&acc)[2 * NG], float m_run, float l_tot,
+                                        float old_lse) {
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if (G0 == 0 && lane < q_n)
-    a.out_lse[(int64_t)head * a.nq + q_row0 + lane] = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
+  float lse = l_tot > 0.f ? (m_run + __builtin_log2f(l_tot)) * LN2 : -INFINITY;
   const int64_t base = ((int64_t)q_row0 * a.H + head) * DV;
   const int rows = max(q_n, 0), pitch = a.H * DV;
   const rows_rsrc ro = rows_buffer(a.out_o + base, rows, pitch * 4);
   const rows_rsrc rb = rows_buffer(o_bf16 + base, o_bf16 ? rows : 0, pitch * 2);
+  float wa[8], wb[8];  // of the rows that this lane stores
+  if constexpr (MERGE) {
+    float a_m, b_m;
+    merge_weights(old_lse, lse, lse, a_m, b_m);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      wa[i] = __shfl(a_m, rows_row(lane, i), 64);
+      wb[i] = __shfl(b_m, rows_row(lane, i), 64);
+    }
+  }
+  if (G0 == 0 && lane < q_n) a.out_lse[(int64_t)head * a.nq + q_row0 + lane] = lse;
   static_for<NG>([&](auto g_) {
     constexpr int gi = decltype(g_)::value, g = G0 + gi;
+    f32x4 old[8];
+    if constexpr (MERGE) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        old[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                               ro, (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0));
+    }
     rows_stage<gi>(obuf, lane, acc, inv);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const f32x4 val = rows_read(obuf, lane, i);
+      f32x4 val = rows_read(obuf, lane, i);
+      if constexpr (MERGE) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[e] = merge_value(wa[i], old[i][e], wb[i], val[e]);
+      }
       const int off = rows_row(lane, i) * pitch + rows_col(lane, i);
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, off * 4 + 256 * g, 0, 0);
       if (o_bf16)
@@ -62,6 +94,7 @@ __device__ __forceinline__ void fwd_out(const AttnArgs& a, uint16_t* o_bf16, lds
   });
 }
 
+template <bool MERGE>
 __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
   // stage 0 | stage 1; before the loop the waves' Q rows from the start of stage 1, after it
   // their outputs
@@ -78,6 +111,8 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
   const Item it(a.items, item);
   const TileRanges kr = tile_ranges(it, FWD_BK);
   const int t0 = it.t0, n_tiles = (it.t1 < 0 ? kr.nt : it.t1) - t0;  // this unit's tiles
+  // nothing to add to the earlier steps, which leaves only their bf16 copy (uniform)
+  if (MERGE && n_tiles == 0 && !o_bf16) return;
   const int kv_head = head / a.grp;  // grouped K/V heads: contiguous groups of query heads
   const int koff = dma_lane_off<DQK>(a.k_s, kv_head, wave, lane);
   const int voff = dma_lane_off<DV>(a.v_s, kv_head, wave, lane);
@@ -218,15 +253,19 @@ __global__ __launch_bounds__(64 * FWD_WAVES, 1) void attn_fwd_kernel(AttnArgs a,
     *reinterpret_cast<float2*>(p + PART_WAVE_128 + lane * 8) = make_float2(m_run, l_tot);
     return;
   }
-  fwd_out<0, DV / 64>(a, o_bf16, smem + wave * ROWS_OUT_BYTES, head, q_row0, q_n, lane, acc, m_run, l_tot);
+  const float old_lse = MERGE ? fwd_old_lse(a, head, q_row0, q_n, lane) : 0.f;
+  fwd_out<MERGE, 0, DV / 64>(a, o_bf16, smem + wave * ROWS_OUT_BYTES, head, q_row0, q_n, lane, acc, m_run, l_tot,
+                             old_lse);
 }
 
-// Merges the parts of a split item: one workgroup of one wave per 32 rows x 64 columns, in the
+// Merges the parts of a split item: one workgroup of two waves per 32 rows, 64 columns each, in the
 // order of the parts.
-__global__ __launch_bounds__(64) void fwd_merge_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[ROWS_OUT_BYTES];
-  const int g = blockIdx.x % 2, wave = blockIdx.x / 2 % FWD_WAVES, rest = blockIdx.x / (2 * FWD_WAVES);
-  const int head = rest % a.H, lane = threadIdx.x;
+template <bool MERGE>
+__global__ __launch_bounds__(128) void fwd_merge_kernel(AttnArgs a, uint16_t* __restrict__ o_bf16) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[2 * ROWS_OUT_BYTES];
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wave = blockIdx.x % FWD_WAVES, rest = blockIdx.x / FWD_WAVES;
+  const int head = rest % a.H;
   const int* mg = a.merges + (rest / a.H) * 4;
   const int q_n = min(32, mg[1] - 32 * wave), part0 = mg[2], n = mg[3];
   if (q_n <= 0) return;
@@ -241,27 +280,41 @@ __global__ __launch_bounds__(64) void fwd_merge_kernel(AttnArgs a, uint16_t* __r
   for (int j = 0; j < n; ++j) l += __builtin_amdgcn_exp2f(ml(j).x - m) * ml(j).y;  // a part that saw nothing: l = 0
   f32x16 acc[2];
   parts_sum(p, FWD_PART_BYTES, n, g, lane, [&](int j) { return __builtin_amdgcn_exp2f(ml(j).x - m); }, acc);
+  const int q_row0 = mg[0] + 32 * wave;
+  lds_char* obuf = (lds_char*)smem_raw + g * ROWS_OUT_BYTES;
+  float old_lse = 0.f;
+  if constexpr (MERGE) {
+    old_lse = fwd_old_lse(a, head, q_row0, q_n, lane);
+    settle(old_lse);
+    __syncthreads();  // both waves have read the LSE that the first one replaces
+  }
   if (g == 0)
-    fwd_out<0, 1>(a, o_bf16, (lds_char*)smem_raw, head, mg[0] + 32 * wave, q_n, lane, acc, m, l);
+    fwd_out<MERGE, 0, 1>(a, o_bf16, obuf, head, q_row0, q_n, lane, acc, m, l, old_lse);
   else
-    fwd_out<1, 1>(a, o_bf16, (lds_char*)smem_raw, head, mg[0] + 32 * wave, q_n, lane, acc, m, l);
+    fwd_out<MERGE, 1, 1>(a, o_bf16, obuf, head, q_row0, q_n, lane, acc, m, l, old_lse);
 }
 
-hipError_t launch_attn_fwd(const AttnArgs& args, const Launch& l, uint16_t* o_bf16, hipStream_t stream) {
+template <bool MERGE>
+hipError_t launch_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, hipStream_t stream) {
+  int tok = prof_begin("attn_fwd", stream);
+  hipLaunchKernelGGL(attn_fwd_kernel<MERGE>, dim3(a.n_items * a.H), dim3(64 * FWD_WAVES), 0, stream, a, o_bf16);
+  prof_end(tok, stream);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || l.n_merges == 0) return e;
+  tok = prof_begin("attn_fwd_merge", stream);
+  hipLaunchKernelGGL(fwd_merge_kernel<MERGE>, dim3(l.n_merges * a.H * FWD_WAVES), dim3(128), 0, stream, a, o_bf16);
+  prof_end(tok, stream);
+  return hipGetLastError();
+}
+
+// merge: into the O and LSE that a.out_o and a.out_lse hold.
+hipError_t launch_attn_fwd(const AttnArgs& args, const Launch& l, uint16_t* o_bf16, bool merge, hipStream_t stream) {
   if (l.n_units == 0) return hipSuccess;
   AttnArgs a = args;
   a.items = l.units;
   a.n_items = l.n_units;
   a.merges = l.merges;
   a.n_parts = l.parts;
-  int tok = prof_begin("attn_fwd", stream);
-  hipLaunchKernelGGL(attn_fwd_kernel, dim3(a.n_items * a.H), dim3(64 * FWD_WAVES), 0, stream, a, o_bf16);
-  prof_end(tok, stream);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess || l.n_merges == 0) return e;
-  tok = prof_begin("attn_fwd_merge", stream);
-  hipLaunchKernelGGL(fwd_merge_kernel, dim3(l.n_merges * a.H * FWD_WAVES * (DV / 64)), dim3(64), 0, stream, a, o_bf16);
-  prof_end(tok, stream);
-  return hipGetLastError();
+  return merge ? launch_fwd<true>(a, l, o_bf16, stream) : launch_fwd<false>(a, l, o_bf16, stream);
 }
 
 }  // namespace hydra

@@ -460,6 +460,26 @@ __device__ __forceinline__ void rows_add(lds_char* buf, int lane, const f32x16 (
   });
 }
 
+// Exact merge of two partials of a row with log-sums La and Lb: weights w_x = e^(Lx - L) of their
+// outputs, and L.  Two empty partials (-inf) give weights 0 and -inf, with no NaN.
+__device__ __forceinline__ void merge_weights(float La, float Lb, float& L, float& wa, float& wb) {
+  const float M = fmaxf(La, Lb);
+  wa = 0.f;
+  wb = 0.f;
+  L = -INFINITY;
+  if (M != -INFINITY) {
+    const float ea = expf(La - M), eb = expf(Lb - M);
+    const float tot = ea + eb;
+    L = M + logf(tot);
+    wa = ea / tot;
+    wb = eb / tot;
+  }
+}
+// A weight of 0 drops its partial, whatever that holds.
+__device__ __forceinline__ float merge_value(float wa, float oa, float wb, float ob) {
+  return (wa > 0.f ? wa * oa : 0.f) + (wb > 0.f ? wb * ob : 0.f);
+}
+
 // A wave's accumulators to and from its place in a part (see tiles.h).
 template <int N> __device__ __forceinline__ void part_store(char* p, int lane, const f32x16 (&acc)[N]) {
 #pragma unroll

@@ -21,21 +21,14 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(int64_t n_rows, int H, f
     const int64_t li = (int64_t)head * n_rows + row;
     // All 32 lanes of a (row, head) sit in one wave and read lse_acc before lane 0 writes it.
     const float La = lse_acc[li], Lb = lse_part[li];
-    const float M = fmaxf(La, Lb);
-    float wa = 0.f, wb = 0.f, L = -INFINITY;
-    if (M != -INFINITY) {
-      const float ea = expf(La - M), eb = expf(Lb - M);
-      const float tot = ea + eb;
-      L = M + logf(tot);
-      wa = ea / tot;
-      wb = eb / tot;
-    }
+    float L, wa, wb;
+    merge_weights(La, Lb, L, wa, wb);
     const int64_t off = rh * DV + sub * 4;
     const f32x4 oa = *reinterpret_cast<const f32x4*>(o_acc + off);
     const f32x4 ob = *reinterpret_cast<const f32x4*>(o_part + off);
     f32x4 res;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) res[i] = (wa > 0.f ? wa * oa[i] : 0.f) + (wb > 0.f ? wb * ob[i] : 0.f);
+    for (int i = 0; i < 4; ++i) res[i] = merge_value(wa, oa[i], wb, ob[i]);
     *reinterpret_cast<f32x4*>(o_acc + off) = res;
     if (o_bf16) {
       const uint32_t lo = pack_bf16x2(res[0], res[1]), hi = pack_bf16x2(res[2], res[3]);

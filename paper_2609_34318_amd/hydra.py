@@ -93,6 +93,8 @@ def lib() -> ctypes.CDLL:
         L.hydra_workspace_size.restype = ctypes.c_size_t
         L.hydra_attn_fwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.hydra_attn_fwd.restype = ctypes.c_int
+        L.hydra_attn_fwd_merge.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, ctypes.c_int32, vp]
+        L.hydra_attn_fwd_merge.restype = ctypes.c_int
         L.hydra_attn_bwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.hydra_attn_bwd.restype = ctypes.c_int
         L.hydra_attn_bwd_ds.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp,
@@ -295,6 +297,17 @@ def attn_fwd(p: Problem, q, k, v, o_part, lse_part, workspace, o_bf16=None, stre
                                 _ptr(lse_part, "lse_part", _F32, nqh), _ptr(o_bf16, "o_bf16", _BF16, nqh * 128),
                                 _ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
                                 _stream(stream)), "hydra_attn_fwd")
+
+
+def attn_fwd_merge(p: Problem, q, k, v, o_acc, lse_acc, workspace, o_bf16=None, stream=None, planned=False):
+    """(o_acc, lse_acc) <- exact merge with the partial that attn_fwd computes, in place and in the
+    same kernel; optional bf16 copy of the merged O.  q, k, v and planned as in attn_fwd."""
+    nqh = p.nq * p.n_heads
+    qp, kp, vp = _set_rows(p, q, k, v)
+    _check(lib().hydra_attn_fwd_merge(p.ref, qp, kp, vp, _ptr(o_acc, "o_acc", _F32, nqh * 128),
+                                      _ptr(lse_acc, "lse_acc", _F32, nqh), _ptr(o_bf16, "o_bf16", _BF16, nqh * 128),
+                                      _ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
+                                      int(planned), _stream(stream)), "hydra_attn_fwd_merge")
 
 
 def attn_bwd(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, workspace,

@@ -1,7 +1,7 @@
 """One rank's attention share over all outer-ring steps, through the C ABI.
 
-Forward: one partial per ring step, merged exactly into (O, LSE) with a bf16 copy of O
-(Sec. 5.2.2, "as in standard ring CP").  Backward: every step differentiates with the
+Forward: one partial per ring step, merged exactly into (O, LSE) by the step's own kernel, with a
+bf16 copy of O (Sec. 5.2.2, "as in standard ring CP").  Backward: every step differentiates with the
 final merged O and LSE; dQ accumulates over steps, dK/dV are per KV chunk.  The
 exchange that would move K/V between ranks is not here (one GPU); each step's chunk is
 simply another buffer with its global offsets.
@@ -26,8 +26,6 @@ class Share:
     step_workspaces: Optional[List[torch.Tensor]]  # one per step, for planned (graph) calls
     o_acc: torch.Tensor
     lse_acc: torch.Tensor
-    o_tmp: Optional[torch.Tensor]
-    lse_tmp: Optional[torch.Tensor]
     o_bf16: torch.Tensor
     ds_buf: Optional[torch.Tensor] = None   # dS scratch of the stored-dS backward
 
@@ -75,7 +73,6 @@ def make_share(cu_seqlens, n_heads: int, q_segs, kv_steps: Sequence, device="cud
         ds_kv_heads = ds_kv_heads_within(probs, ds_budget_bytes)
     ds = max(hydra.bwd_ds_bytes(p, ds_kv_heads) for p in probs) if ds_kv_heads > 0 else 0
     f32 = dict(dtype=torch.float32, device=device)
-    multi = len(probs) > 1
     return Share(
         problems=probs,
         workspace=torch.empty(ws, dtype=torch.uint8, device=device),
@@ -83,8 +80,6 @@ def make_share(cu_seqlens, n_heads: int, q_segs, kv_steps: Sequence, device="cud
         if graph_ready else None,
         o_acc=torch.empty((nq, n_heads, D_V), **f32),
         lse_acc=torch.empty((n_heads, nq), **f32),
-        o_tmp=torch.empty((nq, n_heads, D_V), **f32) if multi else None,
-        lse_tmp=torch.empty((n_heads, nq), **f32) if multi else None,
         o_bf16=torch.empty((nq, n_heads, D_V), dtype=torch.bfloat16, device=device),
         ds_buf=torch.empty(ds, dtype=torch.uint8, device=device) if ds > 0 else None,
     )
@@ -104,7 +99,7 @@ def _ws(sh: Share, i: int, planned: bool):
 
 
 def forward(sh: Share, q: torch.Tensor, kv: Sequence[Tuple[torch.Tensor, torch.Tensor]], planned: bool = False):
-    """Runs every ring step and the merges; returns (O fp32, LSE, O bf16)."""
+    """Runs every ring step, merging as it goes; returns (O fp32, LSE, O bf16)."""
     n = len(sh.problems)
     for i, (p, (k, v)) in enumerate(zip(sh.problems, kv)):
         ws = _ws(sh, i, planned)
@@ -112,8 +107,8 @@ def forward(sh: Share, q: torch.Tensor, kv: Sequence[Tuple[torch.Tensor, torch.T
             hydra.attn_fwd(p, q, k, v, sh.o_acc, sh.lse_acc, ws, o_bf16=sh.o_bf16 if n == 1 else None,
                            planned=planned)
         else:
-            hydra.attn_fwd(p, q, k, v, sh.o_tmp, sh.lse_tmp, ws, planned=planned)
-            hydra.lse_merge(sh.o_acc, sh.lse_acc, sh.o_tmp, sh.lse_tmp, o_bf16=sh.o_bf16 if i == n - 1 else None)
+            hydra.attn_fwd_merge(p, q, k, v, sh.o_acc, sh.lse_acc, ws, o_bf16=sh.o_bf16 if i == n - 1 else None,
+                                 planned=planned)
     return sh.o_acc, sh.lse_acc, sh.o_bf16
 
 
