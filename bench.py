@@ -30,12 +30,12 @@ FWD_FLOP_PER_PAIR = 2 * (D_QK + D_V)            # S = QK^T, O = PV
 BWD_FLOP_PER_PAIR = 2 * (3 * D_QK + 2 * D_V)    # S recompute, dP, dV, dQ, dK
 # contraction FLOPs each kernel performs per visible pair
 KERNEL_FLOP_PER_PAIR = {"attn_fwd": FWD_FLOP_PER_PAIR,
-                        "bwd_dkdv": 2 * (2 * D_QK + 2 * D_V),   # S, dP, dV, dK
-                        "bwd_dkdv_ds": 2 * (2 * D_QK + 2 * D_V),  # the same, and stores dS
-                        "bwd_dq": 2 * (2 * D_QK + D_V),         # S, dP (recomputed), dQ
+                        # dK/dV: S, dP, dV, dK; dQ: S, dP (recomputed), dQ
+                        "bwd_recompute": 2 * (2 * D_QK + 2 * D_V) + 2 * (2 * D_QK + D_V),
+                        "bwd_dkdv_ds": 2 * (2 * D_QK + 2 * D_V),  # S, dP, dV, dK, and stores dS
                         "bwd_dq_ds": 2 * D_QK}                  # dQ from the stored dS
 PEAK_BF16_TFLOPS = 2516.6                        # 256 CU x 4096 FLOP/clk x 2.4 GHz, dense
-KERNEL_SOURCES = {"attn_fwd": "attn_fwd.hip", "bwd_dkdv": "attn_bwd.hip", "bwd_dq": "attn_bwd.hip",
+KERNEL_SOURCES = {"attn_fwd": "attn_fwd.hip", "bwd_recompute": "attn_bwd.hip",
                   "bwd_dkdv_ds": "attn_bwd.hip", "bwd_dq_ds": "attn_bwd.hip"}
 
 
@@ -472,8 +472,8 @@ def main() -> int:
         "clock": clock,
         "kernels": kernels,
         "kernel_timing": f"library launch events over {args.prof_steps} further eager steps; tflops_executed "
-                         "counts each kernel's own contractions (bwd_dq's include its S and dP recompute, "
-                         "640 of its 1024 FLOP per pair, which are not part of the counted work)",
+                         "counts each kernel's own contractions (bwd_recompute's include dQ's S and dP, "
+                         "640 of its 2304 FLOP per pair, which are not part of the counted work)",
         "roofline": roofline,
         "wall_s_timed": round(r["wall"], 3),
         "input_gen_s": round(r["t_gen"], 1),

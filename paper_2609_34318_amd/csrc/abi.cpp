@@ -17,7 +17,7 @@
 namespace hydra {
 hipError_t launch_attn_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, bool merge, hipStream_t stream);
 hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
-                           int kv_heads_per_pass, hipStream_t stream);
+                           char* kv_split, int kv_heads_per_pass, hipStream_t stream);
 hipError_t launch_lse_merge(int64_t n_rows, int H, float* o_acc, float* lse_acc, const float* o_part,
                             const float* lse_part, uint16_t* o_bf16, hipStream_t stream);
 }  // namespace hydra
@@ -107,10 +107,9 @@ int check_ptr(const void* p, bool needed) {
   return aligned16(p) ? HYDRA_OK : HYDRA_ERR_ALIGN;
 }
 
-// A split list in the workspace, and how many heads its launches have; no units: the whole items
-// are launched.
+// A split list in the workspace; no units: the whole items are launched.
 struct ListSize {
-  int units = 0, merges = 0, parts = 0, heads = 0;
+  int units = 0, merges = 0, parts = 0;
   size_t merges_off = 0, units_off = 0;
 };
 
@@ -128,8 +127,8 @@ std::mutex g_plans_mu;
 std::map<const void*, PlanRecord> g_plans;
 
 // Builds the host image of the workspace prefix (documents, records, split lists) and uploads it.
-// kv_heads: K/V heads per dK/dV launch (0: the forward's part only).
-int upload_plan(const Problem& pr, const WsLayout& w, int kv_heads, void* ws, hipStream_t stream, PlanRecord* rec) {
+// backward = false: the forward's part only.
+int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, hipStream_t stream, PlanRecord* rec) {
   std::vector<int32_t> qitems, kitems, qrec, krecs, kbase, kmap32, krec;
   std::vector<char> img;
   auto put = [&](size_t off, const std::vector<int32_t>& v) {
@@ -138,7 +137,7 @@ int upload_plan(const Problem& pr, const WsLayout& w, int kv_heads, void* ws, hi
   };
   plan_items(pr, 0, &qitems);
   put(w.cu_off, pr.cu);
-  if (kv_heads) {
+  if (backward) {
     plan_items(pr, 1, &kitems);
     ds_tables(pr, kitems, &kbase, &kmap32, &krec);
     launch_units(pr, 1, kitems, kbase, &krecs);
@@ -153,7 +152,7 @@ int upload_plan(const Problem& pr, const WsLayout& w, int kv_heads, void* ws, hi
     UnitList l;
     split_units(pr, kernel, records, heads, &l);
     if (l.units.empty()) return ListSize{};
-    ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts, heads};
+    ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts};
     auto next = [&](const std::vector<int32_t>& v) {
       const size_t at = end;
       put(at, v);
@@ -165,11 +164,12 @@ int upload_plan(const Problem& pr, const WsLayout& w, int kv_heads, void* ws, hi
     return z;
   };
   rec->fwd = put_list(Kernel::kFwd, qrec, pr.H);
-  if (kv_heads) {
+  if (backward) {
     rec->dq = put_list(Kernel::kDq, qrec, pr.H);
-    rec->kv = put_list(Kernel::kDkdv, krecs, kv_heads);
+    // one split whatever the heads of a pass: dK and dV then sum in the same order on every path
+    rec->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv);
   }
-  rec->has_kitems = kv_heads != 0;
+  rec->has_kitems = backward;
   if (end > w.d_off) return HYDRA_ERR_WORKSPACE;  // the lists' bound: never so
   // Pageable source: the runtime has consumed `img` when the call returns.
   if (hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, stream) != hipSuccess) return HYDRA_ERR_HIP;
@@ -279,7 +279,7 @@ int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void*
     hipStream_t s = static_cast<hipStream_t>(stream);
     PlanRecord plan;
     if (upload) {  // the forward needs only the query-stationary items
-      rc = upload_plan(pr, w, 0, workspace, s, &plan);
+      rc = upload_plan(pr, w, false, workspace, s, &plan);
       if (rc != HYDRA_OK) return rc;
       record_plan(workspace, pr, PlanRecord(plan));
     } else if (!plan_matches(workspace, pr, false, &plan)) {
@@ -310,7 +310,7 @@ uint64_t ds_bytes_per_head(const Problem& pr) {
 int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const void* k, const void* v,
                   const void* o_final, const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc,
                   float* dv_acc, void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes,
-                  void* stream) {
+                  void* stream, bool noalloc = false) {
   try {
     Problem pr;
     int rc = check_problem(p, &pr);
@@ -321,7 +321,7 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
                   check_ptr(dk_acc, true), check_ptr(dv_acc, true)})
       if (c != HYDRA_OK) return c;
     const WsLayout w = ws_layout(pr);
-    if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < (noalloc ? w.noalloc_total : w.total)) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
     // stored-dS path: K/V heads per pass such that their query heads' dS fits ds_buf
     int kv_per_pass = 0;
@@ -337,23 +337,19 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     const uint64_t qb = rows_bytes(pr.nq, pr.q_s, pr.H * kDqk), kb = rows_bytes(pr.nk, pr.k_s, pr.Hkv * kDqk),
                    vb = rows_bytes(pr.nk, pr.v_s, pr.Hkv * kDv);
     if (outputs_overlap({{dq_acc, qh * kDqk * 4}, {dk_acc, kh * kDqk * 4}, {dv_acc, kh * kDv * 4},
-                         {workspace, w.total}, {kv_per_pass ? ds_buf : nullptr, ds_used}},
+                         {workspace, std::min<uint64_t>(w.total, workspace_bytes)}, {kv_per_pass ? ds_buf : nullptr, ds_used}},
                         {{q, qb}, {k, kb}, {v, vb}, {o_final, qh * kDv * 2}, {lse_final, qh * 4},
                          {d_o, qh * kDv * 2}}))
       return HYDRA_ERR_INVALID;
     hipStream_t s = static_cast<hipStream_t>(stream);
     PlanRecord plan;
-    const int kv_heads = kv_per_pass ? kv_per_pass : pr.Hkv;  // of one dK/dV launch
     if (upload) {
-      rc = upload_plan(pr, w, kv_heads, workspace, s, &plan);
+      rc = upload_plan(pr, w, true, workspace, s, &plan);
       if (rc != HYDRA_OK) return rc;
       record_plan(workspace, pr, PlanRecord(plan));
     } else if (!plan_matches(workspace, pr, true, &plan)) {
       return HYDRA_ERR_WORKSPACE;
     }
-    // the workspace's last upload may have been for passes of fewer heads, whose parts would not
-    // fit the scratch in one launch over all of them
-    if (plan.kv.heads != kv_heads) plan.kv = ListSize{};
     AttnArgs a = base_args(pr, w, workspace);
     a.q = static_cast<const uint16_t*>(q);
     a.k = static_cast<const uint16_t*>(k);
@@ -369,7 +365,8 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     const Launch q_whole = list_launch(workspace, w.qitems_off, w.n_qitems, ListSize{});
     const Launch dq = list_launch(workspace, w.qitems_off, w.n_qitems, plan.dq);
     const Launch kv = list_launch(workspace, w.kitems_off, w.n_kitems, plan.kv);
-    if (launch_attn_bwd(a, q_whole, dq, kv, kv_per_pass, s) != hipSuccess) return HYDRA_ERR_HIP;
+    char* kv_split = workspace_bytes >= w.total ? static_cast<char*>(workspace) + w.kv_split_off : nullptr;
+    if (launch_attn_bwd(a, q_whole, dq, kv, kv_split, kv_per_pass, s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
     return HYDRA_ERR_INVALID;
@@ -389,7 +386,7 @@ int hydra_attn_plan(const hydra_problem_t* p, void* workspace, size_t workspace_
     if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
     PlanRecord plan;
-    rc = upload_plan(pr, w, pr.Hkv, workspace, static_cast<hipStream_t>(stream), &plan);
+    rc = upload_plan(pr, w, true, workspace, static_cast<hipStream_t>(stream), &plan);
     if (rc == HYDRA_OK) record_plan(workspace, pr, std::move(plan));
     return rc;
   } catch (...) {
@@ -473,7 +470,7 @@ int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* 
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws)) != HYDRA_OK) return rc;
     return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, ws,
-                         kNoAllocScratchBytes, stream);
+                         kNoAllocScratchBytes, stream, true);
   } catch (...) {
     return HYDRA_ERR_INVALID;
   }

@@ -1,12 +1,14 @@
 // Backward of one ring step, differentiating with the final merged O and LSE of each row:
 //   D_i = <dO_i, O_i>,  P = exp(S - LSE),  dV += P^T dO,  dS = P o (dO V^T - D),
 //   dK += scale dS^T Q,  dQ += scale dS K.
-// Three kernels:
-//   bwd_pre   -D = -rowsum(dO o O) and LSE * log2(e)                (HBM-bound)
-//   bwd_dq    query-stationary: recomputes S^T and dP^T per key tile, accumulates dQ^T
-//   bwd_dkdv  key-stationary: recomputes S and dP per query tile, accumulates dK^T, dV^T
+// Two kernels:
+//   bwd_pre        -D = -rowsum(dO o O) and LSE * log2(e)                (HBM-bound)
+//   bwd_recompute  dK/dV workgroups, key-stationary: recompute S and dP per query tile,
+//                  accumulate dK^T, dV^T; then dQ workgroups, query-stationary: recompute S^T
+//                  and dP^T per key tile, accumulate dQ^T
+// or, where dS is stored, bwd_pre, bwd_dkdv_ds and bwd_dq_ds (below).
 // Splitting dQ from dK/dV recomputes S and dP once more but needs no atomics and is
-// deterministic: every output row is owned by exactly one workgroup.  Both main kernels
+// deterministic: every output row is owned by exactly one workgroup.  Both kinds
 // stream their other-side tiles through swizzled LDS stages filled by direct
 // buffer->LDS copies issued ahead of use.
 #include "kernels.h"
@@ -62,19 +64,17 @@ __device__ __forceinline__ void dq_issue(lds_char* stage, const AttnArgs& a, con
   dma_tile<DV, DQ_BK, DQ_COPY_WAVES>(stage + DQ_KBYTES, tile_rsrc(a.v, k.row0, k.n, a.v_s), voff, a.v_s, wave);
 }
 
-__global__ __launch_bounds__(64 * DQ_WAVES, 1) void bwd_dq_kernel(AttnArgs a) {
-  // stage 0 | stage 1; before the loop the waves' Q, then dO rows from the start of stage 1,
-  // after it their outputs
-  constexpr int LDS_BYTES = DQ_STAGE + DQ_WAVES * own_bytes<DQK>();
-  static_assert(LDS_BYTES >= DQ_NSTAGE * DQ_STAGE && LDS_BYTES >= DQ_WAVES * ROWS_OUT_BYTES, "LDS");
-  __shared__ __attribute__((aligned(1024))) char smem_raw[LDS_BYTES];
-  lds_char* smem = (lds_char*)smem_raw;
+// stage 0 | stage 1; before the loop the waves' Q, then dO rows from the start of stage 1, after it
+// their outputs
+constexpr int DQ_LDS = DQ_STAGE + DQ_WAVES * own_bytes<DQK>();
+static_assert(DQ_LDS >= DQ_NSTAGE * DQ_STAGE && DQ_LDS >= DQ_WAVES * ROWS_OUT_BYTES, "LDS");
 
+__device__ __forceinline__ void bwd_dq_body(const AttnArgs& a, int block, lds_char* smem) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, known to the compiler
   const int m = lane & 31;
   int hl, item;
-  xcd_head_item(blockIdx.x, a.q_heads, a.n_items, hl, item);
+  xcd_head_item(block, a.q_heads, a.n_items, hl, item);
   const int head = a.q_head0 + hl;
   const Item it(a.items, item);
   const TileRanges kr = tile_ranges(it, DQ_BK);
@@ -252,9 +252,7 @@ __device__ __forceinline__ void kv_clear_tail(lds_char* stage, int n, int wave_b
 // STORE_DS: also store dS (bf16, as the MFMA operand registers hold it) for the query-
 // stationary dQ kernel that reads it back instead of recomputing S and dP.
 template <bool STORE_DS>
-__global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[KV_LDS];
-  lds_char* smem = (lds_char*)smem_raw;
+__device__ __forceinline__ void bwd_dkdv_body(const AttnArgs& a, int block, lds_char* smem) {
   lds_char* pbuf = smem + KV_NSTAGE * KV_STAGE;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
   const int m = lane & 31, hh = lane >> 5;
   // one K/V head per workgroup; its dK/dV sum over the group's query heads head0 ..
   int kvl, item_idx;
-  xcd_head_item(blockIdx.x, a.kv_heads, a.n_items, kvl, item_idx);
+  xcd_head_item(block, a.kv_heads, a.n_items, kvl, item_idx);
   const int kv_head = a.kv_head0 + kvl;
   const int head0 = kv_head * a.grp;
   const Item it(a.items, item_idx);
@@ -513,9 +511,31 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(AttnArgs a) {
   else run(IntC<1>{});
 }
 
+__global__ __launch_bounds__(512, 1) void bwd_dkdv_ds_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[KV_LDS];
+  bwd_dkdv_body<true>(a, blockIdx.x, (lds_char*)smem_raw);
+}
+
+// The recompute backward: dK/dV, then dQ, in one launch.  The workgroups of dQ, which needs nothing
+// from dK/dV, fill the CUs that the last ones of dK/dV leave idle; as two launches dQ waited for
+// them.  dK/dV comes first because its workgroups are the longer ones (of 128 keys, and of all heads
+// of a group).  Two launches and one: 1K rows x 16 heads 106 and 99 us, 2K 150 and 138, ragged 8K 434
+// and 400, 16K on 2 K/V heads 675 and 618, ring of 64K with one head 1.82 and 1.73 ms; the same at
+// 32K and 64K rows in one document (21.6 ms, 84 ms).  The two lists interleaved, both walked to
+// the end together, lost where workgroups are long (64K: 79.3 to 83.2 ms): dK/dV's and dQ's tiles then
+// share the L2s.  Up to seven places after dK/dV stay empty, so that dQ's heads keep their XCDs.
+__global__ __launch_bounds__(512, 1) void bwd_recompute_kernel(AttnArgs q, AttnArgs kv) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[DQ_LDS > KV_LDS ? DQ_LDS : KV_LDS];
+  lds_char* smem = (lds_char*)smem_raw;
+  const int nkv = kv.n_items * kv.kv_heads;
+  const int b = blockIdx.x, q0 = (nkv + N_XCD - 1) / N_XCD * N_XCD;
+  if (b < nkv) bwd_dkdv_body<false>(kv, b, smem);
+  else if (b >= q0) bwd_dq_body(q, b - q0, smem);
+}
+
 // ------------------------------------------------------------------ dQ from stored dS
-// Query-stationary like bwd_dq, but reading the dS that bwd_dkdv<true> stored instead of
-// recomputing S and dP: dQ^T[c][q] += K^T[c][key] dS^T[key][q], 384 of bwd_dq's 1024 FLOP
+// Query-stationary like the dQ above, but reading the dS that bwd_dkdv_ds stored instead of
+// recomputing S and dP: dQ^T[c][q] += K^T[c][key] dS^T[key][q], 384 of its 1024 FLOP
 // per visible pair, and 2 bytes of dS read per pair (HBM-bound).  Eight waves x 32 query
 // rows; keys walk the key items that the query tile's visible ranges touch, 64 keys (half
 // an item) per tile.  Every 32-row query block coincides with one 32-row sub-block of each
@@ -716,11 +736,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
 // otherwise two of the four pairs' dV rows and three of their dK rows of a key item.
 template <bool DQ> constexpr int merge_blocks() { return DQ ? 8 * (DQK / 64) : 4 * (DV / 64 + DQK / 64); }
 
-template <bool DQ>
-__global__ __launch_bounds__(64) void bwd_merge_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(1024))) char smem_raw[ROWS_OUT_BYTES];
+template <bool DQ> __device__ __forceinline__ void bwd_merge_body(const AttnArgs& a, int b, lds_char* smem) {
   const int heads = DQ ? a.q_heads : a.kv_heads, lane = threadIdx.x;
-  const int piece = blockIdx.x % merge_blocks<DQ>(), rest = blockIdx.x / merge_blocks<DQ>();
+  const int piece = b % merge_blocks<DQ>(), rest = b / merge_blocks<DQ>();
   const int hl = rest % heads;
   const int* mg = a.merges + (rest / heads) * 4;
   const bool dv = !DQ && piece < 4 * (DV / 64);
@@ -744,36 +762,66 @@ __global__ __launch_bounds__(64) void bwd_merge_kernel(AttnArgs a) {
   }
   f32x16 acc[2];
   parts_sum(p, part_bytes, n, g, lane, [](int) { return 1.0f; }, acc);
-  rows_add<1>((lds_char*)smem_raw, lane, acc, dv ? 1.0f : a.scale, out + 64 * g, pitch, rows);
+  rows_add<1>(smem, lane, acc, dv ? 1.0f : a.scale, out + 64 * g, pitch, rows);
+}
+
+// The first q_blocks workgroups merge dQ, the others dK and dV.
+__global__ __launch_bounds__(64) void bwd_merge_kernel(AttnArgs q, AttnArgs kv, int q_blocks) {
+  __shared__ __attribute__((aligned(1024))) char smem_raw[ROWS_OUT_BYTES];
+  if ((int)blockIdx.x < q_blocks) bwd_merge_body<true>(q, blockIdx.x, (lds_char*)smem_raw);
+  else bwd_merge_body<false>(kv, blockIdx.x - q_blocks, (lds_char*)smem_raw);
 }
 
 namespace {
 
-// A launch of `kernel` over a list, then the merge of its split items.
-template <bool DQ, class K>
-hipError_t launch_list(K kernel, const char* name, AttnArgs a, const Launch& l, int heads, hipStream_t stream) {
-  if (l.n_units == 0) return hipSuccess;
-  a.items = l.units;
-  a.n_items = l.n_units;
-  a.merges = l.merges;
-  a.n_parts = l.parts;
-  int tok = prof_begin(name, stream);
-  hipLaunchKernelGGL(kernel, dim3(l.n_units * heads), dim3(512), 0, stream, a);
-  prof_end(tok, stream);
-  if (hipError_t e = hipGetLastError(); e != hipSuccess || l.n_merges == 0) return e;
-  tok = prof_begin(DQ ? "bwd_dq_merge" : "bwd_dkdv_merge", stream);
-  hipLaunchKernelGGL(bwd_merge_kernel<DQ>, dim3(l.n_merges * heads * merge_blocks<DQ>()), dim3(64), 0, stream, a);
+// a over a list, whose parts lie at split.
+AttnArgs list_args(const AttnArgs& a, const Launch& l, char* split) {
+  AttnArgs b = a;
+  b.items = l.units;
+  b.n_items = l.n_units;
+  b.merges = l.merges;
+  b.n_parts = l.parts;
+  b.split = split;
+  return b;
+}
+
+template <class K>
+hipError_t launch_list(K kernel, const char* name, const AttnArgs& a, int heads, hipStream_t stream) {
+  if (a.n_items == 0) return hipSuccess;
+  const int tok = prof_begin(name, stream);
+  hipLaunchKernelGGL(kernel, dim3(a.n_items * heads), dim3(512), 0, stream, a);
   prof_end(tok, stream);
   return hipGetLastError();
 }
 
+// The merges of n_q split query items and n_kv split key items.
+hipError_t launch_merges(const AttnArgs& q, int n_q, const AttnArgs& kv, int n_kv, hipStream_t stream) {
+  const int q_blocks = n_q * q.q_heads * merge_blocks<true>(), kv_blocks = n_kv * kv.kv_heads * merge_blocks<false>();
+  if (q_blocks + kv_blocks == 0) return hipSuccess;
+  const int tok = prof_begin("bwd_merge", stream);
+  hipLaunchKernelGGL(bwd_merge_kernel, dim3(q_blocks + kv_blocks), dim3(64), 0, stream, q, kv, q_blocks);
+  prof_end(tok, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_recompute(const AttnArgs& q, int q_merges, const AttnArgs& kv, int kv_merges, hipStream_t stream) {
+  const int64_t nq = (int64_t)q.n_items * q.q_heads, nkv = (int64_t)kv.n_items * kv.kv_heads;
+  if (nq + nkv == 0) return hipSuccess;
+  const int tok = prof_begin("bwd_recompute", stream);
+  hipLaunchKernelGGL(bwd_recompute_kernel, dim3(unsigned((nkv + N_XCD - 1) / N_XCD * N_XCD + nq)), dim3(512), 0, stream, q, kv);
+  prof_end(tok, stream);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return launch_merges(q, q_merges, kv, kv_merges, stream);
+}
+
 }  // namespace
 
-// kv_heads_per_pass = 0: recompute path (bwd_dq + bwd_dkdv over all heads).  Otherwise the
-// stored-dS path, in passes of that many K/V heads (the dS of one pass's query heads fits
-// a.ds): bwd_dkdv<true> stores dS, then bwd_dq_ds reads it back.
+// kv_heads_per_pass = 0: recompute path over all heads (kv_split: the dK/dV parts, apart from dQ's
+// at a.split; null where the scratch holds one kind's parts only: the two then take turns).
+// Otherwise the stored-dS path, in passes of that many K/V heads (the dS of one pass's query heads
+// fits a.ds): bwd_dkdv_ds stores dS, then bwd_dq_ds reads it back.
 hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
-                           int kv_heads_per_pass, hipStream_t stream) {
+                           char* kv_split, int kv_heads_per_pass, hipStream_t stream) {
   const int64_t pairs = (int64_t)a.nq * a.H;
   const int64_t blocks = (pairs + 15) / 16 < (1 << 20) ? (pairs + 15) / 16 : (1 << 20);
   int tok = prof_begin("bwd_pre", stream);
@@ -786,18 +834,30 @@ hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launc
     if (q_whole.n_units == 0 || kv.n_units == 0) return hipSuccess;
     for (int g0 = 0; g0 < a.Hkv; g0 += kv_heads_per_pass) {
       const int G = min(kv_heads_per_pass, a.Hkv - g0);
-      AttnArgs b = a;
+      AttnArgs b = list_args(a, kv, a.split);
       b.kv_head0 = g0;
       b.kv_heads = G;
       b.q_head0 = g0 * a.grp;
       b.q_heads = G * a.grp;
-      if ((e = launch_list<false>(bwd_dkdv_kernel<true>, "bwd_dkdv_ds", b, kv, G, stream)) != hipSuccess) return e;
-      if ((e = launch_list<true>(bwd_dq_ds_kernel, "bwd_dq_ds", b, q_whole, G * a.grp, stream)) != hipSuccess) return e;
+      if ((e = launch_list(bwd_dkdv_ds_kernel, "bwd_dkdv_ds", b, G, stream)) != hipSuccess) return e;
+      if ((e = launch_merges(b, 0, b, kv.n_merges, stream)) != hipSuccess) return e;
+      if ((e = launch_list(bwd_dq_ds_kernel, "bwd_dq_ds", list_args(b, q_whole, a.split), G * a.grp, stream)) !=
+          hipSuccess)
+        return e;
     }
     return hipSuccess;
   }
-  if ((e = launch_list<true>(bwd_dq_kernel, "bwd_dq", a, dq, a.H, stream)) != hipSuccess) return e;
-  return launch_list<false>(bwd_dkdv_kernel<false>, "bwd_dkdv", a, kv, a.Hkv, stream);
+  // a dispatch holds fewer than 2^32 lanes
+  const bool turns = (!kv_split && dq.n_merges && kv.n_merges) ||
+                     (int64_t)dq.n_units * a.H + (int64_t)kv.n_units * a.Hkv + N_XCD > (1 << 23);
+  const AttnArgs q_args = list_args(a, dq, a.split), kv_args = list_args(a, kv, kv_split ? kv_split : a.split);
+  if (turns) {
+    AttnArgs none = a;
+    none.n_items = 0;
+    if ((e = launch_recompute(none, 0, kv_args, kv.n_merges, stream)) != hipSuccess) return e;
+    return launch_recompute(q_args, dq.n_merges, none, 0, stream);
+  }
+  return launch_recompute(q_args, dq.n_merges, kv_args, kv.n_merges, stream);
 }
 
 }  // namespace hydra

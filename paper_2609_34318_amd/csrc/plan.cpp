@@ -236,8 +236,7 @@ int64_t parts_bound(const Problem& pr, Kernel kernel) {
   const bool kv = kernel == Kernel::kDkdv;
   const int64_t n = kv ? n_tiles(pr.kv, kKvTile) : n_tiles(pr.q, kQTile);
   const int64_t most = kv ? n_tiles(pr.q, KV_QTILE_ROWS) * (pr.H / pr.Hkv) : n_tiles(pr.kv, tile_rows(kernel));
-  // a dK/dV launch may hold one K/V head only
-  if (n * (kv ? 1 : pr.H) >= kSplitBelow || most < 2 * kMinPart) return 0;
+  if (n * (kv ? pr.Hkv : pr.H) >= kSplitBelow || most < 2 * kMinPart) return 0;
   return std::min<int64_t>(MAX_PARTS, n * ((most + kMinPart - 1) / kMinPart) * (kv ? pr.Hkv : pr.H));
 }
 
@@ -402,23 +401,23 @@ WsLayout ws_layout(const Problem& pr) {
   w.krec_off = off;
   off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
   w.lists_off = off;
-  size_t split_bytes = 0;
   auto list = [&](Kernel kernel, int64_t n, size_t part_bytes) {
     const size_t parts = size_t(parts_bound(pr, kernel));
-    split_bytes = std::max(split_bytes, parts * part_bytes);
     if (parts)
       off = align_up(off + (size_t(kMaxMerges) * kMergeInts + (parts + size_t(n)) * kUnitInts) * sizeof(int32_t), 256);
+    return parts * part_bytes;
   };
-  list(Kernel::kFwd, nqt, FWD_PART_BYTES);
-  list(Kernel::kDq, nqt, DQ_PART_BYTES);
-  list(Kernel::kDkdv, nkt, KV_PART_BYTES);
+  const size_t fwd = list(Kernel::kFwd, nqt, FWD_PART_BYTES);
+  const size_t dq = list(Kernel::kDq, nqt, DQ_PART_BYTES);
+  const size_t kv = list(Kernel::kDkdv, nkt, KV_PART_BYTES);
   w.d_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
   w.lse2_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
   w.split_off = off;
-  off += split_bytes;
-  w.total = std::max<size_t>(off, 256);
+  w.kv_split_off = off + dq;
+  w.total = std::max<size_t>(off + std::max(fwd, dq + kv), 256);
+  w.noalloc_total = std::max<size_t>(off + std::max({fwd, dq, kv}), 256);
   return w;
 }
 

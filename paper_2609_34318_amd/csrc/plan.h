@@ -66,9 +66,11 @@ void launch_units(const Problem& pr, int which, const std::vector<int32_t>& item
 
 // Byte offsets of the workspace regions.  lists holds the split lists that a plan has, one after
 // another (merges, then units), of no size for a problem none of whose launches can be split;
-// split the parts.
+// split the parts, kv_split those of dK/dV in a launch with dQ.  noalloc_total: without room for
+// both of those, which then take turns.
 struct WsLayout {
-  size_t cu_off, qitems_off, kitems_off, krec_off, lists_off, d_off, lse2_off, split_off, total;
+  size_t cu_off, qitems_off, kitems_off, krec_off, lists_off, d_off, lse2_off, split_off, kv_split_off;
+  size_t total, noalloc_total;
   int64_t n_qitems, n_kitems;
 };
 WsLayout ws_layout(const Problem& pr);

@@ -43,13 +43,13 @@ int main() {
     Problem pr;
     CHECK(check_problem(&p, &pr) == HYDRA_OK);
     const WsLayout w = ws_layout(pr);
-    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
+    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.noalloc_total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
     size_t list_bytes = 0;
     for (Kernel k : {Kernel::kFwd, Kernel::kDq, Kernel::kDkdv}) {
       std::vector<int32_t> items, rec;
       plan_items(pr, k == Kernel::kDkdv ? 1 : 0, &items);
       launch_units(pr, k == Kernel::kDkdv ? 1 : 0, items, {}, &rec);
-      const int heads = k == Kernel::kDkdv ? int(uni(1, pr.Hkv)) : pr.H;
+      const int heads = k == Kernel::kDkdv ? pr.Hkv : pr.H;
       const int64_t rows = k == Kernel::kFwd ? FWD_TILE_ROWS : k == Kernel::kDq ? DQ_TILE_ROWS : KV_QTILE_ROWS;
       UnitList l;
       split_units(pr, k, rec, heads, &l);
@@ -64,7 +64,9 @@ int main() {
       CHECK(w.lists_off + list_bytes <= w.d_off);
       CHECK(l.merges.size() <= size_t(kMaxMerges) * kMergeInts);
       const size_t part = k == Kernel::kFwd ? FWD_PART_BYTES : k == Kernel::kDq ? DQ_PART_BYTES : KV_PART_BYTES;
-      CHECK(w.total >= w.split_off + size_t(l.parts) * size_t(heads) * part);
+      CHECK(w.noalloc_total >= w.split_off + size_t(l.parts) * size_t(heads) * part);
+      CHECK(w.total >= (k == Kernel::kDkdv ? w.kv_split_off : w.split_off) + size_t(l.parts) * size_t(heads) * part);
+      CHECK(k != Kernel::kDq || w.kv_split_off >= w.split_off + size_t(l.parts) * size_t(heads) * part);
       // the units of every item, by first row, in the order of their tiles
       std::map<int32_t, std::vector<const int32_t*>> by_row;
       for (size_t i = 0; i < l.units.size(); i += kUnitInts) by_row[l.units[i]].push_back(&l.units[i]);

@@ -1,4 +1,6 @@
-"""A ring step merged by its own kernel against the partial and the merge call."""
+"""Forms of one launch against each other: a ring step merged by its own kernel against the partial
+and the merge call; the backward's dQ and dK/dV in one launch against two, split and whole; the
+split dK/dV of the stored-dS passes against the recompute path's."""
 import math
 
 import pytest
@@ -74,3 +76,45 @@ def test_merged_step_of_weight_zero_is_dropped():
     hydra.attn_fwd_merge(p, q, k, v, o, lse, _ws(p))
     torch.cuda.synchronize()
     assert torch.equal(o, want) and bool((lse == 300.0).all())
+
+
+def _backward(call, p, t, ds=None):
+    q, k, v, o, lse, d_o, ws = t
+    out = [torch.zeros((p.nq, p.n_heads, D_QK), device="cuda"), torch.zeros((p.nk, p.n_kv_heads, D_QK), device="cuda"),
+           torch.zeros((p.nk, p.n_kv_heads, D_V), device="cuda")]
+    if call is hydra.attn_bwd_noalloc:
+        call(p, q, k, v, o, lse, d_o, *out)
+    elif ds is not None:
+        call(p, q, k, v, o, lse, d_o, *out, ds, ws)
+    else:
+        call(p, q, k, v, o, lse, d_o, *out, ws)
+    torch.cuda.synchronize()
+    return out
+
+
+def _tensors(p, seed):
+    q, k, v, g = _inputs(p, seed)
+    o = torch.empty((p.nq, p.n_heads, D_V), device="cuda")
+    lse = torch.empty((p.n_heads, p.nq), device="cuda")
+    b = torch.empty(o.shape, dtype=BF16, device="cuda")
+    ws = _ws(p)
+    hydra.attn_fwd(p, q, k, v, o, lse, ws, o_bf16=b)
+    return q, k, v, b, lse, _randn(g, o.shape), ws
+
+
+@pytest.mark.parametrize("cu,H,Hkv", [([0, 4000], 1, 1), ([0, 1900, 4096], 4, 1), ([0, 2048], 2, 2)])
+def test_both_split_in_one_launch_and_in_two(cu, H, Hkv):
+    """The no-allocation call has scratch for the parts of one launch at a time, so it takes two."""
+    p = hydra.Problem(cu, H, [(0, cu[-1])], [(0, cu[-1])], n_kv_heads=Hkv)
+    t = _tensors(p, 61)
+    for a, b in zip(_backward(hydra.attn_bwd, p, t), _backward(hydra.attn_bwd_noalloc, p, t)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kv_heads", [1, 2])
+def test_stored_ds_passes_sum_dk_dv_alike(kv_heads):
+    p = hydra.Problem([0, 1920, 4096], 4, [(0, 4096)], [(0, 4096)], n_kv_heads=2)
+    t = _tensors(p, 62)
+    ds = torch.empty(hydra.bwd_ds_bytes(p, kv_heads), dtype=torch.uint8, device="cuda")
+    a, b = _backward(hydra.attn_bwd, p, t), _backward(hydra.attn_bwd_ds, p, t, ds)
+    assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
