@@ -58,7 +58,13 @@ __device__ __forceinline__ void fwd_out(const AttnArgs& a, uint16_t* o_bf16, lds
   const rows_rsrc ro = rows_buffer(a.out_o + base, rows, pitch * 4);
   const rows_rsrc rb = rows_buffer(o_bf16 + base, o_bf16 ? rows : 0, pitch * 2);
   float wa[8], wb[8];  // of the rows that this lane stores
+  f32x4 old[NG][8];
   if constexpr (MERGE) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) old[g][i] = rows_old(ro, lane, i, pitch, G0 + g);
+    sched_fence();
     float a_m, b_m;
     merge_weights(old_lse, lse, lse, a_m, b_m);
 #pragma unroll
@@ -70,20 +76,13 @@ __device__ __forceinline__ void fwd_out(const AttnArgs& a, uint16_t* o_bf16, lds
   if (G0 == 0 && lane < q_n) a.out_lse[(int64_t)head * a.nq + q_row0 + lane] = lse;
   static_for<NG>([&](auto g_) {
     constexpr int gi = decltype(g_)::value, g = G0 + gi;
-    f32x4 old[8];
-    if constexpr (MERGE) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        old[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                               ro, (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0));
-    }
     rows_stage<gi>(obuf, lane, acc, inv);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       f32x4 val = rows_read(obuf, lane, i);
       if constexpr (MERGE) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[e] = merge_value(wa[i], old[i][e], wb[i], val[e]);
+        for (int e = 0; e < 4; ++e) val[e] = merge_value(wa[i], old[gi][i][e], wb[i], val[e]);
       }
       const int off = rows_row(lane, i) * pitch + rows_col(lane, i);
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, val), ro, off * 4 + 256 * g, 0, 0);

@@ -440,22 +440,31 @@ __device__ __forceinline__ rows_rsrc rows_buffer(void* out, int valid, int pitch
                                            0x00020000);
 }
 
+// The 16 bytes that this lane stores in step i, before the sum: column group g of 64.  All groups'
+// loads are issued before the first is used: one workgroup runs on a CU, and nothing else hides
+// the memory's latency at its end.
+__device__ __forceinline__ f32x4 rows_old(rows_rsrc rs, int lane, int i, int pitch, int g) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                       rs, (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0));
+}
+
 // out[row][col] += scale * acc, rows [0, valid), `pitch` elements apart.
 template <int NG>
 __device__ __forceinline__ void rows_add(lds_char* buf, int lane, const f32x16 (&acc)[2 * NG], float scale, float* out,
                                          int pitch, int valid) {
   const rows_rsrc rs = rows_buffer(out, valid, pitch * 4);
+  f32x4 old[NG][8];
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) old[g][i] = rows_old(rs, lane, i, pitch, g);
+  sched_fence();
   static_for<NG>([&](auto g_) {
     constexpr int g = decltype(g_)::value;
-    f32x4 old[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      old[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                             rs, (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0));
     rows_stage<g>(buf, lane, acc, scale);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, old[i] + rows_read(buf, lane, i)), rs,
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, old[g][i] + rows_read(buf, lane, i)), rs,
                                              (rows_row(lane, i) * pitch + rows_col(lane, i)) * 4 + 256 * g, 0, 0);
   });
 }
