@@ -148,9 +148,10 @@ int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, h
   put(w.qitems_off, qrec);
   // the split lists last, one after another, so that only what is there is copied
   size_t end = w.lists_off;
-  auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads) {
+  auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads, Ahead* ahead = nullptr) {
     UnitList l;
-    split_units(pr, kernel, records, heads, &l);
+    split_units(pr, kernel, records, heads, &l, ahead ? *ahead : Ahead{});
+    if (ahead) *ahead = launch_load(pr, kernel, records, heads, l);
     if (l.units.empty()) return ListSize{};
     ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts};
     auto next = [&](const std::vector<int32_t>& v) {
@@ -165,9 +166,10 @@ int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, h
   };
   rec->fwd = put_list(Kernel::kFwd, qrec, pr.H);
   if (backward) {
-    rec->dq = put_list(Kernel::kDq, qrec, pr.H);
     // one split whatever the heads of a pass: dK and dV then sum in the same order on every path
-    rec->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv);
+    Ahead ahead;
+    rec->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv, &ahead);
+    rec->dq = put_list(Kernel::kDq, qrec, pr.H, &ahead);
   }
   rec->has_kitems = backward;
   if (end > w.d_off) return HYDRA_ERR_WORKSPACE;  // the lists' bound: never so

@@ -249,7 +249,24 @@ int64_t record_tiles(const Problem& pr, Kernel kernel, const int32_t* u) {
 
 }  // namespace
 
-void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out) {
+Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, const UnitList& list) {
+  Ahead a;
+  const std::vector<int32_t>& units = list.units.empty() ? records : list.units;
+  const double group = split_cost(kernel).group;
+  for (size_t i = 0; i < units.size(); i += kUnitInts) {
+    const int32_t* u = &units[i];
+    const double t = group + double(u[25] < 0 ? record_tiles(pr, kernel, u) : u[25] - u[24]);
+    a.sum += t * heads;
+    a.longest = std::max(a.longest, t);
+    a.shortest = i == 0 ? t : std::min(a.shortest, t);
+  }
+  a.groups = int64_t(units.size()) / kUnitInts * heads;
+  a.merges = !list.merges.empty();
+  return a;
+}
+
+void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out,
+                 const Ahead& ahead) {
   *out = UnitList{};
   const int64_t n = int64_t(records.size()) / kUnitInts;
   if (n == 0 || heads <= 0 || n * heads >= kSplitBelow) return;
@@ -262,6 +279,9 @@ void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& r
   if (longest < 2 * kMinPart) return;
   // The launch's time with items of more than `most` tiles cut into near-equal parts: one round
   // ends with its longest workgroup; several are filled evenly but for about half a workgroup.
+  // Behind a full round of others the first workgroup starts when the shortest of those ends; and
+  // where those are merged, a merge is no launch of its own.  (2K rows x 16 heads: dQ alone took
+  // 240 parts to fill the chip; behind dK/dV its 128 whole items do.)
   const SplitCost cost = split_cost(kernel);
   auto parts_of = [](int64_t t, int64_t most) { return t > most ? (t + most - 1) / most : int64_t(1); };
   auto time_of = [&](int64_t most, int64_t* parts) {
@@ -275,15 +295,16 @@ void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& r
       sum += double(t) + double(k) * cost.group;
       top = std::max(top, double((t + k - 1) / k) + cost.group);
     }
-    if (units * heads <= kCus) return top;
-    return std::max(top, sum * heads / kCus + 0.5 * sum / double(units));
+    if (ahead.groups + units * heads <= kCus) return std::max(top, ahead.longest);
+    const double start = ahead.groups >= kCus ? ahead.shortest : 0;
+    return std::max({start + top, ahead.longest, (ahead.sum + sum * heads) / kCus + 0.5 * sum / double(units)});
   };
   int64_t parts = 0, best_most = longest;
   double best = time_of(longest, &parts);
   for (int d = 2; d <= 32; ++d) {
     const int64_t most = (longest + d - 1) / d;
     if (most < kMinPart) break;
-    const double t = time_of(most, &parts) + cost.merge;
+    const double t = time_of(most, &parts) + (ahead.merges ? 0 : cost.merge);
     if (parts * heads > MAX_PARTS) break;
     if (t < best) {
       best = t;

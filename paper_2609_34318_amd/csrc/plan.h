@@ -46,13 +46,23 @@ struct UnitList {
   std::vector<int32_t> merges;  // kMergeInts each: the item's first row, rows, first part, parts
   int parts = 0;                // parts per head
 };
+// What a launch holds ahead of the list that is split, in tiles (a workgroup's own cost included).
+struct Ahead {
+  int64_t groups = 0;  // workgroups
+  double sum = 0, longest = 0, shortest = 0;
+  bool merges = false;
+};
 constexpr int kMergeInts = 4;
 constexpr int kMaxMerges = MAX_PARTS / 2;  // a split item has at least two parts
 
 // Splits the items of a launch over `heads` heads whose workgroups leave the chip idle (`records`
 // from launch_units).  A unit is a record with [24], [25] its first and last + 1 tile of the
 // item's walk (for dK/dV: of its group * tiles) and [26] its part, or -1 when it is the whole item.
-void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out);
+// `ahead`: the workgroups that the same launch starts before these.
+void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out,
+                 const Ahead& ahead = Ahead{});
+// The launch of a list (of the whole `records` when it has no units) as what is ahead of another.
+Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, const UnitList& list);
 
 // The launch records of plan_items' work items, in the same order (kUnitInts each): the
 // item's 16 ints, then [16] the document boundary of its first row (its start for query

@@ -45,14 +45,21 @@ int main() {
     const WsLayout w = ws_layout(pr);
     CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.noalloc_total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
     size_t list_bytes = 0;
-    for (Kernel k : {Kernel::kFwd, Kernel::kDq, Kernel::kDkdv}) {
+    Ahead ahead;  // dQ goes behind dK/dV
+    for (Kernel k : {Kernel::kFwd, Kernel::kDkdv, Kernel::kDq}) {
       std::vector<int32_t> items, rec;
       plan_items(pr, k == Kernel::kDkdv ? 1 : 0, &items);
       launch_units(pr, k == Kernel::kDkdv ? 1 : 0, items, {}, &rec);
       const int heads = k == Kernel::kDkdv ? pr.Hkv : pr.H;
       const int64_t rows = k == Kernel::kFwd ? FWD_TILE_ROWS : k == Kernel::kDq ? DQ_TILE_ROWS : KV_QTILE_ROWS;
       UnitList l;
-      split_units(pr, k, rec, heads, &l);
+      split_units(pr, k, rec, heads, &l, ahead);
+      if (k == Kernel::kDkdv) {
+        ahead = launch_load(pr, k, rec, heads, l);
+        const size_t groups = (l.units.empty() ? rec : l.units).size() / kUnitInts * size_t(heads);
+        CHECK(ahead.groups == int64_t(groups) && ahead.merges == !l.merges.empty());
+        CHECK(ahead.shortest <= ahead.longest && ahead.longest * double(groups) >= ahead.sum);
+      }
       if (l.units.empty()) {
         CHECK(l.merges.empty() && l.parts == 0);
         ++whole;
