@@ -808,7 +808,8 @@ hipError_t launch_recompute(const AttnArgs& q, int q_merges, const AttnArgs& kv,
   const int64_t nq = (int64_t)q.n_items * q.q_heads, nkv = (int64_t)kv.n_items * kv.kv_heads;
   if (nq + nkv == 0) return hipSuccess;
   const int tok = prof_begin("bwd_recompute", stream);
-  hipLaunchKernelGGL(bwd_recompute_kernel, dim3(unsigned((nkv + N_XCD - 1) / N_XCD * N_XCD + nq)), dim3(512), 0, stream, q, kv);
+  const int64_t kv_blocks = nq > 0 ? (nkv + N_XCD - 1) / N_XCD * N_XCD : nkv;
+  hipLaunchKernelGGL(bwd_recompute_kernel, dim3(unsigned(kv_blocks + nq)), dim3(512), 0, stream, q, kv);
   prof_end(tok, stream);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return launch_merges(q, q_merges, kv, kv_merges, stream);
