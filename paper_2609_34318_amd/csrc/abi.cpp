@@ -107,12 +107,6 @@ int check_ptr(const void* p, bool needed) {
   return aligned16(p) ? HYDRA_OK : HYDRA_ERR_ALIGN;
 }
 
-// A split list in the workspace; no units: the whole items are launched.
-struct ListSize {
-  int units = 0, merges = 0, parts = 0;
-  size_t merges_off = 0, units_off = 0;
-};
-
 // Which problem's plan each workspace holds, as far as this library uploaded it: the
 // planned calls launch on the plan in the workspace, so they refuse a workspace whose
 // plan was made for another problem (its row ranges would not fit the buffers) or that
@@ -126,55 +120,19 @@ struct PlanRecord {
 std::mutex g_plans_mu;
 std::map<const void*, PlanRecord> g_plans;
 
-// Builds the host image of the workspace prefix (documents, records, split lists) and uploads it.
-// backward = false: the forward's part only.
+// Uploads the plan (backward = false: what the forward reads only) and says in *rec what it holds.
 int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, hipStream_t stream, PlanRecord* rec) {
-  std::vector<int32_t> qitems, kitems, qrec, krecs, kbase, kmap32, krec;
-  std::vector<char> img;
-  auto put = [&](size_t off, const std::vector<int32_t>& v) {
-    if (img.size() < off + v.size() * sizeof(int32_t)) img.resize(off + v.size() * sizeof(int32_t), 0);
-    if (!v.empty()) std::memcpy(img.data() + off, v.data(), v.size() * sizeof(int32_t));
-  };
-  plan_items(pr, 0, &qitems);
-  put(w.cu_off, pr.cu);
-  if (backward) {
-    plan_items(pr, 1, &kitems);
-    ds_tables(pr, kitems, &kbase, &kmap32, &krec);
-    launch_units(pr, 1, kitems, kbase, &krecs);
-    put(w.kitems_off, krecs);
-    put(w.krec_off, krec);
-  }
-  launch_units(pr, 0, qitems, kmap32, &qrec);
-  put(w.qitems_off, qrec);
-  // the split lists last, one after another, so that only what is there is copied
-  size_t end = w.lists_off;
-  auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads, Ahead* ahead = nullptr) {
-    UnitList l;
-    split_units(pr, kernel, records, heads, &l, ahead ? *ahead : Ahead{});
-    if (ahead) *ahead = launch_load(pr, kernel, records, heads, l);
-    if (l.units.empty()) return ListSize{};
-    ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts};
-    auto next = [&](const std::vector<int32_t>& v) {
-      const size_t at = end;
-      put(at, v);
-      end = (at + v.size() * sizeof(int32_t) + 255) / 256 * 256;
-      return at;
-    };
-    z.merges_off = next(l.merges);
-    z.units_off = next(l.units);
-    return z;
-  };
-  rec->fwd = put_list(Kernel::kFwd, qrec, pr.H);
-  if (backward) {
-    // one split whatever the heads of a pass: dK and dV then sum in the same order on every path
-    Ahead ahead;
-    rec->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv, &ahead);
-    rec->dq = put_list(Kernel::kDq, qrec, pr.H, &ahead);
-  }
+  PlanImage img;
+  plan_image(pr, w, backward, &img);
   rec->has_kitems = backward;
-  if (end > w.d_off) return HYDRA_ERR_WORKSPACE;  // the lists' bound: never so
-  // Pageable source: the runtime has consumed `img` when the call returns.
-  if (hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, stream) != hipSuccess) return HYDRA_ERR_HIP;
+  rec->fwd = img.fwd;
+  rec->dq = img.dq;
+  rec->kv = img.kv;
+  if (img.off + img.bytes.size() > w.d_off) return HYDRA_ERR_WORKSPACE;  // the lists' bound: never so
+  // Pageable source: the runtime has consumed the image when the call returns.
+  if (hipMemcpyAsync(static_cast<char*>(ws) + img.off, img.bytes.data(), img.bytes.size(), hipMemcpyHostToDevice,
+                     stream) != hipSuccess)
+    return HYDRA_ERR_HIP;
   return HYDRA_OK;
 }
 
@@ -225,6 +183,7 @@ AttnArgs base_args(const Problem& pr, const WsLayout& w, void* ws) {
   a.Dvec = reinterpret_cast<float*>(base + w.d_off);
   a.lse2 = reinterpret_cast<float*>(base + w.lse2_off);
   a.krec = reinterpret_cast<const int*>(base + w.krec_off);
+  a.qslots = reinterpret_cast<const int*>(base + w.qslots_off);
   a.split = base + w.split_off;
   a.H = pr.H;
   a.Hkv = pr.Hkv;

@@ -286,7 +286,7 @@ __device__ __forceinline__ void bwd_dkdv_body(const AttnArgs& a, int block, lds_
   const int poff = pair * (KV_NSB * 2048) + lane * 16;  // this lane's P slot: + sb*2048 + half*1024
   const bool active = kn_w > 0;               // uniform over the pair
   // first dS slot of this key item (stored-dS backward only)
-  const int ds_slot0 = it.x0, ds_head0 = kvl * a.grp;
+  const int ds_slot0 = it.ds_slot, ds_head0 = kvl * a.grp;
 
   // The two roles run separate copies of the tile loop, with the same copies and the same
   // two barriers per tile: each copy keeps only its own role's operands and accumulators
@@ -569,8 +569,11 @@ struct DsWalk {
 };
 
 typedef const __attribute__((address_space(4))) i32x16 crec16;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) i32x4 cint4;
 
-// The item's ranges, a value type of scalars like TileRanges.
+// The item's ranges, a value type of scalars like TileRanges; x*: the record (krec) of the key item
+// that holds the range's first row.
 struct DsRanges {
   int nr, r0, p0, c0, x0, r1, p1, c1, x1, r2, p2, c2, x2, r3, p3, c3, x3;
 };
@@ -633,8 +636,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_ds_kernel(AttnArgs a) {
   const Item it(a.items, item);
   const bool wave_rows = 32 * wave < it.n;  // the wave's 32 query rows (all valid or none)
   const int qrow0 = it.row0 + 32 * wave;
-  const DsRanges R = {it.nr,  it.r0, it.p0, it.c0, it.x0, it.r1, it.p1, it.c1, it.x1,
-                      it.r2, it.p2, it.c2, it.x2, it.r3, it.p3, it.c3, it.x3};
+  const i32x4 x = *(cint4*)(a.qslots + (int64_t)item * MAX_RANGES);
+  const DsRanges R = {it.nr, it.r0, it.p0, it.c0, x[0], it.r1, it.p1, it.c1, x[1],
+                      it.r2, it.p2, it.c2, x[2],  it.r3, it.p3, it.c3, x[3]};
   DsWalk walk;
   walk.rr = -1;
   walk.r = 0;

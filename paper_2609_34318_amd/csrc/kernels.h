@@ -586,7 +586,7 @@ struct Item {
   int row0, pos0, n, nr;
   int r0, p0, c0, r1, p1, c1, r2, p2, c2, r3, p3, c3;
   int edge0, lo_last, d0, d1;  // document boundary of the first row, start of the last row's, their indices
-  int x0, x1, x2, x3;          // query items: first key record of each range; key items: x0 = first dS slot
+  int ds_slot;                 // key items: first dS slot
   int t0, t1, part;            // tiles of the walk (t1 < 0: to its end), part of a split item or -1
 
   __device__ __forceinline__ Item(const int* items, int idx) {
@@ -611,10 +611,7 @@ struct Item {
     lo_last = __builtin_amdgcn_readfirstlane(s[17]);
     d0 = __builtin_amdgcn_readfirstlane(s[18]);
     d1 = __builtin_amdgcn_readfirstlane(s[19]);
-    x0 = __builtin_amdgcn_readfirstlane(s[20]);
-    x1 = __builtin_amdgcn_readfirstlane(s[21]);
-    x2 = __builtin_amdgcn_readfirstlane(s[22]);
-    x3 = __builtin_amdgcn_readfirstlane(s[23]);
+    ds_slot = __builtin_amdgcn_readfirstlane(s[20]);
     t0 = __builtin_amdgcn_readfirstlane(s[24]);
     t1 = __builtin_amdgcn_readfirstlane(s[25]);
     part = __builtin_amdgcn_readfirstlane(s[26]);
@@ -688,10 +685,12 @@ struct AttnArgs {
   int kv_head0, kv_heads;
   int q_head0, q_heads;
   // stored-dS backward: dS blocks of the launch's query heads, ds_head_bytes apart; the key
-  // items in row order as records (row0, rows, ranges, first slot, ranges)
+  // items in row order as records (row0, rows, ranges, first slot, ranges); of each query item
+  // the record of the key item that holds each range's first row
   char* ds;
   int64_t ds_head_bytes;
   const int* krec;
+  const int* qslots;
   // split launches: the parts of all heads, parts per head, and the split items (merges)
   char* split;
   int n_parts;

@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <numeric>
 
 namespace hydra {
@@ -186,7 +187,7 @@ void plan_items(const Problem& pr, int which, std::vector<int32_t>* items) {
 }
 
 void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
-                  const std::vector<int32_t>& table, std::vector<int32_t>* units) {
+                  const std::vector<int32_t>& kbase, std::vector<int32_t>* units) {
   const size_t n = items.size() / kItemInts;
   units->assign(n * kUnitInts, 0);
   for (size_t i = 0; i < n; ++i) {
@@ -199,11 +200,7 @@ void launch_units(const Problem& pr, int which, const std::vector<int32_t>& item
     u[18] = d0;
     u[19] = d1;
     u[25] = u[26] = -1;
-    if (table.empty()) continue;
-    if (which == 0)
-      for (int r = 0; r < it[3]; ++r) u[20 + r] = table[size_t(it[4 + 3 * r]) / 32];
-    else
-      u[20] = table[i];
+    if (!kbase.empty()) u[20] = kbase[i];
   }
 }
 
@@ -413,14 +410,16 @@ WsLayout ws_layout(const Problem& pr) {
   w.n_qitems = nqt;
   w.n_kitems = nkt;
   size_t off = 0;
+  w.krec_off = off;
+  off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
+  w.qslots_off = off;
+  off = align_up(off + size_t(nqt) * HYDRA_MAX_SEGS * sizeof(int32_t), 256);
+  w.kitems_off = off;
+  off = align_up(off + size_t(nkt) * kUnitInts * sizeof(int32_t), 256);
   w.cu_off = off;
   off = align_up(off + pr.cu.size() * sizeof(int32_t), 256);
   w.qitems_off = off;
   off = align_up(off + size_t(nqt) * kUnitInts * sizeof(int32_t), 256);
-  w.kitems_off = off;
-  off = align_up(off + size_t(nkt) * kUnitInts * sizeof(int32_t), 256);
-  w.krec_off = off;
-  off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
   w.lists_off = off;
   auto list = [&](Kernel kernel, int64_t n, size_t part_bytes) {
     const size_t parts = size_t(parts_bound(pr, kernel));
@@ -440,6 +439,59 @@ WsLayout ws_layout(const Problem& pr) {
   w.total = std::max<size_t>(off + std::max(fwd, dq + kv), 256);
   w.noalloc_total = std::max<size_t>(off + std::max({fwd, dq, kv}), 256);
   return w;
+}
+
+void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* out) {
+  *out = PlanImage{};
+  out->off = backward ? w.krec_off : w.cu_off;
+  auto put = [&](size_t off, const std::vector<int32_t>& v) {
+    const size_t at = off - out->off, end = at + v.size() * sizeof(int32_t);
+    if (out->bytes.size() < end) out->bytes.resize(end, 0);
+    if (!v.empty()) std::memcpy(out->bytes.data() + at, v.data(), v.size() * sizeof(int32_t));
+  };
+  std::vector<int32_t> qitems, kitems, qrec, krecs;
+  plan_items(pr, 0, &qitems);
+  launch_units(pr, 0, qitems, {}, &qrec);
+  if (backward) {
+    std::vector<int32_t> kbase, kmap32, krec, qslots(qitems.size() / kItemInts * HYDRA_MAX_SEGS, 0);
+    plan_items(pr, 1, &kitems);
+    ds_tables(pr, kitems, &kbase, &kmap32, &krec);
+    for (size_t i = 0; i < qitems.size() / kItemInts; ++i) {
+      const int32_t* it = &qitems[i * kItemInts];
+      for (int r = 0; r < it[3]; ++r) qslots[i * HYDRA_MAX_SEGS + size_t(r)] = kmap32[size_t(it[4 + 3 * r]) / 32];
+    }
+    launch_units(pr, 1, kitems, kbase, &krecs);
+    put(w.krec_off, krec);
+    put(w.qslots_off, qslots);
+    put(w.kitems_off, krecs);
+  }
+  put(w.cu_off, pr.cu);
+  put(w.qitems_off, qrec);
+  // the split lists last, one after another, so that only what is there is copied
+  size_t end = w.lists_off;
+  auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads, Ahead* ahead) {
+    UnitList l;
+    split_units(pr, kernel, records, heads, &l, ahead ? *ahead : Ahead{});
+    if (ahead) *ahead = launch_load(pr, kernel, records, heads, l);
+    if (l.units.empty()) return ListSize{};
+    ListSize z{int(l.units.size()) / kUnitInts, int(l.merges.size()) / kMergeInts, l.parts, 0, 0};
+    auto next = [&](const std::vector<int32_t>& v) {
+      const size_t at = end;
+      put(at, v);
+      end = align_up(at + v.size() * sizeof(int32_t), 256);
+      return at;
+    };
+    z.merges_off = next(l.merges);
+    z.units_off = next(l.units);
+    return z;
+  };
+  out->fwd = put_list(Kernel::kFwd, qrec, pr.H, nullptr);
+  if (backward) {
+    // one split whatever the heads of a pass: dK and dV then sum in the same order on every path
+    Ahead ahead;
+    out->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv, &ahead);
+    out->dq = put_list(Kernel::kDq, qrec, pr.H, &ahead);
+  }
 }
 
 }  // namespace hydra

@@ -67,23 +67,43 @@ Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& 
 // The launch records of plan_items' work items, in the same order (kUnitInts each): the
 // item's 16 ints, then [16] the document boundary of its first row (its start for query
 // items, its end for key items), [17] the start of its last row's document, [18], [19] the
-// document indices of its first and last row, [20..23] per visible range of a query item the
-// row-order index of the key item that holds the range's first row (see ds_tables), or [20]
-// of a key item its first dS slot; [24] = 0, [25] = -1 (all tiles), [26] = -1 (whole).  A kernel that reads one record instead of searching
-// cu_seqlens and the tables has one memory round trip before its first copy, not several.
+// document indices of its first and last row, [20] of a key item its first dS slot (`kbase`, see
+// ds_tables); [24] = 0, [25] = -1 (all tiles), [26] = -1 (whole).  A kernel that reads one record
+// instead of searching cu_seqlens has one memory round trip before its first copy, not several.
+// `kbase` is empty for query items: their records hold nothing of the key side, so that they are
+// the same whether or not the key side is planned (plan_image).
 void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
-                  const std::vector<int32_t>& table, std::vector<int32_t>* units);
+                  const std::vector<int32_t>& kbase, std::vector<int32_t>* units);
 
-// Byte offsets of the workspace regions.  lists holds the split lists that a plan has, one after
+// Byte offsets of the workspace regions, in this order: the key side (krec, qslots, kitems), then
+// what the forward reads (cu, qitems, and at lists the forward's split list), then the backward's
+// split lists, D and LSE*log2(e).  lists holds the split lists that a plan has, one after
 // another (merges, then units), of no size for a problem none of whose launches can be split;
 // split the parts, kv_split those of dK/dV in a launch with dQ.  noalloc_total: without room for
 // both of those, which then take turns.
 struct WsLayout {
-  size_t cu_off, qitems_off, kitems_off, krec_off, lists_off, d_off, lse2_off, split_off, kv_split_off;
+  size_t krec_off, qslots_off, kitems_off, cu_off, qitems_off, lists_off, d_off, lse2_off, split_off, kv_split_off;
   size_t total, noalloc_total;
   int64_t n_qitems, n_kitems;
 };
 WsLayout ws_layout(const Problem& pr);
+
+// A split list in the workspace; no units: the whole items are launched.
+struct ListSize {
+  int units = 0, merges = 0, parts = 0;
+  size_t merges_off = 0, units_off = 0;
+};
+
+// What an upload writes: `bytes` at workspace offset `off`.
+struct PlanImage {
+  size_t off = 0;
+  std::vector<char> bytes;
+  ListSize fwd, dq, kv;
+};
+// backward = false: what the forward reads only.  Every byte of it is a function of the problem
+// alone, and the forward's image is a range of the complete one: an upload for a call on the same
+// problem leaves a plan that a recorded graph still reads as it was.
+void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* out);
 
 // What the no-allocation backward's 32 MiB limit is counted on: D, LSE*log2(e), the documents,
 // 64 bytes per query tile, 148 per key tile (its item, its record, its dS slot and its 32-key
@@ -104,7 +124,8 @@ bool ds_path_applies(const Problem& pr);
 // slot of item i (slots of 24 KB, one per query tile of the item); the items again in
 // row order as records of kItemInts ints, krec[j] = {row0, n, n_ranges, first slot, then
 // (first row, rows) of each query range}; kmap32[b] = the row-order index of the item
-// holding local key rows [32b, 32b + 32).  Returns the slots per query head.
+// holding local key rows [32b, 32b + 32).  Returns the slots per query head.  (qslots, in the
+// workspace: per query item, in launch order, the kmap32 entry of the first row of each range.)
 int64_t ds_tables(const Problem& pr, const std::vector<int32_t>& kitems, std::vector<int32_t>* kbase,
                   std::vector<int32_t>* kmap32, std::vector<int32_t>* krec);
 

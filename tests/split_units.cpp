@@ -1,6 +1,7 @@
 // Split launch lists of random problems: each item's tiles are covered once by its units, in
 // order; parts are numbered without gaps and fit the scratch; the merges name them; the list
-// fits its workspace region.  Built with g++ (no GPU code) by tests/test_split_units.py.
+// fits its workspace region.  And the plan images: what a forward's upload writes is what the
+// complete plan has there.  Built with g++ (no GPU code) by tests/test_split_units.py.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -44,6 +45,14 @@ int main() {
     CHECK(check_problem(&p, &pr) == HYDRA_OK);
     const WsLayout w = ws_layout(pr);
     CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.noalloc_total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
+    PlanImage all, fwd;
+    plan_image(pr, w, true, &all);
+    plan_image(pr, w, false, &fwd);
+    CHECK(all.off + all.bytes.size() <= w.d_off && fwd.off >= all.off);
+    CHECK(fwd.off + fwd.bytes.size() <= all.off + all.bytes.size());
+    CHECK(std::equal(fwd.bytes.begin(), fwd.bytes.end(), all.bytes.begin() + int64_t(fwd.off - all.off)));
+    CHECK(fwd.fwd.units == all.fwd.units && fwd.fwd.units_off == all.fwd.units_off && fwd.dq.units + fwd.kv.units == 0);
+    CHECK(fwd.fwd.merges == all.fwd.merges && fwd.fwd.merges_off == all.fwd.merges_off);
     size_t list_bytes = 0;
     Ahead ahead;  // dQ goes behind dK/dV
     for (Kernel k : {Kernel::kFwd, Kernel::kDkdv, Kernel::kDq}) {

@@ -1,6 +1,7 @@
 """Forms of one launch against each other: a ring step merged by its own kernel against the partial
 and the merge call; the backward's dQ and dK/dV in one launch against two, split and whole; the
-split dK/dV of the stored-dS passes against the recompute path's."""
+split dK/dV of the stored-dS passes against the recompute path's; recorded calls before and after an
+upload for the same problem."""
 import math
 
 import pytest
@@ -118,3 +119,33 @@ def test_stored_ds_passes_sum_dk_dv_alike(kv_heads):
     ds = torch.empty(hydra.bwd_ds_bytes(p, kv_heads), dtype=torch.uint8, device="cuda")
     a, b = _backward(hydra.attn_bwd, p, t), _backward(hydra.attn_bwd_ds, p, t, ds)
     assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+
+
+def test_recorded_calls_survive_a_forward_of_the_same_problem():
+    """A forward that uploads its own plan into the workspace of a recorded forward and backward of
+    the same problem writes the bytes that are there: the replays read the same plan."""
+    for cu, H in (([0, 3000, 4096], 2), ([0, 300], 3)):  # split and whole items
+        p = hydra.Problem(cu, H, [(0, cu[-1])], [(0, cu[-1])])
+        q, k, v, b, lse, d_o, ws = _tensors(p, 63)
+        hydra.attn_plan(p, ws)
+        o = torch.empty((p.nq, H, D_V), device="cuda")
+        grads = [torch.empty((p.nq, H, D_QK), device="cuda"), torch.empty((p.nk, H, D_QK), device="cuda"),
+                 torch.empty((p.nk, H, D_V), device="cuda")]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for t in grads:
+                t.fill_(0.0)
+            hydra.attn_fwd(p, q, k, v, o, lse, ws, o_bf16=b, planned=True)
+            hydra.attn_bwd(p, q, k, v, b, lse, d_o, *grads, ws, planned=True)
+        want = None
+        for rep in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            got = [t.clone() for t in grads + [o, lse]]
+            want = want or got
+            for x, y in zip(got, want):
+                assert torch.equal(x, y), rep
+            assert all(bool(t.abs().max() > 0) for t in got)
+            hydra.attn_fwd(p, q, k, v, torch.empty_like(o), torch.empty_like(lse), ws)
+            torch.cuda.synchronize()
