@@ -120,6 +120,23 @@ int hydra_attn_fwd_merge(const hydra_problem_t* p, const void* q, const void* k,
                          float* o_acc, float* lse_acc, void* o_bf16, void* workspace,
                          size_t workspace_bytes, int32_t planned, void* stream);
 
+/* hydra_attn_fwd, hydra_attn_fwd_merge (merge != 0) and their planned forms (planned != 0) with
+ * `scratch` for split work items.  A step of few (tile, head) work items leaves most of the GPU idle;
+ * with scratch, the longest items of such a step are cut into parts for several workgroups, which
+ * leave their partial sums there for a second, small kernel to add in a fixed order.  Results are
+ * deterministic, and differ from the calls without scratch by rounding (the order of the sums).
+ *   scratch        NULL (the call is the one without), or device memory, 16-byte aligned, that
+ *                  overlaps no other argument; its contents are meaningless afterwards
+ *   scratch_bytes  its size.  hydra_split_scratch_size(p) holds the parts of every launch of `p`, the
+ *                  backward's included (at most 88 MiB; 0: nothing is split); where a launch's
+ *                  parts do not fit, its items stay whole.
+ * Calls on one plan, which a planned call only reads, may overlap where each has a scratch of its
+ * own (or none); calls that share a scratch must not. */
+int hydra_attn_fwd_split(const hydra_problem_t* p, const void* q, const void* k, const void* v,
+                         float* o, float* lse, void* o_bf16, void* workspace, size_t workspace_bytes,
+                         void* scratch, size_t scratch_bytes, int32_t merge, int32_t planned, void* stream);
+size_t hydra_split_scratch_size(const hydra_problem_t* p);
+
 /* Backward of one ring step, given the FINAL merged output and LSE of the rows (the same
  * function is differentiated at every step):
  *   o_final [Nq][H][128] bf16, lse_final [H][Nq] fp32, d_o [Nq][H][128] bf16
@@ -155,6 +172,15 @@ int hydra_attn_bwd_ds(const hydra_problem_t* p, const void* q, const void* k, co
                       float* dq_acc, float* dk_acc, float* dv_acc, void* ds_buf, size_t ds_bytes,
                       void* workspace, size_t workspace_bytes, void* stream);
 
+/* hydra_attn_bwd, hydra_attn_bwd_ds (ds_buf not NULL) and hydra_attn_bwd_planned (planned != 0;
+ * ds_buf must be NULL) with scratch for split work items, as hydra_attn_fwd_split.  Given the same
+ * scratch_bytes, dK and dV are the same bit for bit with and without ds_buf. */
+int hydra_attn_bwd_split(const hydra_problem_t* p, const void* q, const void* k, const void* v,
+                         const void* o_final, const float* lse_final, const void* d_o,
+                         float* dq_acc, float* dk_acc, float* dv_acc, void* ds_buf, size_t ds_bytes,
+                         void* workspace, size_t workspace_bytes, void* scratch, size_t scratch_bytes,
+                         int32_t planned, void* stream);
+
 /* Bytes of ds_buf that hydra_attn_bwd_ds needs to process `kv_heads_per_pass` K/V heads (and
  * their query heads) per pass; 0 when `p` is invalid or the stored-dS path does not apply
  * (host only). */
@@ -181,8 +207,9 @@ size_t hydra_noalloc_scratch_bytes(void);
  * host, and only launch kernels (no copy, no host-side wait), reading the plan from the
  * workspace.  The workspace must hold the plan of this same problem (same cu_seqlens,
  * chunks and head counts; strides may differ) and must not be reused for another problem
- * while a recorded graph still uses it; one workspace per ring step.  The backward writes
- * D and LSE*log2(e) into the workspace as before.  The library remembers, per workspace
+ * while a recorded graph still uses it; one workspace per ring step.  The forward only reads the
+ * workspace, so forwards of one plan may overlap on several streams, with each other and with one
+ * backward; the backward writes D and LSE*log2(e) into it.  The library remembers, per workspace
  * address, which problem its last upload was for (hydra_attn_plan, or the upload inside
  * hydra_attn_fwd / hydra_attn_bwd, where the forward's holds only the query-side items):
  * a planned call on a workspace whose recorded plan is another problem's, or lacks the

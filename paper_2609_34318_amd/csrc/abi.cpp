@@ -16,8 +16,8 @@
 
 namespace hydra {
 hipError_t launch_attn_fwd(const AttnArgs& a, const Launch& l, uint16_t* o_bf16, bool merge, hipStream_t stream);
-hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
-                           char* kv_split, int kv_heads_per_pass, hipStream_t stream);
+hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, char* dq_parts, const Launch& kv,
+                           char* kv_parts, int kv_heads_per_pass, hipStream_t stream);
 hipError_t launch_lse_merge(int64_t n_rows, int H, float* o_acc, float* lse_acc, const float* o_part,
                             const float* lse_part, uint16_t* o_bf16, hipStream_t stream);
 }  // namespace hydra
@@ -120,11 +120,12 @@ struct PlanRecord {
 std::mutex g_plans_mu;
 std::map<const void*, PlanRecord> g_plans;
 
-// Uploads the plan (backward = false: what the forward reads only) and says in *rec what it holds.
-int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, hipStream_t stream, PlanRecord* rec) {
+// Uploads the plan (see plan_image) and says in *rec what it holds.
+int upload_plan(const Problem& pr, const WsLayout& w, PlanFor call, bool lists, void* ws, hipStream_t stream,
+                PlanRecord* rec) {
   PlanImage img;
-  plan_image(pr, w, backward, &img);
-  rec->has_kitems = backward;
+  plan_image(pr, w, call, lists, &img);
+  rec->has_kitems = call != PlanFor::kForward;
   rec->fwd = img.fwd;
   rec->dq = img.dq;
   rec->kv = img.kv;
@@ -136,10 +137,24 @@ int upload_plan(const Problem& pr, const WsLayout& w, bool backward, void* ws, h
   return HYDRA_OK;
 }
 
-// A launch of the whole items at `whole`, or of the split list.
-Launch list_launch(void* ws, size_t whole, int64_t n_whole, const ListSize& l) {
+// A call's scratch for the parts of split items: none (null) launches the whole items.
+struct Scratch {
+  char* at = nullptr;
+  uint64_t bytes = 0;
+  // `need` bytes at its start; null where it holds fewer, and for no bytes
+  char* take(uint64_t need) {
+    if (!at || need == 0 || bytes < need) return nullptr;
+    char* p = at;
+    at += need;
+    bytes -= need;
+    return p;
+  }
+};
+
+// A launch of the split list, where its parts have a place, or of the whole items at `whole`.
+Launch list_launch(void* ws, size_t whole, int64_t n_whole, const ListSize& l, const char* parts) {
   auto at = [&](size_t off) { return reinterpret_cast<const int*>(static_cast<const char*>(ws) + off); };
-  if (l.units == 0) return {at(whole), int(n_whole), nullptr, 0, 0};
+  if (!parts) return {at(whole), int(n_whole), nullptr, 0, 0};
   return {at(l.units_off), l.units, at(l.merges_off), l.merges, l.parts};
 }
 
@@ -184,7 +199,6 @@ AttnArgs base_args(const Problem& pr, const WsLayout& w, void* ws) {
   a.lse2 = reinterpret_cast<float*>(base + w.lse2_off);
   a.krec = reinterpret_cast<const int*>(base + w.krec_off);
   a.qslots = reinterpret_cast<const int*>(base + w.qslots_off);
-  a.split = base + w.split_off;
   a.H = pr.H;
   a.Hkv = pr.Hkv;
   a.grp = pr.H / pr.Hkv;
@@ -218,7 +232,7 @@ namespace {
 // Forward of one ring step; `upload` = false launches only (the plan is already in the
 // workspace, from hydra_attn_plan); `merge` = true merges the partial into o_part and lse_part.
 int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
-                  float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
+                  float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, Scratch scratch, void* stream) {
   try {
     Problem pr;
     int rc = check_problem(p, &pr);
@@ -226,7 +240,8 @@ int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void*
     if (pr.nq == 0) return HYDRA_OK;
     const bool has_k = pr.nk > 0;
     for (int c : {check_ptr(q, true), check_ptr(k, has_k), check_ptr(v, has_k), check_ptr(o_part, true),
-                  check_ptr(lse_part, true), o_bf16 ? check_ptr(o_bf16, true) : HYDRA_OK})
+                  check_ptr(lse_part, true), o_bf16 ? check_ptr(o_bf16, true) : HYDRA_OK,
+                  scratch.at ? check_ptr(scratch.at, true) : HYDRA_OK})
       if (c != HYDRA_OK) return c;
     const WsLayout w = ws_layout(pr);
     if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
@@ -234,13 +249,14 @@ int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void*
     const uint64_t qh = uint64_t(pr.nq) * pr.H;
     const uint64_t qb = rows_bytes(pr.nq, pr.q_s, pr.H * kDqk), kb = rows_bytes(pr.nk, pr.k_s, pr.Hkv * kDqk),
                    vb = rows_bytes(pr.nk, pr.v_s, pr.Hkv * kDv);
-    if (outputs_overlap({{o_part, qh * kDv * 4}, {lse_part, qh * 4}, {o_bf16, qh * kDv * 2}, {workspace, w.total}},
+    if (outputs_overlap({{o_part, qh * kDv * 4}, {lse_part, qh * 4}, {o_bf16, qh * kDv * 2}, {workspace, w.total},
+                         {scratch.at, scratch.bytes}},
                         {{q, qb}, {k, kb}, {v, vb}}))
       return HYDRA_ERR_INVALID;
     hipStream_t s = static_cast<hipStream_t>(stream);
     PlanRecord plan;
     if (upload) {  // the forward needs only the query-stationary items
-      rc = upload_plan(pr, w, false, workspace, s, &plan);
+      rc = upload_plan(pr, w, PlanFor::kForward, scratch.at != nullptr, workspace, s, &plan);
       if (rc != HYDRA_OK) return rc;
       record_plan(workspace, pr, PlanRecord(plan));
     } else if (!plan_matches(workspace, pr, false, &plan)) {
@@ -252,7 +268,8 @@ int attn_fwd_impl(bool upload, bool merge, const hydra_problem_t* p, const void*
     a.v = static_cast<const uint16_t*>(v);
     a.out_o = o_part;
     a.out_lse = lse_part;
-    const Launch l = list_launch(workspace, w.qitems_off, w.n_qitems, plan.fwd);
+    a.split = scratch.take(parts_bytes(Kernel::kFwd, plan.fwd, pr.H));
+    const Launch l = list_launch(workspace, w.qitems_off, w.n_qitems, plan.fwd, a.split);
     if (launch_attn_fwd(a, l, static_cast<uint16_t*>(o_bf16), merge, s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
@@ -270,8 +287,8 @@ uint64_t ds_bytes_per_head(const Problem& pr) {
 
 int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const void* k, const void* v,
                   const void* o_final, const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc,
-                  float* dv_acc, void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes,
-                  void* stream, bool noalloc = false) {
+                  float* dv_acc, void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes, Scratch scratch,
+                  void* stream) {
   try {
     Problem pr;
     int rc = check_problem(p, &pr);
@@ -279,10 +296,10 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     if (pr.nq == 0 || pr.nk == 0) return HYDRA_OK;
     for (int c : {check_ptr(q, true), check_ptr(k, true), check_ptr(v, true), check_ptr(o_final, true),
                   check_ptr(lse_final, true), check_ptr(d_o, true), check_ptr(dq_acc, true),
-                  check_ptr(dk_acc, true), check_ptr(dv_acc, true)})
+                  check_ptr(dk_acc, true), check_ptr(dv_acc, true), scratch.at ? check_ptr(scratch.at, true) : HYDRA_OK})
       if (c != HYDRA_OK) return c;
     const WsLayout w = ws_layout(pr);
-    if (!workspace || workspace_bytes < (noalloc ? w.noalloc_total : w.total)) return HYDRA_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
     // stored-dS path: K/V heads per pass such that their query heads' dS fits ds_buf
     int kv_per_pass = 0;
@@ -298,14 +315,15 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     const uint64_t qb = rows_bytes(pr.nq, pr.q_s, pr.H * kDqk), kb = rows_bytes(pr.nk, pr.k_s, pr.Hkv * kDqk),
                    vb = rows_bytes(pr.nk, pr.v_s, pr.Hkv * kDv);
     if (outputs_overlap({{dq_acc, qh * kDqk * 4}, {dk_acc, kh * kDqk * 4}, {dv_acc, kh * kDv * 4},
-                         {workspace, std::min<uint64_t>(w.total, workspace_bytes)}, {kv_per_pass ? ds_buf : nullptr, ds_used}},
+                         {workspace, w.total}, {kv_per_pass ? ds_buf : nullptr, ds_used}, {scratch.at, scratch.bytes}},
                         {{q, qb}, {k, kb}, {v, vb}, {o_final, qh * kDv * 2}, {lse_final, qh * 4},
                          {d_o, qh * kDv * 2}}))
       return HYDRA_ERR_INVALID;
     hipStream_t s = static_cast<hipStream_t>(stream);
     PlanRecord plan;
     if (upload) {
-      rc = upload_plan(pr, w, true, workspace, s, &plan);
+      rc = upload_plan(pr, w, kv_per_pass ? PlanFor::kStoredDs : PlanFor::kBackward, scratch.at != nullptr, workspace,
+                       s, &plan);
       if (rc != HYDRA_OK) return rc;
       record_plan(workspace, pr, PlanRecord(plan));
     } else if (!plan_matches(workspace, pr, true, &plan)) {
@@ -323,11 +341,13 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
     a.dv = dv_acc;
     a.ds = static_cast<char*>(kv_per_pass ? ds_buf : nullptr);
     a.ds_head_bytes = int64_t(ds_head);
-    const Launch q_whole = list_launch(workspace, w.qitems_off, w.n_qitems, ListSize{});
-    const Launch dq = list_launch(workspace, w.qitems_off, w.n_qitems, plan.dq);
-    const Launch kv = list_launch(workspace, w.kitems_off, w.n_kitems, plan.kv);
-    char* kv_split = workspace_bytes >= w.total ? static_cast<char*>(workspace) + w.kv_split_off : nullptr;
-    if (launch_attn_bwd(a, q_whole, dq, kv, kv_split, kv_per_pass, s) != hipSuccess) return HYDRA_ERR_HIP;
+    // dK/dV's parts first, on either path: whether they are split does not depend on dQ
+    char* kv_parts = scratch.take(parts_bytes(Kernel::kDkdv, plan.kv, pr.Hkv));
+    char* dq_parts = scratch.take(parts_bytes(Kernel::kDq, plan.dq, pr.H));
+    const Launch q_whole = list_launch(workspace, w.qitems_off, w.n_qitems, ListSize{}, nullptr);
+    const Launch dq = list_launch(workspace, w.qitems_off, w.n_qitems, plan.dq, dq_parts);
+    const Launch kv = list_launch(workspace, w.kitems_off, w.n_kitems, plan.kv, kv_parts);
+    if (launch_attn_bwd(a, q_whole, dq, dq_parts, kv, kv_parts, kv_per_pass, s) != hipSuccess) return HYDRA_ERR_HIP;
     return HYDRA_OK;
   } catch (...) {
     return HYDRA_ERR_INVALID;
@@ -347,7 +367,7 @@ int hydra_attn_plan(const hydra_problem_t* p, void* workspace, size_t workspace_
     if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
     PlanRecord plan;
-    rc = upload_plan(pr, w, true, workspace, static_cast<hipStream_t>(stream), &plan);
+    rc = upload_plan(pr, w, PlanFor::kBackward, true, workspace, static_cast<hipStream_t>(stream), &plan);
     if (rc == HYDRA_OK) record_plan(workspace, pr, std::move(plan));
     return rc;
   } catch (...) {
@@ -357,32 +377,40 @@ int hydra_attn_plan(const hydra_problem_t* p, void* workspace, size_t workspace_
 
 int hydra_attn_fwd(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
                    float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
-  return attn_fwd_impl(true, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
+  return attn_fwd_impl(true, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, Scratch{}, stream);
 }
 
 int hydra_attn_fwd_planned(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_part,
                            float* lse_part, void* o_bf16, void* workspace, size_t workspace_bytes, void* stream) {
-  return attn_fwd_impl(false, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, stream);
+  return attn_fwd_impl(false, false, p, q, k, v, o_part, lse_part, o_bf16, workspace, workspace_bytes, Scratch{}, stream);
 }
 
 int hydra_attn_fwd_merge(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o_acc,
                          float* lse_acc, void* o_bf16, void* workspace, size_t workspace_bytes, int32_t planned,
                          void* stream) {
-  return attn_fwd_impl(planned == 0, true, p, q, k, v, o_acc, lse_acc, o_bf16, workspace, workspace_bytes, stream);
+  return attn_fwd_impl(planned == 0, true, p, q, k, v, o_acc, lse_acc, o_bf16, workspace, workspace_bytes, Scratch{},
+                       stream);
+}
+
+int hydra_attn_fwd_split(const hydra_problem_t* p, const void* q, const void* k, const void* v, float* o, float* lse,
+                         void* o_bf16, void* workspace, size_t workspace_bytes, void* scratch, size_t scratch_bytes,
+                         int32_t merge, int32_t planned, void* stream) {
+  return attn_fwd_impl(planned == 0, merge != 0, p, q, k, v, o, lse, o_bf16, workspace, workspace_bytes,
+                       Scratch{static_cast<char*>(scratch), scratch_bytes}, stream);
 }
 
 int hydra_attn_bwd(const hydra_problem_t* p, const void* q, const void* k, const void* v, const void* o_final,
                    const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc, float* dv_acc,
                    void* workspace, size_t workspace_bytes, void* stream) {
   return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, workspace,
-                       workspace_bytes, stream);
+                       workspace_bytes, Scratch{}, stream);
 }
 
 int hydra_attn_bwd_ds(const hydra_problem_t* p, const void* q, const void* k, const void* v, const void* o_final,
                       const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc, float* dv_acc,
                       void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes, void* stream) {
   return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, ds_buf, ds_bytes,
-                       workspace, workspace_bytes, stream);
+                       workspace, workspace_bytes, Scratch{}, stream);
 }
 
 }  // extern "C"
@@ -431,7 +459,7 @@ int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* 
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws)) != HYDRA_OK) return rc;
     return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, ws,
-                         kNoAllocScratchBytes, stream, true);
+                         kNoAllocScratchBytes, Scratch{}, stream);
   } catch (...) {
     return HYDRA_ERR_INVALID;
   }
@@ -452,7 +480,25 @@ int hydra_attn_bwd_planned(const hydra_problem_t* p, const void* q, const void* 
                            const void* o_final, const float* lse_final, const void* d_o, float* dq_acc,
                            float* dk_acc, float* dv_acc, void* workspace, size_t workspace_bytes, void* stream) {
   return attn_bwd_impl(false, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, workspace,
-                       workspace_bytes, stream);
+                       workspace_bytes, Scratch{}, stream);
+}
+
+int hydra_attn_bwd_split(const hydra_problem_t* p, const void* q, const void* k, const void* v, const void* o_final,
+                         const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc, float* dv_acc,
+                         void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes, void* scratch,
+                         size_t scratch_bytes, int32_t planned, void* stream) {
+  if (planned && ds_buf) return HYDRA_ERR_INVALID;
+  return attn_bwd_impl(planned == 0, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, ds_buf, ds_bytes,
+                       workspace, workspace_bytes, Scratch{static_cast<char*>(scratch), scratch_bytes}, stream);
+}
+
+size_t hydra_split_scratch_size(const hydra_problem_t* p) {
+  try {
+    Problem pr;
+    return check_problem(p, &pr) == HYDRA_OK ? size_t(split_scratch_bytes(pr)) : 0;
+  } catch (...) {
+    return 0;
+  }
 }
 
 int hydra_lse_merge(int64_t n_rows, int32_t n_heads, int32_t d_v, float* o_acc, float* lse_acc,

@@ -821,12 +821,12 @@ hipError_t launch_recompute(const AttnArgs& q, int q_merges, const AttnArgs& kv,
 
 }  // namespace
 
-// kv_heads_per_pass = 0: recompute path over all heads (kv_split: the dK/dV parts, apart from dQ's
-// at a.split; null where the scratch holds one kind's parts only: the two then take turns).
+// kv_heads_per_pass = 0: recompute path over all heads.  kv_parts, dq_parts: where the parts of dK/dV
+// and dQ go, for a list that has any.
 // Otherwise the stored-dS path, in passes of that many K/V heads (the dS of one pass's query heads
 // fits a.ds): bwd_dkdv_ds stores dS, then bwd_dq_ds reads it back.
-hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, const Launch& kv,
-                           char* kv_split, int kv_heads_per_pass, hipStream_t stream) {
+hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launch& dq, char* dq_parts, const Launch& kv,
+                           char* kv_parts, int kv_heads_per_pass, hipStream_t stream) {
   const int64_t pairs = (int64_t)a.nq * a.H;
   const int64_t blocks = (pairs + 15) / 16 < (1 << 20) ? (pairs + 15) / 16 : (1 << 20);
   int tok = prof_begin("bwd_pre", stream);
@@ -839,23 +839,22 @@ hipError_t launch_attn_bwd(const AttnArgs& a, const Launch& q_whole, const Launc
     if (q_whole.n_units == 0 || kv.n_units == 0) return hipSuccess;
     for (int g0 = 0; g0 < a.Hkv; g0 += kv_heads_per_pass) {
       const int G = min(kv_heads_per_pass, a.Hkv - g0);
-      AttnArgs b = list_args(a, kv, a.split);
+      AttnArgs b = list_args(a, kv, kv_parts);
       b.kv_head0 = g0;
       b.kv_heads = G;
       b.q_head0 = g0 * a.grp;
       b.q_heads = G * a.grp;
       if ((e = launch_list(bwd_dkdv_ds_kernel, "bwd_dkdv_ds", b, G, stream)) != hipSuccess) return e;
       if ((e = launch_merges(b, 0, b, kv.n_merges, stream)) != hipSuccess) return e;
-      if ((e = launch_list(bwd_dq_ds_kernel, "bwd_dq_ds", list_args(b, q_whole, a.split), G * a.grp, stream)) !=
+      if ((e = launch_list(bwd_dq_ds_kernel, "bwd_dq_ds", list_args(b, q_whole, nullptr), G * a.grp, stream)) !=
           hipSuccess)
         return e;
     }
     return hipSuccess;
   }
   // a dispatch holds fewer than 2^32 lanes
-  const bool turns = (!kv_split && dq.n_merges && kv.n_merges) ||
-                     (int64_t)dq.n_units * a.H + (int64_t)kv.n_units * a.Hkv + N_XCD > (1 << 23);
-  const AttnArgs q_args = list_args(a, dq, a.split), kv_args = list_args(a, kv, kv_split ? kv_split : a.split);
+  const bool turns = (int64_t)dq.n_units * a.H + (int64_t)kv.n_units * a.Hkv + N_XCD > (1 << 23);
+  const AttnArgs q_args = list_args(a, dq, dq_parts), kv_args = list_args(a, kv, kv_parts);
   if (turns) {
     AttnArgs none = a;
     none.n_items = 0;

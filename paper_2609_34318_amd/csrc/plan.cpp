@@ -208,10 +208,6 @@ namespace {
 
 constexpr int kCus = 256;
 
-// Workgroups of a launch below which splitting is considered at all.  At two per CU and more the
-// heavy-first order fills the chip: no shape measured there gained.
-constexpr int64_t kSplitBelow = 2 * kCus;
-
 // In tiles of the kernel's loop: what a workgroup costs besides its tiles (its own rows in, the
 // first copies, its rows out), and the merge launch.  Measured, 2.4 GHz: a forward tile takes
 // 1.7 us, a dQ tile 3.0 us, a dK/dV tile 2.9 us; a workgroup's own cost 4-6 us, a merge 5-7 us.
@@ -226,16 +222,6 @@ SplitCost split_cost(Kernel k) {
 constexpr int64_t kMinPart = 4;
 
 int tile_rows(Kernel k) { return k == Kernel::kFwd ? FWD_TILE_ROWS : k == Kernel::kDq ? DQ_TILE_ROWS : KV_QTILE_ROWS; }
-
-// At least as many parts as any launch of this kernel can have over all its heads (0: none is
-// split): workspace sizes are asked for without a plan.
-int64_t parts_bound(const Problem& pr, Kernel kernel) {
-  const bool kv = kernel == Kernel::kDkdv;
-  const int64_t n = kv ? n_tiles(pr.kv, kKvTile) : n_tiles(pr.q, kQTile);
-  const int64_t most = kv ? n_tiles(pr.q, KV_QTILE_ROWS) * (pr.H / pr.Hkv) : n_tiles(pr.kv, tile_rows(kernel));
-  if (n * (kv ? pr.Hkv : pr.H) >= kSplitBelow || most < 2 * kMinPart) return 0;
-  return std::min<int64_t>(MAX_PARTS, n * ((most + kMinPart - 1) / kMinPart) * (kv ? pr.Hkv : pr.H));
-}
 
 int64_t record_tiles(const Problem& pr, Kernel kernel, const int32_t* u) {
   const int rows = tile_rows(kernel);
@@ -421,29 +407,19 @@ WsLayout ws_layout(const Problem& pr) {
   w.qitems_off = off;
   off = align_up(off + size_t(nqt) * kUnitInts * sizeof(int32_t), 256);
   w.lists_off = off;
-  auto list = [&](Kernel kernel, int64_t n, size_t part_bytes) {
-    const size_t parts = size_t(parts_bound(pr, kernel));
-    if (parts)
-      off = align_up(off + (size_t(kMaxMerges) * kMergeInts + (parts + size_t(n)) * kUnitInts) * sizeof(int32_t), 256);
-    return parts * part_bytes;
-  };
-  const size_t fwd = list(Kernel::kFwd, nqt, FWD_PART_BYTES);
-  const size_t dq = list(Kernel::kDq, nqt, DQ_PART_BYTES);
-  const size_t kv = list(Kernel::kDkdv, nkt, KV_PART_BYTES);
+  off += 3 * kListBytes;
   w.d_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
   w.lse2_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
-  w.split_off = off;
-  w.kv_split_off = off + dq;
-  w.total = std::max<size_t>(off + std::max(fwd, dq + kv), 256);
-  w.noalloc_total = std::max<size_t>(off + std::max({fwd, dq, kv}), 256);
+  w.total = off;
   return w;
 }
 
-void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* out) {
+void plan_image(const Problem& pr, const WsLayout& w, PlanFor call, bool lists, PlanImage* out) {
   *out = PlanImage{};
-  out->off = backward ? w.krec_off : w.cu_off;
+  const bool backward = call != PlanFor::kForward;
+  out->off = call == PlanFor::kStoredDs ? w.krec_off : backward ? w.kitems_off : w.cu_off;
   auto put = [&](size_t off, const std::vector<int32_t>& v) {
     const size_t at = off - out->off, end = at + v.size() * sizeof(int32_t);
     if (out->bytes.size() < end) out->bytes.resize(end, 0);
@@ -453,20 +429,24 @@ void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* 
   plan_items(pr, 0, &qitems);
   launch_units(pr, 0, qitems, {}, &qrec);
   if (backward) {
-    std::vector<int32_t> kbase, kmap32, krec, qslots(qitems.size() / kItemInts * HYDRA_MAX_SEGS, 0);
+    std::vector<int32_t> kbase, kmap32, krec;
     plan_items(pr, 1, &kitems);
     ds_tables(pr, kitems, &kbase, &kmap32, &krec);
-    for (size_t i = 0; i < qitems.size() / kItemInts; ++i) {
-      const int32_t* it = &qitems[i * kItemInts];
-      for (int r = 0; r < it[3]; ++r) qslots[i * HYDRA_MAX_SEGS + size_t(r)] = kmap32[size_t(it[4 + 3 * r]) / 32];
+    if (call == PlanFor::kStoredDs) {
+      std::vector<int32_t> qslots(qitems.size() / kItemInts * HYDRA_MAX_SEGS, 0);
+      for (size_t i = 0; i < qitems.size() / kItemInts; ++i) {
+        const int32_t* it = &qitems[i * kItemInts];
+        for (int r = 0; r < it[3]; ++r) qslots[i * HYDRA_MAX_SEGS + size_t(r)] = kmap32[size_t(it[4 + 3 * r]) / 32];
+      }
+      put(w.krec_off, krec);
+      put(w.qslots_off, qslots);
     }
     launch_units(pr, 1, kitems, kbase, &krecs);
-    put(w.krec_off, krec);
-    put(w.qslots_off, qslots);
     put(w.kitems_off, krecs);
   }
   put(w.cu_off, pr.cu);
   put(w.qitems_off, qrec);
+  if (!lists) return;
   // the split lists last, one after another, so that only what is there is copied
   size_t end = w.lists_off;
   auto put_list = [&](Kernel kernel, const std::vector<int32_t>& records, int heads, Ahead* ahead) {
@@ -492,6 +472,19 @@ void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* 
     out->kv = put_list(Kernel::kDkdv, krecs, pr.Hkv, &ahead);
     out->dq = put_list(Kernel::kDq, qrec, pr.H, &ahead);
   }
+}
+
+uint64_t parts_bytes(Kernel kernel, const ListSize& l, int heads) {
+  const int bytes = kernel == Kernel::kFwd ? FWD_PART_BYTES : kernel == Kernel::kDq ? DQ_PART_BYTES : KV_PART_BYTES;
+  return uint64_t(l.parts) * uint64_t(heads) * uint64_t(bytes);
+}
+
+uint64_t split_scratch_bytes(const Problem& pr) {
+  if (n_tiles(pr.q, kQTile) * pr.H >= kSplitBelow && n_tiles(pr.kv, kKvTile) * pr.Hkv >= kSplitBelow) return 0;
+  PlanImage img;
+  plan_image(pr, ws_layout(pr), PlanFor::kBackward, true, &img);
+  return std::max(parts_bytes(Kernel::kFwd, img.fwd, pr.H),
+                  parts_bytes(Kernel::kDkdv, img.kv, pr.Hkv) + parts_bytes(Kernel::kDq, img.dq, pr.H));
 }
 
 }  // namespace hydra

@@ -54,6 +54,12 @@ struct Ahead {
 };
 constexpr int kMergeInts = 4;
 constexpr int kMaxMerges = MAX_PARTS / 2;  // a split item has at least two parts
+// Workgroups of a launch from which on nothing is split: at two per CU (256) and more the
+// heavy-first order fills the chip, and no shape measured there gained.
+constexpr int64_t kSplitBelow = 512;
+// The most bytes of a split list: its merges, and a unit for every part and every whole item.
+constexpr size_t kListBytes = (size_t(kMaxMerges) * kMergeInts + size_t(MAX_PARTS + kSplitBelow) * kUnitInts) * sizeof(int32_t);
+static_assert(kListBytes % 256 == 0, "lists end on a region boundary");
 
 // Splits the items of a launch over `heads` heads whose workgroups leave the chip idle (`records`
 // from launch_units).  A unit is a record with [24], [25] its first and last + 1 tile of the
@@ -75,15 +81,13 @@ Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& 
 void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,
                   const std::vector<int32_t>& kbase, std::vector<int32_t>* units);
 
-// Byte offsets of the workspace regions, in this order: the key side (krec, qslots, kitems), then
-// what the forward reads (cu, qitems, and at lists the forward's split list), then the backward's
-// split lists, D and LSE*log2(e).  lists holds the split lists that a plan has, one after
-// another (merges, then units), of no size for a problem none of whose launches can be split;
-// split the parts, kv_split those of dK/dV in a launch with dQ.  noalloc_total: without room for
-// both of those, which then take turns.
+// Byte offsets of the workspace regions, in this order: what the stored-dS backward alone reads
+// (krec, qslots), the key items, what the forward reads too (cu, qitems, and at lists the forward's
+// split list), the backward's split lists, D and LSE*log2(e).  lists holds the split lists that a plan has, one after
+// another (merges, then units); it has the same size for every problem, so that no problem needs
+// more workspace than one with more rows.
 struct WsLayout {
-  size_t krec_off, qslots_off, kitems_off, cu_off, qitems_off, lists_off, d_off, lse2_off, split_off, kv_split_off;
-  size_t total, noalloc_total;
+  size_t krec_off, qslots_off, kitems_off, cu_off, qitems_off, lists_off, d_off, lse2_off, total;
   int64_t n_qitems, n_kitems;
 };
 WsLayout ws_layout(const Problem& pr);
@@ -100,20 +104,27 @@ struct PlanImage {
   std::vector<char> bytes;
   ListSize fwd, dq, kv;
 };
-// backward = false: what the forward reads only.  Every byte of it is a function of the problem
-// alone, and the forward's image is a range of the complete one: an upload for a call on the same
-// problem leaves a plan that a recorded graph still reads as it was.
-void plan_image(const Problem& pr, const WsLayout& w, bool backward, PlanImage* out);
+// The calls a plan is for; an upload of up to 16 KB costs some 10 us less than a larger one (ragged 8K
+// window: 387 against 397 us for forward and backward), so a call writes what it reads and no more.
+enum class PlanFor { kForward, kBackward, kStoredDs };
+// lists = false: without the split lists, for a call that launches the whole items.  Every byte of an
+// image is a function of the problem alone, and every image a range of the largest: an upload for a
+// call on the same problem leaves a plan that a recorded graph still reads as it was.
+void plan_image(const Problem& pr, const WsLayout& w, PlanFor call, bool lists, PlanImage* out);
+
+// Bytes of scratch that hold the parts of `l` over `heads` heads.
+uint64_t parts_bytes(Kernel kernel, const ListSize& l, int heads);
+// Scratch with which every launch of a plan that has split lists uses them (the dK/dV parts, then
+// the dQ parts, or the forward's).
+uint64_t split_scratch_bytes(const Problem& pr);
 
 // What the no-allocation backward's 32 MiB limit is counted on: D, LSE*log2(e), the documents,
 // 64 bytes per query tile, 148 per key tile (its item, its record, its dS slot and its 32-key
-// blocks).  The launch records and split lists take more than that, at most 64 bytes per query
-// tile and 48 per key tile and 128 KB: kNoAllocExtraBytes holds them and the parts for every
-// problem within the limit, so that a plan may grow without a call that was accepted being
-// refused, and the call splits as hydra_attn_bwd does.
+// blocks).  The launch records and the lists' region take more than that: kNoAllocExtraBytes holds
+// it for every problem within the limit.
 uint64_t noalloc_bytes(const Problem& pr);
 constexpr size_t kNoAllocLimitBytes = size_t(32) << 20;
-constexpr size_t kNoAllocExtraBytes = (size_t(12) << 20) + SPLIT_BYTES;
+constexpr size_t kNoAllocExtraBytes = size_t(12) << 20;
 
 // The stored-dS backward applies when every segment of both chunks starts and ends on a
 // multiple of 32 positions: the key-stationary tiles then cut the query rows into 32-row

@@ -16,7 +16,7 @@ constexpr int FWD_TILE_ROWS = 64;
 constexpr int DQ_TILE_ROWS = 96;
 
 // A work item split over several workgroups: each leaves its accumulators in a part of the
-// split scratch, as its registers hold them (one 1 KB row of 64 lanes x 16 bytes per four
+// caller's scratch, as its registers hold them (one 1 KB row of 64 lanes x 16 bytes per four
 // registers).  Per wave: 32 rows x 128 (O, with two more rows for the running max and sum, or
 // dV) or x 192 columns (dQ, dK) in fp32.
 constexpr int PART_WAVE_128 = 32 * 128 * 4;
@@ -25,8 +25,7 @@ constexpr int PART_WAVE_O = PART_WAVE_128 + 512;
 constexpr int FWD_PART_BYTES = 8 * PART_WAVE_O;
 constexpr int DQ_PART_BYTES = 8 * PART_WAVE_192;
 constexpr int KV_PART_BYTES = 4 * (PART_WAVE_128 + PART_WAVE_192);
-// Parts of one launch (over all its heads), and the scratch that holds them.
+// Parts of one launch (over all its heads).
 constexpr int MAX_PARTS = 256;
-constexpr long long SPLIT_BYTES = (long long)MAX_PARTS * DQ_PART_BYTES;  // 48 MiB, the largest of the three
 
 }  // namespace hydra

@@ -95,11 +95,19 @@ def lib() -> ctypes.CDLL:
         L.hydra_attn_fwd.restype = ctypes.c_int
         L.hydra_attn_fwd_merge.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, ctypes.c_int32, vp]
         L.hydra_attn_fwd_merge.restype = ctypes.c_int
+        L.hydra_attn_fwd_split.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp, ctypes.c_size_t,
+                                           ctypes.c_int32, ctypes.c_int32, vp]
+        L.hydra_attn_fwd_split.restype = ctypes.c_int
+        L.hydra_split_scratch_size.argtypes = [P]
+        L.hydra_split_scratch_size.restype = ctypes.c_size_t
         L.hydra_attn_bwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.hydra_attn_bwd.restype = ctypes.c_int
         L.hydra_attn_bwd_ds.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp,
                                         ctypes.c_size_t, vp]
         L.hydra_attn_bwd_ds.restype = ctypes.c_int
+        L.hydra_attn_bwd_split.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp,
+                                           ctypes.c_size_t, vp, ctypes.c_size_t, ctypes.c_int32, vp]
+        L.hydra_attn_bwd_split.restype = ctypes.c_int
         L.hydra_bwd_ds_bytes.argtypes = [P, ctypes.c_int32]
         L.hydra_bwd_ds_bytes.restype = ctypes.c_size_t
         L.hydra_attn_bwd_noalloc.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
@@ -187,6 +195,11 @@ class Problem:
 
 def workspace_size(p: Problem) -> int:
     return int(lib().hydra_workspace_size(p.ref))
+
+
+def split_scratch_size(p: Problem) -> int:
+    """Bytes of scratch for the calls' `scratch` (0: nothing of p is split)."""
+    return int(lib().hydra_split_scratch_size(p.ref))
 
 
 def visible_pairs(p: Problem) -> int:
@@ -285,44 +298,55 @@ def attn_plan(p: Problem, workspace, stream=None):
                                  _stream(stream)), "hydra_attn_plan")
 
 
-def attn_fwd(p: Problem, q, k, v, o_part, lse_part, workspace, o_bf16=None, stream=None, planned=False):
+def _scratch(t) -> Tuple[Optional[int], int]:
+    return _ptr(t, "scratch"), 0 if t is None else t.numel() * t.element_size()
+
+
+def _fwd(what: str, merge: bool, p: Problem, q, k, v, o, lse, workspace, o_bf16, stream, planned, scratch):
+    nqh = p.nq * p.n_heads
+    qp, kp, vp = _set_rows(p, q, k, v)
+    _check(lib().hydra_attn_fwd_split(p.ref, qp, kp, vp, _ptr(o, "o", _F32, nqh * 128), _ptr(lse, "lse", _F32, nqh),
+                                      _ptr(o_bf16, "o_bf16", _BF16, nqh * 128), _ptr(workspace, "workspace"),
+                                      workspace.numel() * workspace.element_size(), *_scratch(scratch), int(merge),
+                                      int(planned), _stream(stream)), what)
+
+
+def attn_fwd(p: Problem, q, k, v, o_part, lse_part, workspace, o_bf16=None, stream=None, planned=False, scratch=None):
     """Partial O (fp32) and LSE of one ring step; optional bf16 copy of O.  q, k, v may be
     views whose token rows are further apart than dense (e.g. slices of a fused buffer).
     planned: the workspace already holds p's plan (attn_plan); only kernels are launched,
-    so the call can be recorded into a graph."""
-    nqh = p.nq * p.n_heads
-    qp, kp, vp = _set_rows(p, q, k, v)
-    fn = lib().hydra_attn_fwd_planned if planned else lib().hydra_attn_fwd
-    _check(fn(p.ref, qp, kp, vp, _ptr(o_part, "o_part", _F32, nqh * 128),
-                                _ptr(lse_part, "lse_part", _F32, nqh), _ptr(o_bf16, "o_bf16", _BF16, nqh * 128),
-                                _ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
-                                _stream(stream)), "hydra_attn_fwd")
+    so the call can be recorded into a graph.  scratch: a uint8 device tensor of
+    split_scratch_size(p), used by this call alone, in which a step of few work items is split
+    over more workgroups (results then differ by rounding)."""
+    _fwd("hydra_attn_fwd", False, p, q, k, v, o_part, lse_part, workspace, o_bf16, stream, planned, scratch)
 
 
-def attn_fwd_merge(p: Problem, q, k, v, o_acc, lse_acc, workspace, o_bf16=None, stream=None, planned=False):
+def attn_fwd_merge(p: Problem, q, k, v, o_acc, lse_acc, workspace, o_bf16=None, stream=None, planned=False,
+                   scratch=None):
     """(o_acc, lse_acc) <- exact merge with the partial that attn_fwd computes, in place and in the
-    same kernel; optional bf16 copy of the merged O.  q, k, v and planned as in attn_fwd."""
-    nqh = p.nq * p.n_heads
+    same kernel; optional bf16 copy of the merged O.  q, k, v, planned and scratch as in attn_fwd."""
+    _fwd("hydra_attn_fwd_merge", True, p, q, k, v, o_acc, lse_acc, workspace, o_bf16, stream, planned, scratch)
+
+
+def _bwd(what: str, p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, ds_buf, workspace,
+         stream, planned, scratch):
+    nqh, nkh = p.nq * p.n_heads, p.nk * p.n_kv_heads
     qp, kp, vp = _set_rows(p, q, k, v)
-    _check(lib().hydra_attn_fwd_merge(p.ref, qp, kp, vp, _ptr(o_acc, "o_acc", _F32, nqh * 128),
-                                      _ptr(lse_acc, "lse_acc", _F32, nqh), _ptr(o_bf16, "o_bf16", _BF16, nqh * 128),
+    _check(lib().hydra_attn_bwd_split(p.ref, qp, kp, vp, _ptr(o_final_bf16, "o_final", _BF16, nqh * 128),
+                                      _ptr(lse_final, "lse_final", _F32, nqh), _ptr(d_o, "d_o", _BF16, nqh * 128),
+                                      _ptr(dq_acc, "dq_acc", _F32, nqh * 192), _ptr(dk_acc, "dk_acc", _F32, nkh * 192),
+                                      _ptr(dv_acc, "dv_acc", _F32, nkh * 128), _ptr(ds_buf, "ds_buf"),
+                                      0 if ds_buf is None else ds_buf.numel() * ds_buf.element_size(),
                                       _ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
-                                      int(planned), _stream(stream)), "hydra_attn_fwd_merge")
+                                      *_scratch(scratch), int(planned), _stream(stream)), what)
 
 
 def attn_bwd(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, workspace,
-             stream=None, planned=False):
-    """dQ/dK/dV of one ring step, accumulated (+=) into fp32 buffers (q, k, v and planned as
-    in attn_fwd)."""
-    nqh, nkh = p.nq * p.n_heads, p.nk * p.n_kv_heads
-    qp, kp, vp = _set_rows(p, q, k, v)
-    fn = lib().hydra_attn_bwd_planned if planned else lib().hydra_attn_bwd
-    _check(fn(p.ref, qp, kp, vp, _ptr(o_final_bf16, "o_final", _BF16, nqh * 128),
-                                _ptr(lse_final, "lse_final", _F32, nqh), _ptr(d_o, "d_o", _BF16, nqh * 128),
-                                _ptr(dq_acc, "dq_acc", _F32, nqh * 192), _ptr(dk_acc, "dk_acc", _F32, nkh * 192),
-                                _ptr(dv_acc, "dv_acc", _F32, nkh * 128), _ptr(workspace, "workspace"),
-                                workspace.numel() * workspace.element_size(), _stream(stream)),
-           "hydra_attn_bwd")
+             stream=None, planned=False, scratch=None):
+    """dQ/dK/dV of one ring step, accumulated (+=) into fp32 buffers (q, k, v, planned and scratch
+    as in attn_fwd)."""
+    _bwd("hydra_attn_bwd", p, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, None, workspace, stream,
+         planned, scratch)
 
 
 def attn_bwd_noalloc(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, stream=None):
@@ -345,18 +369,11 @@ def bwd_ds_bytes(p: Problem, kv_heads_per_pass: int) -> int:
 
 
 def attn_bwd_ds(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, ds_buf, workspace,
-                stream=None):
+                stream=None, scratch=None):
     """attn_bwd with dQ from the dS the dK/dV kernel stores into ds_buf (a uint8 device
     tensor; None or too small: the recompute path)."""
-    nqh, nkh = p.nq * p.n_heads, p.nk * p.n_kv_heads
-    qp, kp, vp = _set_rows(p, q, k, v)
-    _check(lib().hydra_attn_bwd_ds(p.ref, qp, kp, vp, _ptr(o_final_bf16, "o_final", _BF16, nqh * 128),
-                                   _ptr(lse_final, "lse_final", _F32, nqh), _ptr(d_o, "d_o", _BF16, nqh * 128),
-                                   _ptr(dq_acc, "dq_acc", _F32, nqh * 192), _ptr(dk_acc, "dk_acc", _F32, nkh * 192),
-                                   _ptr(dv_acc, "dv_acc", _F32, nkh * 128), _ptr(ds_buf, "ds_buf"),
-                                   0 if ds_buf is None else ds_buf.numel() * ds_buf.element_size(),
-                                   _ptr(workspace, "workspace"), workspace.numel() * workspace.element_size(),
-                                   _stream(stream)), "hydra_attn_bwd_ds")
+    _bwd("hydra_attn_bwd_ds", p, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, ds_buf, workspace,
+         stream, False, scratch)
 
 
 def lse_merge(o_acc, lse_acc, o_part, lse_part, o_bf16=None, stream=None):

@@ -28,6 +28,7 @@ class Share:
     lse_acc: torch.Tensor
     o_bf16: torch.Tensor
     ds_buf: Optional[torch.Tensor] = None   # dS scratch of the stored-dS backward
+    scratch: Optional[torch.Tensor] = None  # of the split work items, shared by the steps, which run in order
 
     @property
     def nq(self) -> int:
@@ -72,6 +73,7 @@ def make_share(cu_seqlens, n_heads: int, q_segs, kv_steps: Sequence, device="cud
     if ds_kv_heads <= 0 and ds_budget_bytes > 0:
         ds_kv_heads = ds_kv_heads_within(probs, ds_budget_bytes)
     ds = max(hydra.bwd_ds_bytes(p, ds_kv_heads) for p in probs) if ds_kv_heads > 0 else 0
+    split = max(hydra.split_scratch_size(p) for p in probs)
     f32 = dict(dtype=torch.float32, device=device)
     return Share(
         problems=probs,
@@ -82,6 +84,7 @@ def make_share(cu_seqlens, n_heads: int, q_segs, kv_steps: Sequence, device="cud
         lse_acc=torch.empty((n_heads, nq), **f32),
         o_bf16=torch.empty((nq, n_heads, D_V), dtype=torch.bfloat16, device=device),
         ds_buf=torch.empty(ds, dtype=torch.uint8, device=device) if ds > 0 else None,
+        scratch=torch.empty(split, dtype=torch.uint8, device=device) if split > 0 else None,
     )
 
 
@@ -105,10 +108,10 @@ def forward(sh: Share, q: torch.Tensor, kv: Sequence[Tuple[torch.Tensor, torch.T
         ws = _ws(sh, i, planned)
         if i == 0:
             hydra.attn_fwd(p, q, k, v, sh.o_acc, sh.lse_acc, ws, o_bf16=sh.o_bf16 if n == 1 else None,
-                           planned=planned)
+                           planned=planned, scratch=sh.scratch)
         else:
             hydra.attn_fwd_merge(p, q, k, v, sh.o_acc, sh.lse_acc, ws, o_bf16=sh.o_bf16 if i == n - 1 else None,
-                                 planned=planned)
+                                 planned=planned, scratch=sh.scratch)
     return sh.o_acc, sh.lse_acc, sh.o_bf16
 
 
@@ -117,7 +120,8 @@ def backward(sh: Share, q, kv, d_o, dq: torch.Tensor, dkv: Sequence[Tuple[torch.
     """Accumulates dQ (over steps) and each step's dK/dV; buffers are += targets."""
     for i, (p, (k, v), (dk, dv)) in enumerate(zip(sh.problems, kv, dkv)):
         if sh.ds_buf is not None and not planned:
-            hydra.attn_bwd_ds(p, q, k, v, sh.o_bf16, sh.lse_acc, d_o, dq, dk, dv, sh.ds_buf, sh.workspace)
+            hydra.attn_bwd_ds(p, q, k, v, sh.o_bf16, sh.lse_acc, d_o, dq, dk, dv, sh.ds_buf, sh.workspace,
+                              scratch=sh.scratch)
         else:
             hydra.attn_bwd(p, q, k, v, sh.o_bf16, sh.lse_acc, d_o, dq, dk, dv, _ws(sh, i, planned),
-                           planned=planned)
+                           planned=planned, scratch=sh.scratch)

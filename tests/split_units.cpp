@@ -1,5 +1,5 @@
 // Split launch lists of random problems: each item's tiles are covered once by its units, in
-// order; parts are numbered without gaps and fit the scratch; the merges name them; the list
+// order; parts are numbered without gaps; the merges name them; the list
 // fits its workspace region.  And the plan images: what a forward's upload writes is what the
 // complete plan has there.  Built with g++ (no GPU code) by tests/test_split_units.py.
 #include <algorithm>
@@ -44,15 +44,25 @@ int main() {
     Problem pr;
     CHECK(check_problem(&p, &pr) == HYDRA_OK);
     const WsLayout w = ws_layout(pr);
-    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.noalloc_total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
-    PlanImage all, fwd;
-    plan_image(pr, w, true, &all);
-    plan_image(pr, w, false, &fwd);
+    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
+    PlanImage all, bwd, fwd, whole_only;
+    plan_image(pr, w, PlanFor::kStoredDs, true, &all);
+    plan_image(pr, w, PlanFor::kBackward, true, &bwd);
+    plan_image(pr, w, PlanFor::kForward, true, &fwd);
+    plan_image(pr, w, PlanFor::kStoredDs, false, &whole_only);
+    CHECK(bwd.off >= all.off && bwd.off + bwd.bytes.size() == all.off + all.bytes.size());
+    CHECK(std::equal(bwd.bytes.begin(), bwd.bytes.end(), all.bytes.begin() + int64_t(bwd.off - all.off)));
+    CHECK(bwd.kv.units_off == all.kv.units_off && bwd.dq.units_off == all.dq.units_off && bwd.fwd.units_off == all.fwd.units_off);
     CHECK(all.off + all.bytes.size() <= w.d_off && fwd.off >= all.off);
     CHECK(fwd.off + fwd.bytes.size() <= all.off + all.bytes.size());
     CHECK(std::equal(fwd.bytes.begin(), fwd.bytes.end(), all.bytes.begin() + int64_t(fwd.off - all.off)));
     CHECK(fwd.fwd.units == all.fwd.units && fwd.fwd.units_off == all.fwd.units_off && fwd.dq.units + fwd.kv.units == 0);
     CHECK(fwd.fwd.merges == all.fwd.merges && fwd.fwd.merges_off == all.fwd.merges_off);
+    CHECK(whole_only.off == all.off && whole_only.bytes.size() <= all.bytes.size());
+    CHECK(std::equal(whole_only.bytes.begin(), whole_only.bytes.end(), all.bytes.begin()));
+    CHECK(whole_only.fwd.units + whole_only.dq.units + whole_only.kv.units == 0);
+    CHECK(split_scratch_bytes(pr) == std::max(parts_bytes(Kernel::kFwd, all.fwd, pr.H),
+                                              parts_bytes(Kernel::kDkdv, all.kv, pr.Hkv) + parts_bytes(Kernel::kDq, all.dq, pr.H)));
     size_t list_bytes = 0;
     Ahead ahead;  // dQ goes behind dK/dV
     for (Kernel k : {Kernel::kFwd, Kernel::kDkdv, Kernel::kDq}) {
@@ -79,10 +89,8 @@ int main() {
       list_bytes += (l.merges.size() * 4 + 255) / 256 * 256 + (l.units.size() * 4 + 255) / 256 * 256;
       CHECK(w.lists_off + list_bytes <= w.d_off);
       CHECK(l.merges.size() <= size_t(kMaxMerges) * kMergeInts);
-      const size_t part = k == Kernel::kFwd ? FWD_PART_BYTES : k == Kernel::kDq ? DQ_PART_BYTES : KV_PART_BYTES;
-      CHECK(w.noalloc_total >= w.split_off + size_t(l.parts) * size_t(heads) * part);
-      CHECK(w.total >= (k == Kernel::kDkdv ? w.kv_split_off : w.split_off) + size_t(l.parts) * size_t(heads) * part);
-      CHECK(k != Kernel::kDq || w.kv_split_off >= w.split_off + size_t(l.parts) * size_t(heads) * part);
+      const ListSize& z = k == Kernel::kFwd ? all.fwd : k == Kernel::kDq ? all.dq : all.kv;
+      CHECK(z.parts == l.parts && size_t(z.units) * kUnitInts == l.units.size());
       // the units of every item, by first row, in the order of their tiles
       std::map<int32_t, std::vector<const int32_t*>> by_row;
       for (size_t i = 0; i < l.units.size(); i += kUnitInts) by_row[l.units[i]].push_back(&l.units[i]);

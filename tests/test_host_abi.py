@@ -173,6 +173,44 @@ def test_planned_calls_refuse_an_unplanned_workspace():
     assert L.hydra_attn_bwd_planned(p.ref, q, k, v, of, lf, do, dq, dk, dv, w, ws, None) == -4
 
 
+def test_workspace_holds_smaller_problems():
+    """A workspace sized for a problem serves every one of fewer rows and no more heads; the plan adds
+    little to D and LSE*log2(e); the parts of split items are not in it."""
+    for H in (1, 2, 16):
+        last = 0
+        for n in (1, 64, 512, 2048, 2049, 32768, 65003, 130000, 131072, 200000):
+            p = _problem([0, n], H, [(0, n)], [(0, n)])
+            ws = hydra.workspace_size(p)
+            assert last <= ws <= 8 * n * H + 8 * n + (320 << 10)
+            last = ws
+        assert hydra.workspace_size(_problem([0, 32768], 1, [(0, 32768)], [(0, 32768)])) <= ws
+    # three documents in 2K rows x 16 heads split the forward alone, by 12 parts a head of eight waves' 32
+    # rows of O with their running max and sum; one head splits all; 128K x 16 heads nothing
+    size = lambda cu, h: hydra.split_scratch_size(_problem(cu, h, [(0, cu[-1])], [(0, cu[-1])]))  # noqa: E731
+    assert size([0, 716, 1001, 2048], 16) == 12 * 16 * 8 * (32 * 128 + 2 * 64) * 4
+    assert 36 << 20 < size([0, 65536], 1) <= 88 << 20 and size([0, 131072], 16) == 0
+    assert hydra.split_scratch_size(_problem([0, 100], 0, [(0, 10)], [(0, 10)])) == 0
+
+
+def test_scratch_checked_on_host():
+    """The scratch of the split calls is an output of its whole size; a planned backward stores no dS."""
+    L = hydra.lib()
+    p = _problem([0, 64], 2, [(0, 64)], [(0, 64)])
+    ws = hydra.workspace_size(p)
+    M = 1 << 24
+    q, k, v, o, lse, w, sc = (M * i for i in range(1, 8))
+    fwd = lambda s, n: L.hydra_attn_fwd_split(p.ref, q, k, v, o, lse, None, w, ws, s, n, 0, 1, None)  # noqa: E731
+    assert fwd(sc + 8, 1 << 20) == -3
+    assert fwd(sc, 1 << 20) == -4                  # unplanned workspace
+    assert fwd(o - 4096, 8192) == -1 and fwd(w + ws - 16, 4096) == -1 and fwd(k, 16) == -1
+    dq, dk, dv, of, lf, do = (M * i for i in range(8, 14))
+    bwd = lambda ds, s, n, planned: L.hydra_attn_bwd_split(p.ref, q, k, v, of, lf, do, dq, dk, dv, ds, 1 << 20 if ds else 0,  # noqa: E731
+                                                           w, ws, s, n, planned, None)
+    assert bwd(M * 20, None, 0, 1) == -1
+    assert bwd(None, sc, 1 << 20, 1) == -4
+    assert bwd(None, dv + 64 * 2 * 128 * 4 - 16, 4096, 1) == -1
+
+
 def test_noalloc_backward_checks_before_any_hip_call():
     """The no-allocation backward rejects malformed problems (-1) and problems whose
     workspace exceeds its 32 MiB scratch (-6) on the host; nothing is dereferenced."""
