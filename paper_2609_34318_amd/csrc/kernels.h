@@ -36,7 +36,6 @@ typedef __attribute__((address_space(3))) char lds_char;
 constexpr int DQK = 192;
 constexpr int DV = 128;
 constexpr int ITEM_INTS = 16;
-constexpr int UNIT_INTS = 32;
 constexpr int MAX_RANGES = 4;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
@@ -579,18 +578,18 @@ __device__ __forceinline__ void xcd_head_item(int b, int n_heads, int n_items, i
   }
 }
 
-// A work item's launch record (32 ints, see launch_units), read once into scalar registers.
+// A work item's launch record (see tiles.h), read once into scalar registers.
 // Plain scalar members only: an array here would be placed in scratch memory and indexed
 // dynamically.
 struct Item {
   int row0, pos0, n, nr;
   int r0, p0, c0, r1, p1, c1, r2, p2, c2, r3, p3, c3;
-  int edge0, lo_last, d0, d1;  // document boundary of the first row, start of the last row's, their indices
-  int ds_slot;                 // key items: first dS slot
-  int t0, t1, part;            // tiles of the walk (t1 < 0: to its end), part of a split item or -1
+  int edge0, d0, d1;  // document boundary of the first row, documents of the first and the last row
+  int ds_slot;        // key items: first dS slot
+  int t0, t1, part;   // tiles of the walk (t1 < 0: to its end), part of a split item or -1
 
   __device__ __forceinline__ Item(const int* items, int idx) {
-    const int* s = items + (int64_t)idx * UNIT_INTS;
+    const int* s = items + (int64_t)idx * REC_INTS;
     row0 = __builtin_amdgcn_readfirstlane(s[0]);
     pos0 = __builtin_amdgcn_readfirstlane(s[1]);
     n = __builtin_amdgcn_readfirstlane(s[2]);
@@ -607,14 +606,13 @@ struct Item {
     r3 = __builtin_amdgcn_readfirstlane(s[13]);
     p3 = __builtin_amdgcn_readfirstlane(s[14]);
     c3 = nr > 3 ? __builtin_amdgcn_readfirstlane(s[15]) : 0;
-    edge0 = __builtin_amdgcn_readfirstlane(s[16]);
-    lo_last = __builtin_amdgcn_readfirstlane(s[17]);
-    d0 = __builtin_amdgcn_readfirstlane(s[18]);
-    d1 = __builtin_amdgcn_readfirstlane(s[19]);
-    ds_slot = __builtin_amdgcn_readfirstlane(s[20]);
-    t0 = __builtin_amdgcn_readfirstlane(s[24]);
-    t1 = __builtin_amdgcn_readfirstlane(s[25]);
-    part = __builtin_amdgcn_readfirstlane(s[26]);
+    edge0 = __builtin_amdgcn_readfirstlane(s[REC_EDGE]);
+    d0 = __builtin_amdgcn_readfirstlane(s[REC_DOC0]);
+    d1 = __builtin_amdgcn_readfirstlane(s[REC_DOC1]);
+    ds_slot = __builtin_amdgcn_readfirstlane(s[REC_SLOT]);
+    t0 = __builtin_amdgcn_readfirstlane(s[REC_T0]);
+    t1 = __builtin_amdgcn_readfirstlane(s[REC_T1]);
+    part = __builtin_amdgcn_readfirstlane(s[REC_PART]);
   }
 };
 

@@ -195,12 +195,11 @@ void launch_units(const Problem& pr, int which, const std::vector<int32_t>& item
     int32_t* u = &(*units)[i * kUnitInts];
     std::copy(it, it + kItemInts, u);
     const int d0 = doc_index(pr.cu, it[1]), d1 = doc_index(pr.cu, int64_t(it[1]) + it[2] - 1);
-    u[16] = which == 0 ? pr.cu[d0] : pr.cu[d0 + 1];
-    u[17] = pr.cu[d1];
-    u[18] = d0;
-    u[19] = d1;
-    u[25] = u[26] = -1;
-    if (!kbase.empty()) u[20] = kbase[i];
+    u[REC_EDGE] = which == 0 ? pr.cu[d0] : pr.cu[d0 + 1];
+    u[REC_DOC0] = d0;
+    u[REC_DOC1] = d1;
+    u[REC_T1] = u[REC_PART] = -1;
+    if (!kbase.empty()) u[REC_SLOT] = kbase[i];
   }
 }
 
@@ -238,7 +237,7 @@ Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& 
   const double group = split_cost(kernel).group;
   for (size_t i = 0; i < units.size(); i += kUnitInts) {
     const int32_t* u = &units[i];
-    const double t = group + double(u[25] < 0 ? record_tiles(pr, kernel, u) : u[25] - u[24]);
+    const double t = group + double(u[REC_T1] < 0 ? record_tiles(pr, kernel, u) : u[REC_T1] - u[REC_T0]);
     a.sum += t * heads;
     a.longest = std::max(a.longest, t);
     a.shortest = i == 0 ? t : std::min(a.shortest, t);
@@ -306,9 +305,9 @@ void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& r
     for (int64_t j = 0; j < k; ++j) {
       const size_t at = out->units.size();
       out->units.insert(out->units.end(), u, u + kUnitInts);
-      out->units[at + 24] = int32_t(t * j / k);
-      out->units[at + 25] = k > 1 ? int32_t(t * (j + 1) / k) : -1;
-      out->units[at + 26] = k > 1 ? out->parts++ : -1;
+      out->units[at + REC_T0] = int32_t(t * j / k);
+      out->units[at + REC_T1] = k > 1 ? int32_t(t * (j + 1) / k) : -1;
+      out->units[at + REC_PART] = k > 1 ? out->parts++ : -1;
       order.push_back({t * (j + 1) / k - t * j / k, at});
     }
   }

@@ -14,7 +14,7 @@ constexpr int kDv = 128;
 constexpr int kQTile = 256;    // query rows per query-stationary workgroup (8 waves x 32)
 constexpr int kKvTile = 128;   // key rows per key-stationary workgroup (4 waves x 32)
 constexpr int kItemInts = 16;  // int32 per work item
-constexpr int kUnitInts = 32;  // int32 per launch record: a work item and what its kernel would else look up
+constexpr int kUnitInts = REC_INTS;  // int32 per launch record: a work item and what its kernel would else look up
 
 // Checked and normalised view of a hydra_problem_t.
 struct Problem {
@@ -62,20 +62,16 @@ constexpr size_t kListBytes = (size_t(kMaxMerges) * kMergeInts + size_t(MAX_PART
 static_assert(kListBytes % 256 == 0, "lists end on a region boundary");
 
 // Splits the items of a launch over `heads` heads whose workgroups leave the chip idle (`records`
-// from launch_units).  A unit is a record with [24], [25] its first and last + 1 tile of the
-// item's walk (for dK/dV: of its group * tiles) and [26] its part, or -1 when it is the whole item.
+// from launch_units).  A unit is a record with the tiles of its part, or that of the whole item.
 // `ahead`: the workgroups that the same launch starts before these.
 void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, UnitList* out,
                  const Ahead& ahead = Ahead{});
 // The launch of a list (of the whole `records` when it has no units) as what is ahead of another.
 Ahead launch_load(const Problem& pr, Kernel kernel, const std::vector<int32_t>& records, int heads, const UnitList& list);
 
-// The launch records of plan_items' work items, in the same order (kUnitInts each): the
-// item's 16 ints, then [16] the document boundary of its first row (its start for query
-// items, its end for key items), [17] the start of its last row's document, [18], [19] the
-// document indices of its first and last row, [20] of a key item its first dS slot (`kbase`, see
-// ds_tables); [24] = 0, [25] = -1 (all tiles), [26] = -1 (whole).  A kernel that reads one record
-// instead of searching cu_seqlens has one memory round trip before its first copy, not several.
+// The launch records (tiles.h) of plan_items' work items, in the same order, as whole items.  A kernel
+// that reads one record instead of searching cu_seqlens has one memory round trip before its first
+// copy, not several.  kbase: the first dS slot of each key item (ds_tables).
 // `kbase` is empty for query items: their records hold nothing of the key side, so that they are
 // the same whether or not the key side is planned (plan_image).
 void launch_units(const Problem& pr, int which, const std::vector<int32_t>& items,

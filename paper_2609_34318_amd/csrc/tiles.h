@@ -15,6 +15,18 @@ constexpr int DS_TILE_BYTES = (KV_QTILE_ROWS / 32) * 4 * DS_BLOCK_BYTES;  // 24 
 constexpr int FWD_TILE_ROWS = 64;
 constexpr int DQ_TILE_ROWS = 96;
 
+// Launch records: the 16 ints of a work item, then (launch_units in plan.h)
+enum Record {
+  REC_EDGE = 16,  // document boundary of the first row: its start for query items, its end for key items
+  REC_DOC0,       // document indices of the first and the last row
+  REC_DOC1,
+  REC_SLOT,       // key items: first dS slot
+  REC_T0,         // first tile of the walk and the one past the last (-1: all tiles); for dK/dV of its
+  REC_T1,         // group * tiles
+  REC_PART,       // part of a split item, or -1
+  REC_INTS = 24
+};
+
 // A work item split over several workgroups: each leaves its accumulators in a part of the
 // caller's scratch, as its registers hold them (one 1 KB row of 64 lanes x 16 bytes per four
 // registers).  Per wave: 32 rows x 128 (O, with two more rows for the running max and sum, or

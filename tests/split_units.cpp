@@ -101,7 +101,7 @@ int main() {
         int64_t t = 0;
         for (int r = 0; r < u[3]; ++r) t += (u[4 + 3 * r + 2] + rows - 1) / rows;
         if (k == Kernel::kDkdv) t *= pr.H / pr.Hkv;
-        const int64_t n = (u[25] < 0 ? t : u[25]) - u[24];
+        const int64_t n = (u[REC_T1] < 0 ? t : u[REC_T1]) - u[REC_T0];
         CHECK(n <= last);
         last = n;
         longest = std::max(longest, n);
@@ -111,10 +111,10 @@ int main() {
         const int32_t* it = &rec[i];
         auto& us = by_row[it[0]];
         CHECK(!us.empty());
-        for (const int32_t* u : us) CHECK(std::equal(it, it + 24, u));
-        std::sort(us.begin(), us.end(), [](const int32_t* a, const int32_t* b) { return a[24] < b[24]; });
+        for (const int32_t* u : us) CHECK(std::equal(it, it + REC_T0, u));
+        std::sort(us.begin(), us.end(), [](const int32_t* a, const int32_t* b) { return a[REC_T0] < b[REC_T0]; });
         if (us.size() == 1) {
-          CHECK(us[0][24] == 0 && us[0][25] == -1 && us[0][26] == -1);
+          CHECK(us[0][REC_T0] == 0 && us[0][REC_T1] == -1 && us[0][REC_PART] == -1);
           continue;
         }
         int64_t t = 0;
@@ -122,15 +122,15 @@ int main() {
         if (k == Kernel::kDkdv) t *= pr.H / pr.Hkv;
         int32_t next = 0;
         for (size_t j = 0; j < us.size(); ++j) {
-          CHECK(us[j][24] == next && us[j][25] > next && us[j][26] == us[0][26] + int32_t(j));
-          next = us[j][25];
-          ++used[size_t(us[j][26])];
+          CHECK(us[j][REC_T0] == next && us[j][REC_T1] > next && us[j][REC_PART] == us[0][REC_PART] + int32_t(j));
+          next = us[j][REC_T1];
+          ++used[size_t(us[j][REC_PART])];
         }
         CHECK(next == t);
         bool named = false;
         for (size_t g = 0; g < l.merges.size(); g += kMergeInts)
           if (l.merges[g] == it[0])
-            named = l.merges[g + 1] == it[2] && l.merges[g + 2] == us[0][26] && l.merges[g + 3] == int32_t(us.size());
+            named = l.merges[g + 1] == it[2] && l.merges[g + 2] == us[0][REC_PART] && l.merges[g + 3] == int32_t(us.size());
         CHECK(named);
         ++n_merges;
       }
