@@ -47,7 +47,7 @@ extern "C" {
 #define HYDRA_ERR_ALIGN         -3  /* a device pointer is not 16-byte aligned */
 #define HYDRA_ERR_WORKSPACE     -4  /* workspace NULL or smaller than hydra_workspace_size() */
 #define HYDRA_ERR_HIP           -5  /* a HIP runtime call or kernel launch failed */
-#define HYDRA_ERR_TOO_LARGE     -6  /* beyond the no-allocation call's scratch (see below) */
+#define HYDRA_ERR_TOO_LARGE     -6  /* beyond the no-allocation call's limit (see below)   */
 
 #define HYDRA_MAX_SEGS 4
 
@@ -189,16 +189,20 @@ size_t hydra_bwd_ds_bytes(const hydra_problem_t* p, int32_t kv_heads_per_pass);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): hydra_attn_bwd without the workspace
  * argument.  The workspace (plan, D, LSE*log2(e)) lives in a device array of the library,
- * one per GPU, held until the process ends; the call allocates nothing.  Problems whose D,
- * LSE*log2(e), documents and tile plan exceed hydra_noalloc_scratch_bytes() = 32 MiB are
- * refused with HYDRA_ERR_TOO_LARGE before any HIP call (32 MiB covers n_heads x Nq up to about 4M, e.g.
- * 16 heads x 256K rows).  Every call on a GPU uses that GPU's one array: calls that overlap
+ * one of 32.5 MiB per GPU, held until the process ends; the call allocates nothing.  Problems whose
+ * hydra_noalloc_size() exceeds hydra_noalloc_scratch_bytes() = 32 MiB are refused with
+ * HYDRA_ERR_TOO_LARGE before any HIP call.  hydra_noalloc_size() counts 4 bytes each for D and
+ * LSE*log2(e) per row and head, 4 per document boundary, 64 per 256 query rows and 64 + 64 + 4 per
+ * 128 key rows (per part of them, in each segment) and 4 per 32 key rows, each of these rounded up to
+ * 256: n_heads x Nq below about 4M, e.g. 16 heads x 250K rows (16 x 256K is just beyond).  0: `p` is
+ * invalid.  Every call on a GPU uses that GPU's one array: calls that overlap
  * on one GPU (other streams, other threads) race and must be serialised by the caller.
  * Everything else (arguments, checks, results) is hydra_attn_bwd's, bit for bit. */
 int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* k, const void* v,
                            const void* o_final, const float* lse_final, const void* d_o,
                            float* dq_acc, float* dk_acc, float* dv_acc, void* stream);
 size_t hydra_noalloc_scratch_bytes(void);
+size_t hydra_noalloc_size(const hydra_problem_t* p);
 
 /* For callers that record the calls into a HIP graph (stream capture), where the plan's
  * host-to-device copy cannot be recorded: hydra_attn_plan uploads the complete work plan of

@@ -288,7 +288,7 @@ uint64_t ds_bytes_per_head(const Problem& pr) {
 int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const void* k, const void* v,
                   const void* o_final, const float* lse_final, const void* d_o, float* dq_acc, float* dk_acc,
                   float* dv_acc, void* ds_buf, size_t ds_bytes, void* workspace, size_t workspace_bytes, Scratch scratch,
-                  void* stream) {
+                  void* stream, bool noalloc = false) {
   try {
     Problem pr;
     int rc = check_problem(p, &pr);
@@ -298,7 +298,7 @@ int attn_bwd_impl(bool upload, const hydra_problem_t* p, const void* q, const vo
                   check_ptr(lse_final, true), check_ptr(d_o, true), check_ptr(dq_acc, true),
                   check_ptr(dk_acc, true), check_ptr(dv_acc, true), scratch.at ? check_ptr(scratch.at, true) : HYDRA_OK})
       if (c != HYDRA_OK) return c;
-    const WsLayout w = ws_layout(pr);
+    const WsLayout w = ws_layout(pr, noalloc);
     if (!workspace || workspace_bytes < w.total) return HYDRA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HYDRA_ERR_ALIGN;
     // stored-dS path: K/V heads per pass such that their query heads' dS fits ds_buf
@@ -448,6 +448,15 @@ extern "C" {
 
 size_t hydra_noalloc_scratch_bytes(void) { return kNoAllocLimitBytes; }
 
+size_t hydra_noalloc_size(const hydra_problem_t* p) {
+  try {
+    Problem pr;
+    return check_problem(p, &pr) == HYDRA_OK ? size_t(noalloc_bytes(pr)) : 0;
+  } catch (...) {
+    return 0;
+  }
+}
+
 int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* k, const void* v,
                            const void* o_final, const float* lse_final, const void* d_o, float* dq_acc,
                            float* dk_acc, float* dv_acc, void* stream) {
@@ -459,7 +468,7 @@ int hydra_attn_bwd_noalloc(const hydra_problem_t* p, const void* q, const void* 
     void* ws = nullptr;
     if ((rc = scratch_ptr(&ws)) != HYDRA_OK) return rc;
     return attn_bwd_impl(true, p, q, k, v, o_final, lse_final, d_o, dq_acc, dk_acc, dv_acc, nullptr, 0, ws,
-                         kNoAllocScratchBytes, Scratch{}, stream);
+                         kNoAllocScratchBytes, Scratch{}, stream, true);
   } catch (...) {
     return HYDRA_ERR_INVALID;
   }
@@ -529,7 +538,7 @@ const char* hydra_strerror(int status) {
     case HYDRA_ERR_WORKSPACE: return "workspace missing or too small";
     case HYDRA_ERR_HIP: return "HIP runtime error";
     case HYDRA_ERR_TOO_LARGE:
-      return "problem needs more workspace than the no-allocation call's 32 MiB scratch holds";
+      return "problem needs more workspace than the no-allocation call's limit of 32 MiB";
     default: return "unknown status";
   }
 }

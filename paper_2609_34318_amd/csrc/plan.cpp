@@ -389,16 +389,16 @@ uint64_t noalloc_bytes(const Problem& pr) {
   return n;
 }
 
-WsLayout ws_layout(const Problem& pr) {
+WsLayout ws_layout(const Problem& pr, bool noalloc) {
   WsLayout w{};
   const int64_t nqt = n_tiles(pr.q, kQTile), nkt = n_tiles(pr.kv, kKvTile);
   w.n_qitems = nqt;
   w.n_kitems = nkt;
   size_t off = 0;
   w.krec_off = off;
-  off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
+  if (!noalloc) off = align_up(off + size_t(nkt) * kItemInts * sizeof(int32_t), 256);
   w.qslots_off = off;
-  off = align_up(off + size_t(nqt) * HYDRA_MAX_SEGS * sizeof(int32_t), 256);
+  if (!noalloc) off = align_up(off + size_t(nqt) * HYDRA_MAX_SEGS * sizeof(int32_t), 256);
   w.kitems_off = off;
   off = align_up(off + size_t(nkt) * kUnitInts * sizeof(int32_t), 256);
   w.cu_off = off;
@@ -406,7 +406,7 @@ WsLayout ws_layout(const Problem& pr) {
   w.qitems_off = off;
   off = align_up(off + size_t(nqt) * kUnitInts * sizeof(int32_t), 256);
   w.lists_off = off;
-  off += 3 * kListBytes;
+  if (!noalloc) off += 3 * kListBytes;
   w.d_off = off;
   off = align_up(off + size_t(pr.H) * size_t(pr.nq) * sizeof(float), 256);
   w.lse2_off = off;

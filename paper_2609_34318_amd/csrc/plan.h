@@ -81,12 +81,13 @@ void launch_units(const Problem& pr, int which, const std::vector<int32_t>& item
 // (krec, qslots), the key items, what the forward reads too (cu, qitems, and at lists the forward's
 // split list), the backward's split lists, D and LSE*log2(e).  lists holds the split lists that a plan has, one after
 // another (merges, then units); it has the same size for every problem, so that no problem needs
-// more workspace than one with more rows.
+// more workspace than one with more rows.  For the no-allocation call, which stores no dS and splits
+// nothing, those regions are empty.
 struct WsLayout {
   size_t krec_off, qslots_off, kitems_off, cu_off, qitems_off, lists_off, d_off, lse2_off, total;
   int64_t n_qitems, n_kitems;
 };
-WsLayout ws_layout(const Problem& pr);
+WsLayout ws_layout(const Problem& pr, bool noalloc = false);
 
 // A split list in the workspace; no units: the whole items are launched.
 struct ListSize {
@@ -115,12 +116,14 @@ uint64_t parts_bytes(Kernel kernel, const ListSize& l, int heads);
 uint64_t split_scratch_bytes(const Problem& pr);
 
 // What the no-allocation backward's 32 MiB limit is counted on: D, LSE*log2(e), the documents,
-// 64 bytes per query tile, 148 per key tile (its item, its record, its dS slot and its 32-key
-// blocks).  The launch records and the lists' region take more than that: kNoAllocExtraBytes holds
-// it for every problem within the limit.
+// 64 bytes per query tile, 148 per key tile (128 rows; 4 for each 32 of them), each to 256 bytes.
 uint64_t noalloc_bytes(const Problem& pr);
 constexpr size_t kNoAllocLimitBytes = size_t(32) << 20;
-constexpr size_t kNoAllocExtraBytes = size_t(12) << 20;
+// A query tile's record takes 32 bytes more than are counted, a key tile's fewer, and a query tile of
+// 256 rows counts at least 64 + 256 * 8 (each of the four segments may end in a shorter one): what the
+// no-allocation workspace of a problem within the limit takes beyond it is at most
+constexpr size_t kNoAllocExtraBytes =
+    (kNoAllocLimitBytes / (64 + kQTile * 8) + HYDRA_MAX_SEGS + 1) * (kUnitInts * 4 - 64) / 256 * 256 + 256;
 
 // The stored-dS backward applies when every segment of both chunks starts and ends on a
 // multiple of 32 positions: the key-stationary tiles then cut the query rows into 32-row

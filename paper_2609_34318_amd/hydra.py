@@ -114,6 +114,8 @@ def lib() -> ctypes.CDLL:
         L.hydra_attn_bwd_noalloc.restype = ctypes.c_int
         L.hydra_noalloc_scratch_bytes.argtypes = []
         L.hydra_noalloc_scratch_bytes.restype = ctypes.c_size_t
+        L.hydra_noalloc_size.argtypes = [P]
+        L.hydra_noalloc_size.restype = ctypes.c_size_t
         L.hydra_attn_plan.argtypes = [P, vp, ctypes.c_size_t, vp]
         L.hydra_attn_plan.restype = ctypes.c_int
         L.hydra_attn_fwd_planned.argtypes = L.hydra_attn_fwd.argtypes
@@ -200,6 +202,11 @@ def workspace_size(p: Problem) -> int:
 def split_scratch_size(p: Problem) -> int:
     """Bytes of scratch for the calls' `scratch` (0: nothing of p is split)."""
     return int(lib().hydra_split_scratch_size(p.ref))
+
+
+def noalloc_size(p: Problem) -> int:
+    """What counts of p against the limit of attn_bwd_noalloc."""
+    return int(lib().hydra_noalloc_size(p.ref))
 
 
 def visible_pairs(p: Problem) -> int:
@@ -351,7 +358,7 @@ def attn_bwd(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, 
 
 def attn_bwd_noalloc(p: Problem, q, k, v, o_final_bf16, lse_final, d_o, dq_acc, dk_acc, dv_acc, stream=None):
     """attn_bwd with the library's own per-GPU scratch as the workspace (allocates nothing;
-    calls on one GPU must not overlap)."""
+    calls on one GPU must not overlap).  For problems whose noalloc_size is within its 32 MiB."""
     nqh, nkh = p.nq * p.n_heads, p.nk * p.n_kv_heads
     qp, kp, vp = _set_rows(p, q, k, v)
     _check(lib().hydra_attn_bwd_noalloc(p.ref, qp, kp, vp, _ptr(o_final_bf16, "o_final", _BF16, nqh * 128),

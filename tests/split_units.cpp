@@ -1,7 +1,7 @@
 // Split launch lists of random problems: each item's tiles are covered once by its units, in
 // order; parts are numbered without gaps; the merges name them; the list
 // fits its workspace region.  And the plan images: what a forward's upload writes is what the
-// complete plan has there.  Built with g++ (no GPU code) by tests/test_split_units.py.
+// complete plan has there.  And the no-allocation call's array, for the largest problems it takes.  Built with g++ (no GPU code) by tests/test_split_units.py.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -44,7 +44,6 @@ int main() {
     Problem pr;
     CHECK(check_problem(&p, &pr) == HYDRA_OK);
     const WsLayout w = ws_layout(pr);
-    CHECK(noalloc_bytes(pr) > kNoAllocLimitBytes || w.total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
     PlanImage all, bwd, fwd, whole_only;
     plan_image(pr, w, PlanFor::kStoredDs, true, &all);
     plan_image(pr, w, PlanFor::kBackward, true, &bwd);
@@ -137,6 +136,38 @@ int main() {
       CHECK(n_merges * kMergeInts == l.merges.size());
       CHECK(std::all_of(used.begin(), used.end(), [](int x) { return x == 1; }));
     }
+  }
+  // the no-allocation call's array at its limit: the most rows that are accepted, where the query
+  // side, the key side or the documents take it, in one segment or four with short last tiles
+  for (int trial = 0; trial < 200; ++trial) {
+    std::vector<int32_t> cu(size_t(trial % 20 == 3 ? uni(1, 4000000) : 1) + 1, 0);
+    cu.back() = 1 << 30;
+    hydra_problem_t p{};
+    p.n_heads = trial % 5 ? int32_t(uni(1, 64)) : 1;
+    p.d_qk = 192;
+    p.d_v = 128;
+    p.cu_seqlens = cu.data();
+    p.n_docs = int32_t(cu.size()) - 1;
+    const bool by_keys = trial % 2;
+    hydra_chunk_t &a = by_keys ? p.kv : p.q, &b = by_keys ? p.q : p.kv;
+    a.n_segs = b.n_segs = trial % 3 ? 4 : 1;
+    for (int s = 0; s < b.n_segs; ++s) b.len[s] = int32_t(uni(0, 300));
+    auto bytes = [&](int64_t rows) {
+      for (int s = 1; s < a.n_segs; ++s) a.len[s] = trial % 7 ? 1 : 257;
+      a.len[0] = int32_t(rows);
+      Problem pr;
+      return check_problem(&p, &pr) == HYDRA_OK ? noalloc_bytes(pr) : UINT64_MAX;
+    };
+    int64_t lo = 0, hi = 1 << 29;
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) / 2;
+      (bytes(mid) <= kNoAllocLimitBytes ? lo : hi) = mid;
+    }
+    CHECK(bytes(lo) <= kNoAllocLimitBytes);
+    Problem pr;
+    CHECK(check_problem(&p, &pr) == HYDRA_OK);
+    CHECK(ws_layout(pr, true).total <= kNoAllocLimitBytes + kNoAllocExtraBytes);
+    CHECK(lo > 1000);
   }
   std::printf("split %d whole %d\n", split, whole);
   return 0;

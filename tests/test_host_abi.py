@@ -224,6 +224,25 @@ def test_noalloc_backward_checks_before_any_hip_call():
     assert L.hydra_strerror(-6).decode().startswith("problem needs more workspace")
 
 
+def test_noalloc_limit_from_both_sides():
+    """hydra_noalloc_size says what the limit counts; the first call beyond is refused for it, the last
+    one within passes on to the next check (no GPU, or here the buffers, all one address)."""
+    L = hydra.lib()
+    size = lambda n, h=16: hydra.noalloc_size(_problem([0, n], h, [(0, n)], [(0, n)]))  # noqa: E731
+    call = lambda n, h=16: L.hydra_attn_bwd_noalloc(_problem([0, n], h, [(0, n)], [(0, n)]).ref, *([16] * 9), None)  # noqa: E731
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    n = 250000
+    tiles = (n + 255) // 256, (n + 127) // 128, (n + 31) // 32
+    assert size(n) == 2 * up(16 * 4 * n) + 256 + up(64 * tiles[0]) + 2 * up(64 * tiles[1]) + up(4 * tiles[1]) + up(4 * tiles[2])
+    lo, hi = 1, 1 << 18
+    assert size(hi) > 32 << 20           # 16 heads x 256K rows
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if size(mid) <= 32 << 20 else (lo, mid)
+    assert lo > 250000 and call(lo) in (-5, -1) and call(hi) == -6
+    assert hydra.noalloc_size(_problem([0, 100], 0, [(0, 10)], [(0, 10)])) == 0
+
+
 def test_binding_refuses_host_tensors():
     """The library takes plain device pointers; the binding refuses a host tensor before
     any call (its address would reach a kernel)."""
