@@ -405,9 +405,19 @@ __device__ __forceinline__ void own_rows_read(const lds_char* buf, int lane, bf1
 // every wave past its last read of the LDS that holds buf.
 constexpr int ROWS_OUT_BYTES = 32 * 256;
 
+// Between LDS accesses of a wave whose lanes exchange data: the lanes of a wave access LDS in program
+// order, and this keeps the compiler, which sees one lane's addresses, from changing that order.  It
+// is no instruction.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 template <int G, int N>
 __device__ __forceinline__ void rows_stage(lds_char* buf, int lane, const f32x16 (&acc)[N], float scale) {
   const int m = lane & 31, h = lane >> 5;
+  wave_lds_order();  // after the reads of the group before
 #pragma unroll
   for (int d = 0; d < 2; ++d)
 #pragma unroll
@@ -417,6 +427,7 @@ __device__ __forceinline__ void rows_stage(lds_char* buf, int lane, const f32x16
       *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(buf + m * 256 +
                                                                    (((8 * d + 2 * rr + h) ^ (m & 15)) << 4)) = v;
     }
+  wave_lds_order();  // before rows_read
 }
 // Row and first column (of the 64) of the 16 bytes that this lane handles in step i of 8.
 __device__ __forceinline__ int rows_row(int lane, int i) { return 4 * i + (lane >> 4); }
