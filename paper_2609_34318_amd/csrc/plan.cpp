@@ -208,8 +208,14 @@ namespace {
 constexpr int kCus = 256;
 
 // In tiles of the kernel's loop: what a workgroup costs besides its tiles (its own rows in, the
-// first copies, its rows out), and the merge launch.  Measured, 2.4 GHz: a forward tile takes
-// 1.7 us, a dQ tile 3.0 us, a dK/dV tile 2.9 us; a workgroup's own cost 4-6 us, a merge 5-7 us.
+// first copies, its rows out), and what a split is charged for its merge.  Measured, 2.4 GHz: a
+// forward tile takes 1.6 to 1.7 us, a dQ tile 3.0 us, a dK/dV tile 2.5 to 2.9 us; a workgroup's own
+// cost 4 to 6 us.  A merge takes longer than it is charged, by its parts (least squares over 150
+// windows and ring steps, whole and in up to 32 parts an item: forward 4.6 us and 0.047 us a part of
+// 132 KB, dK/dV 2.4 us and 0.060 us a part of 160 KB, so up to 17 and 18 us), but charged by the part
+// the choices got worse where dQ fills the chip beside dK/dV (1.5K rows of 16 heads on 2: 81 to
+// 114 us; recompute backward over the windows 3% slower, the forward and the stored-dS backward 1%
+// faster).
 struct SplitCost {
   double group, merge;
 };
@@ -260,7 +266,10 @@ void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& r
   }
   if (longest < 2 * kMinPart) return;
   // The launch's time with items of more than `most` tiles cut into near-equal parts: one round
-  // ends with its longest workgroup; several are filled evenly but for about half a workgroup.
+  // ends with its longest workgroup; several are filled evenly but for about half a workgroup, and
+  // take no less than the shortest of the longest workgroups that must share a CU: two of 257, three
+  // of 513 (16K ring step of 6 heads: 192 workgroups of 128 and 64 tiles take 246 us, as 288 of 64
+  // tiles, which an even share puts at 0.8 times that, 273).
   // Behind a full round of others the first workgroup starts when the shortest of those ends; and
   // where those are merged, a merge is no launch of its own.  (2K rows x 16 heads: dQ alone took
   // 240 parts to fill the chip; behind dK/dV its 128 whole items do.)
@@ -279,7 +288,20 @@ void split_units(const Problem& pr, Kernel kernel, const std::vector<int32_t>& r
     }
     if (ahead.groups + units * heads <= kCus) return std::max(top, ahead.longest);
     const double start = ahead.groups >= kCus ? ahead.shortest : 0;
-    return std::max({start + top, ahead.longest, (ahead.sum + sum * heads) / kCus + 0.5 * sum / double(units)});
+    double t = std::max({start + top, ahead.longest, (ahead.sum + sum * heads) / kCus + 0.5 * sum / double(units)});
+    if (ahead.groups > 0) return t;
+    // workgroups by length, in 128 steps
+    int64_t count[128] = {}, more = 0;
+    for (int64_t x : tiles) {
+      const int64_t k = parts_of(x, most);
+      count[int(127 * (double(x) / double(k) + cost.group) / top)] += k * heads;
+    }
+    int b = 127;
+    for (int64_t r = 1; r * kCus < units * heads; ++r) {
+      while (more + count[b] <= r * kCus) more += count[b--];
+      t = std::max(t, double(r + 1) * top * b / 127);
+    }
+    return t;
   };
   int64_t parts = 0, best_most = longest;
   double best = time_of(longest, &parts);

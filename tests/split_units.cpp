@@ -1,7 +1,7 @@
 // Split launch lists of random problems: each item's tiles are covered once by its units, in
 // order; parts are numbered without gaps; the merges name them; the list
 // fits its workspace region.  And the plan images: what a forward's upload writes is what the
-// complete plan has there.  And the no-allocation call's array, for the largest problems it takes.  Built with g++ (no GPU code) by tests/test_split_units.py.
+// complete plan has there.  And the no-allocation call's array, for the largest problems it takes; and a split that would need a second round.  Built with g++ (no GPU code) by tests/test_split_units.py.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -136,6 +136,26 @@ int main() {
       CHECK(n_merges * kMergeInts == l.merges.size());
       CHECK(std::all_of(used.begin(), used.end(), [](int x) { return x == 1; }));
     }
+  }
+  // 192 workgroups of 128 and of 64 tiles, which 96 of the longer ones cut in two would make two
+  // rounds of the chip: whole
+  {
+    const int trial = -1;
+    int32_t cu[2] = {0, 16384};
+    hydra_problem_t p{};
+    p.n_heads = 6;
+    p.n_kv_heads = 3;
+    p.d_qk = 192;
+    p.d_v = 128;
+    p.cu_seqlens = cu;
+    p.n_docs = 1;
+    p.q = {2, {4096, 12288}, {4096, 4096}};
+    p.kv = {2, {0, 8192}, {4096, 4096}};
+    Problem pr;
+    CHECK(check_problem(&p, &pr) == HYDRA_OK);
+    PlanImage img;
+    plan_image(pr, ws_layout(pr), PlanFor::kBackward, true, &img);
+    CHECK(img.fwd.units == 0);
   }
   // the no-allocation call's array at its limit: the most rows that are accepted, where the query
   // side, the key side or the documents take it, in one segment or four with short last tiles
