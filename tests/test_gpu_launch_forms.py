@@ -1,5 +1,5 @@
 """Forms of one launch against each other: a ring step merged by its own kernel against the partial
-and the merge call; the backward's dQ and dK/dV in one launch against two, split and whole; the
+and the merge call; split work items against whole ones; the
 split dK/dV of the stored-dS passes against the recompute path's; recorded calls before and after an
 upload for the same problem; calls on one plan that overlap."""
 import math
