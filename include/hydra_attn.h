@@ -130,8 +130,8 @@ int hydra_attn_fwd_merge(const hydra_problem_t* p, const void* q, const void* k,
  *   scratch_bytes  its size.  hydra_split_scratch_size(p) holds the parts of every launch of `p`, the
  *                  backward's included (at most 88 MiB; 0: nothing is split); where a launch's
  *                  parts do not fit, its items stay whole.
- * Calls on one plan, which a planned call only reads, may overlap where each has a scratch of its
- * own (or none); calls that share a scratch must not. */
+ * Planned forwards of one plan may overlap, with each other and with one backward, where each call
+ * has a scratch of its own (or none); calls that share a scratch must not overlap. */
 int hydra_attn_fwd_split(const hydra_problem_t* p, const void* q, const void* k, const void* v,
                          float* o, float* lse, void* o_bf16, void* workspace, size_t workspace_bytes,
                          void* scratch, size_t scratch_bytes, int32_t merge, int32_t planned, void* stream);
